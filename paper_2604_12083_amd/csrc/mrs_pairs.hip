@@ -102,9 +102,119 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Sources of one staged round, as the pair loops read them (a wave reads one
+// source at a time, as broadcasts).  w is the anchored position, m = 1.5 w x n
+// and k = w x f the source's parts of the split cross products (far_block),
+// h + l the position in units of eps.
+struct SrcStage {
+    float4 W[kSrcTile];   // w, fx
+    float4 F[kSrcTile];   // fy, fz, nx, ny
+    float4 M[kSrcTile];   // nz, m
+    float4 K[kSrcTile];   // k, lx
+    float4 H[kSrcTile];   // h, ly
+    float lz[kSrcTile];
+};
+
+// Sums of the 64 staged sources from sb on into p, for targets at u relative
+// to the block's anchor (no near pair in the block).
+//
+// The loop is bound by VALU issue (the launch issues one instruction per 2.4
+// clocks and SIMD, its instruction mix allows one per 2.35) and by the clock
+// the card holds under it, so it is written for the fewest instructions per
+// pair:
+//   * The cross products are split along r = u - w: sum H3 (n x r) =
+//     (sum H3 n) x u + sum H3 (w x n), and the same for f, so a pair adds
+//     H3 n, H3 f and H3 m, H3 k with products m, k that the staging forms
+//     once per source, and u enters once per block.
+//   * H4 = u7 - H3/2 with u7 = 3.75 Q^7: its second part is -1/2 of the sum
+//     H3 n already kept.  REMOTE: u7 is below half an ulp of H3/2, and H4 n
+//     needs no sum of its own.
+//   * H3, H5 and u7 are kept divided by 1.5 (one product less); m is staged
+//     times 1.5 and the sums of H3 and of Omega are multiplied once per block.
+// 42 instructions per pair and one v_rsq_f32 (REMOTE; 46 otherwise) against
+// 51 for the direct form: pair kernel 58.1 -> 52.6 ms at 256,000 points, 165
+// -> 151.5 us at 12,800 (one target per lane, MI355X).  Two sources at a time
+// with their reciprocal roots together: 0.7% faster than one at a time at
+// 256,000 points, 2% at 51,000 (swimmers); four at a time spills.
+template <int T, bool REMOTE>
+__device__ __forceinline__ void far_block(const SrcStage &S, int sb, const float (&ux)[T], const float (&uy)[T],
+                                          const float (&uz)[T], float (&p)[T][6]) {
+    constexpr int G = 2;
+    float sn[T][3], sf[T][3], o[T][3];
+#pragma unroll
+    for (int t = 0; t < T; t++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) { sn[t][k] = 0.0f; sf[t][k] = 0.0f; o[t][k] = 0.0f; }
+#pragma unroll 2
+    for (int j0 = sb; j0 < sb + kKahanBlock; j0 += G) {
+        float rx[G][T], ry[G][T], rz[G][T], q[G][T], fx[G];
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            const float4 W = S.W[j0 + g];
+            fx[g] = W.w;
+#pragma unroll
+            for (int t = 0; t < T; t++) {
+                const float x = ux[t] - W.x, y = uy[t] - W.y, z = uz[t] - W.z;
+                rx[g][t] = x; ry[g][t] = y; rz[g][t] = z;
+                q[g][t] = rsq_f32(fmaf(z, z, fmaf(y, y, fmaf(x, x, 1.0f))));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            const float4 F = S.F[j0 + g], M = S.M[j0 + g], K = S.K[j0 + g];
+#pragma unroll
+            for (int t = 0; t < T; t++) {
+                const float x = q[g][t] * q[g][t], q3 = q[g][t] * x, q5 = q3 * x;
+                const float h1 = q[g][t] + q3;
+                const float h3 = fmaf(2.0f / 3.0f, q3, q5);  // H3 / 1.5
+                const float q7 = q5 * x;
+                const float h5 = fmaf(2.5f, q7, q5);         // H5 / 1.5
+                const float fr = fmaf(F.y, rz[g][t], fmaf(F.x, ry[g][t], fx[g] * rx[g][t]));
+                const float nr = fmaf(M.x, rz[g][t], fmaf(F.w, ry[g][t], F.z * rx[g][t]));
+                const float a = q3 * fr, b = h5 * nr;
+                p[t][0] = fmaf(h3, M.y, fmaf(a, rx[g][t], fmaf(h1, fx[g], p[t][0])));
+                p[t][1] = fmaf(h3, M.z, fmaf(a, ry[g][t], fmaf(h1, F.x, p[t][1])));
+                p[t][2] = fmaf(h3, M.w, fmaf(a, rz[g][t], fmaf(h1, F.y, p[t][2])));
+                o[t][0] = fmaf(h3, K.x, fmaf(b, rx[g][t], o[t][0]));
+                o[t][1] = fmaf(h3, K.y, fmaf(b, ry[g][t], o[t][1]));
+                o[t][2] = fmaf(h3, K.z, fmaf(b, rz[g][t], o[t][2]));
+                sn[t][0] = fmaf(h3, F.z, sn[t][0]);
+                sn[t][1] = fmaf(h3, F.w, sn[t][1]);
+                sn[t][2] = fmaf(h3, M.x, sn[t][2]);
+                sf[t][0] = fmaf(h3, fx[g], sf[t][0]);
+                sf[t][1] = fmaf(h3, F.x, sf[t][1]);
+                sf[t][2] = fmaf(h3, F.y, sf[t][2]);
+                if (!REMOTE) {
+                    const float u7 = 2.5f * q7;  // 3.75 Q^7 / 1.5
+                    o[t][0] = fmaf(u7, F.z, o[t][0]);
+                    o[t][1] = fmaf(u7, F.w, o[t][1]);
+                    o[t][2] = fmaf(u7, M.x, o[t][2]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < T; t++) {
+        p[t][0] = fmaf(1.5f, fmaf(sn[t][1], uz[t], -(sn[t][2] * uy[t])), p[t][0]);
+        p[t][1] = fmaf(1.5f, fmaf(sn[t][2], ux[t], -(sn[t][0] * uz[t])), p[t][1]);
+        p[t][2] = fmaf(1.5f, fmaf(sn[t][0], uy[t], -(sn[t][1] * ux[t])), p[t][2]);
+        o[t][0] = fmaf(-0.5f, sn[t][0], o[t][0] + fmaf(sf[t][1], uz[t], -(sf[t][2] * uy[t])));
+        o[t][1] = fmaf(-0.5f, sn[t][1], o[t][1] + fmaf(sf[t][2], ux[t], -(sf[t][0] * uz[t])));
+        o[t][2] = fmaf(-0.5f, sn[t][2], o[t][2] + fmaf(sf[t][0], uy[t], -(sf[t][1] * ux[t])));
+#pragma unroll
+        for (int k = 0; k < 3; k++) p[t][3 + k] = fmaf(1.5f, o[t][k], p[t][3 + k]);
+    }
+}
+
+// Beyond this squared gap between the boxes u7 = 3.75 Q^7 is less than 2^-25
+// of H3/2 >= Q^3/2 (7.5 Q^4 < 7.5 / 16384^2 < 2^-25), which is below half an
+// ulp of any FP32 value: H4 = u7 - H3/2 rounds to -H3/2.
+constexpr float kRemoteBoxGap2 = 16384.0f;
+
 // Blocks per CU the register budget must allow: 5 with one target per lane
-// (<= 102 VGPRs), 3 with two (<= 170).  PERSIST: items claimed from the queue;
-// otherwise block b runs item b.
+// (<= 102 VGPRs; four were even), 3 with two (<= 170).  PERSIST: items claimed
+// from the queue; otherwise block b runs item b.
 //
 // QUAD (one target per lane): the block's four waves share the item's 64
 // targets and split its sources, wave w taking the 64-source blocks w, w + 4,
@@ -117,10 +227,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
                                                            const PairItem *__restrict__ items, int n_items,
                                                            uint32_t *queue) {
     static_assert(!QUAD || T == 1, "four-wave source split: one target per lane");
-    // staged sources: sW = (w, fx) with w the anchored position, sF = (fy, fz,
-    // nx, ny), sN = (nz, lo), sH = (hi, 0)
-    __shared__ float4 sW[kSrcTile], sF[kSrcTile], sN[kSrcTile], sH[kSrcTile];
-    __shared__ double sNear[6][T][kBlock];  // FP64 near-pair sums, one slot per lane and target
+    __shared__ SrcStage S;
     static_assert(kSrcTile / kKahanBlock == kBlock / 64 && kKahanBlock == kDescPoints,
                   "one source block (one descriptor) per wave");
     __shared__ int sNext;
@@ -134,6 +241,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
     const int tl = QUAD ? (tid & 63) : tid;
     float thx[T], thy[T], thz[T], tlx[T], tly[T], tlz[T];
     float s[T][6], c[T][6];
+    double pn[T][6];  // FP64 sums of the near pairs and contact sources
     // box of this wave's targets: the descriptors of the blocks they lie in
     // (tiles start on block boundaries; lanes past the tile repeat its last
     // target, which lies in the block of the last real lane)
@@ -149,7 +257,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
 #pragma unroll
         for (int k = 0; k < 3; k++) { tlo[k] = fminf(tlo[k], d[k]); thi[k] = fmaxf(thi[k], d[3 + k]); }
 #pragma unroll
-        for (int k = 0; k < 6; k++) { s[t][k] = 0.0f; c[t][k] = 0.0f; sNear[k][t][tid] = 0.0; }
+        for (int k = 0; k < 6; k++) { s[t][k] = 0.0f; c[t][k] = 0.0f; pn[t][k] = 0.0; }
     }
     for (int base = 0; base < it.nsrc; base += kSrcTile) {
         if (QUAD) {
@@ -170,15 +278,23 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
         }
         // a source with contact forces enters the FP32 sums with zero loads;
         // the FP64 pass evaluates it with its own loads
-        bool contact = false;
         if (E.lj_mask && real) {
             const int jg = it.src0 + j;
-            contact = (E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1;
+            if ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1) {
+                a.w = 0.0f; b.w = 0.0f;
+                cc = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
         }
-        sW[tid] = make_float4(w.x, w.y, w.z, contact ? 0.0f : a.w);
-        sF[tid] = contact ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(b.w, cc.x, cc.y, cc.z);
-        sN[tid] = make_float4(contact ? 0.0f : cc.w, b.x, b.y, b.z);
-        sH[tid] = make_float4(a.x, a.y, a.z, 0.0f);
+        const float fx = a.w, fy = b.w, fz = cc.x, nx = cc.y, ny = cc.z, nz = cc.w;
+        S.W[tid] = make_float4(w.x, w.y, w.z, fx);
+        S.F[tid] = make_float4(fy, fz, nx, ny);
+        // |w| < |r| in the blocks that use them: m and k overflow no earlier
+        // (up to their factor) than the products n . r and f . r
+        S.M[tid] = make_float4(nz, 1.5f * fmaf(w.y, nz, -(w.z * ny)), 1.5f * fmaf(w.z, nx, -(w.x * nz)),
+                               1.5f * fmaf(w.x, ny, -(w.y * nx)));
+        S.K[tid] = make_float4(fmaf(w.y, fz, -(w.z * fy)), fmaf(w.z, fx, -(w.x * fz)), fmaf(w.x, fy, -(w.y * fx)), b.x);
+        S.H[tid] = make_float4(a.x, a.y, a.z, b.y);
+        S.lz[tid] = b.z;
         if (QUAD) wave_sync();
         else __syncthreads();
         const int cnt = min(kSrcTile, it.nsrc - base);
@@ -229,42 +345,33 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
                     uy[t] = (thy[t] - bx[7]) + tly[t];
                     uz[t] = (thz[t] - bx[8]) + tlz[t];
                 }
-                // four sources per iteration: 51.5 instead of 52 VALU
-                // instructions per pair (LDS address and loop counter) and
-                // 2-3% faster on MI355X; still 96 VGPRs, no spills
-#pragma unroll 4
-                for (int jj = sb; jj < sb + kKahanBlock; jj++) {
-                    const float4 W = sW[jj], F = sF[jj], Nn = sN[jj];
-#pragma unroll
-                    for (int t = 0; t < T; t++) {
-                        const float rx = ux[t] - W.x, ry = uy[t] - W.y, rz = uz[t] - W.z;
-                        const float R2 = fmaf(rz, rz, fmaf(ry, ry, fmaf(rx, rx, 1.0f)));
-                        pair_core_f32<false>(rx, ry, rz, R2, W.w, F.x, F.y, F.z, F.w, Nn.x, p[t]);
-                    }
-                }
+                if (gap2 > kRemoteBoxGap2) far_block<T, true>(S, sb, ux, uy, uz, p);
+                else far_block<T, false>(S, sb, ux, uy, uz, p);
             } else if (gap2 > kFarBoxGap2) {
                 // wave-uniform: no near pair, exact hi/lo separation
 #pragma unroll 2
                 for (int jj = sb; jj < sb + kKahanBlock; jj++) {
-                    const float4 W = sW[jj], F = sF[jj], Nn = sN[jj], H = sH[jj];
+                    const float4 F = S.F[jj], H = S.H[jj];
+                    const float Fx = S.W[jj].w, Nz = S.M[jj].x, lx = S.K[jj].w, lz = S.lz[jj];
 #pragma unroll
                     for (int t = 0; t < T; t++) {
                         float rx, ry, rz;
-                        const float R2 = sep_f32(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], H.x, H.y, H.z,
-                                                 Nn.y, Nn.z, Nn.w, rx, ry, rz);
-                        pair_core_f32<false>(rx, ry, rz, R2, W.w, F.x, F.y, F.z, F.w, Nn.x, p[t]);
+                        const float R2 = sep_f32(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], H.x, H.y, H.z, lx,
+                                                 H.w, lz, rx, ry, rz);
+                        pair_core_f32<false>(rx, ry, rz, R2, Fx, F.x, F.y, F.z, F.w, Nz, p[t]);
                     }
                 }
             } else {
 #pragma unroll 2
                 for (int jj = sb; jj < sb + kKahanBlock; jj++) {
-                    const float4 W = sW[jj], F = sF[jj], Nn = sN[jj], H = sH[jj];
+                    const float4 F = S.F[jj], H = S.H[jj];
+                    const float Fx = S.W[jj].w, Nz = S.M[jj].x, lx = S.K[jj].w, lz = S.lz[jj];
 #pragma unroll
                     for (int t = 0; t < T; t++) {
                         float rx, ry, rz;
-                        const float R2 = sep_f32(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], H.x, H.y, H.z,
-                                                 Nn.y, Nn.z, Nn.w, rx, ry, rz);
-                        pair_core_f32<true>(rx, ry, rz, R2, W.w, F.x, F.y, F.z, F.w, Nn.x, p[t]);
+                        const float R2 = sep_f32(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], H.x, H.y, H.z, lx,
+                                                 H.w, lz, rx, ry, rz);
+                        pair_core_f32<true>(rx, ry, rz, R2, Fx, F.x, F.y, F.z, F.w, Nz, p[t]);
                         near[t] |= (uint64_t)(R2 < kNearR2) << (jj - sb);
                     }
                 }
@@ -281,40 +388,42 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
 #pragma unroll
             for (int t = 0; t < T; t++) {
                 uint64_t m = near[t];
-                if (m) {
-                    double pn[6];
-#pragma unroll
-                    for (int k = 0; k < 6; k++) pn[k] = sNear[k][t][tid];
-                    do {
-                        const int jj = sb + __builtin_ctzll(m);
-                        m &= m - 1;
-                        const float4 W = sW[jj], F = sF[jj], Nn = sN[jj], H = sH[jj];
-                        float fx = W.w, fy = F.x, fz = F.y, nx = F.z, ny = F.w, nz = Nn.x;
-                        if ((ljm >> (jj - sb)) & 1) {  // staged with zero loads: take them from the record
-                            const RecF32 r = rec[it.src0 + base + jj];
-                            fx = r.a.w; fy = r.b.w; fz = r.c.x; nx = r.c.y; ny = r.c.z; nz = r.c.w;
-                        }
-                        near_pair_f64(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], H.x, H.y, H.z, Nn.y, Nn.z,
-                                      Nn.w, fx, fy, fz, nx, ny, nz, pn);
-                    } while (m);
-#pragma unroll
-                    for (int k = 0; k < 6; k++) sNear[k][t][tid] = pn[k];
+                while (m) {
+                    const int jj = sb + __builtin_ctzll(m);
+                    m &= m - 1;
+                    const float4 F = S.F[jj], H = S.H[jj];
+                    const float lx = S.K[jj].w, lz = S.lz[jj];
+                    float fx = S.W[jj].w, fy = F.x, fz = F.y, nx = F.z, ny = F.w, nz = S.M[jj].x;
+                    if ((ljm >> (jj - sb)) & 1) {  // staged with zero loads: take them from the record
+                        const RecF32 r = rec[it.src0 + base + jj];
+                        fx = r.a.w; fy = r.b.w; fz = r.c.x; nx = r.c.y; ny = r.c.z; nz = r.c.w;
+                    }
+                    near_pair_f64(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], H.x, H.y, H.z, lx, H.w, lz, fx, fy,
+                                  fz, nx, ny, nz, pn[t]);
                 }
             }
         }
     }
     const int N = E.N;
-    if (QUAD) {
-        // the four waves' sums for the same targets, added in wave order
 #pragma unroll
-        for (int k = 0; k < 6; k++) sNear[k][0][tid] += (double)s[0][k] - (double)c[0][k];
+    for (int t = 0; t < T; t++)
+#pragma unroll
+        for (int k = 0; k < 6; k++) pn[t][k] += (double)s[t][k] - (double)c[t][k];
+    if (QUAD) {
+        // the four waves' sums for the same targets, added in wave order (the
+        // staged sources are no longer needed)
+        double *sum = reinterpret_cast<double *>(&S);  // [6][kBlock]
+        static_assert(sizeof(SrcStage) >= 6 * kBlock * sizeof(double), "sums of four waves");
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 6; k++) sum[k * kBlock + tid] = pn[0][k];
         __syncthreads();
         if (tid < 64 && tid < it.ntgt) {
 #pragma unroll
             for (int k = 0; k < 6; k++) {
-                double v = sNear[k][0][tid];
+                double v = sum[k * kBlock + tid];
 #pragma unroll
-                for (int w = 1; w < kBlock / 64; w++) v += sNear[k][0][w * 64 + tid];
+                for (int w = 1; w < kBlock / 64; w++) v += sum[k * kBlock + w * 64 + tid];
                 E.part[((size_t)it.chunk * 6 + k) * N + it.tgt0 + tid] = v;
             }
         }
@@ -324,9 +433,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
             const int li = tid + t * kBlock;
             if (li < it.ntgt) {
 #pragma unroll
-                for (int k = 0; k < 6; k++)
-                    E.part[((size_t)it.chunk * 6 + k) * N + it.tgt0 + li] =
-                        ((double)s[t][k] - (double)c[t][k]) + sNear[k][t][tid];
+                for (int k = 0; k < 6; k++) E.part[((size_t)it.chunk * 6 + k) * N + it.tgt0 + li] = pn[t][k];
             }
         }
     }
