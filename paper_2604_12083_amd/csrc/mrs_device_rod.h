@@ -169,8 +169,16 @@ __device__ __forceinline__ void preferred_strain(const EnsDesc &E, double s, dou
     if (E.has_wave) om[1] += -E.wave[1] * E.wave[1] * E.wave[0] * sin(E.wave[1] * s + E.wave[2] * t);
 }
 
-// F and N of the segment between nodes ka and kb = ka + 1 (SoA state of N
-// points) at arclength s_mid (its midpoint) and time t.
+// Component c of the w-vector of point p: SoA arrays of N points (resident
+// ensembles) or the caller's row-major arrays (AOS).
+template <bool AOS>
+__device__ __forceinline__ size_t at(int N, int w, int c, int p) {
+    return AOS ? (size_t)w * p + c : (size_t)c * N + p;
+}
+
+// F and N of the segment between nodes ka and kb = ka + 1 at arclength s_mid
+// (its midpoint) and time t.
+template <bool AOS>
 __device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__restrict__ X,
                                             const double *__restrict__ D, int N, int ka, int kb,
                                             double s_mid, double t, double *F, double *Nv, double *dX) {
@@ -178,8 +186,8 @@ __device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__re
     double Da[9], Db[9];
 #pragma unroll
     for (int k = 0; k < 9; k++) {
-        Da[k] = D[(size_t)k * N + ka];
-        Db[k] = D[(size_t)k * N + kb];
+        Da[k] = D[at<AOS>(N, 9, k, ka)];
+        Db[k] = D[at<AOS>(N, 9, k, kb)];
     }
     // A = sum_j D^j_b (D^j_a)^T maps frame a onto frame b.
     double A[9];
@@ -194,7 +202,7 @@ __device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__re
 #pragma unroll
     for (int i = 0; i < 3; i++) quat_rotate(h, Da + 3 * i, Dh + 3 * i);
 #pragma unroll
-    for (int c = 0; c < 3; c++) dX[c] = X[(size_t)c * N + kb] - X[(size_t)c * N + ka];
+    for (int c = 0; c < 3; c++) dX[c] = X[at<AOS>(N, 3, c, kb)] - X[at<AOS>(N, 3, c, ka)];
     const double ids = 1.0 / E.ds;
     F[0] = F[1] = F[2] = 0.0;
     Nv[0] = Nv[1] = Nv[2] = 0.0;
@@ -217,24 +225,23 @@ __device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__re
     }
 }
 
-// Rod forces of one filament (nodes k0 .. k0 + M - 1 of an SoA state of N
-// points; Sec. II.B, Alg. 1): for every node, the point force and torque on
-// the fluid, g = F_{k+1/2} - F_{k-1/2} + external, m = N_{k+1/2} - N_{k-1/2}
-// + (dX_{k+1/2} x F_{k+1/2} + dX_{k-1/2} x F_{k-1/2}) / 2 + external, written
-// as source records into rec[point].  BLOCK threads walk the filament in
-// chunks of BLOCK - 1 nodes: thread t computes segment c0 - 1 + t into LDS,
-// then node c0 + t combines its two neighbouring segments (a node's result
-// does not depend on the chunking).  Every thread of the block must call it.
-template <int BLOCK>
+// Rod forces of one filament (nodes k0 .. k0 + M - 1; Sec. II.B, Alg. 1): for
+// every node, the point force and torque on the fluid, g = F_{k+1/2} -
+// F_{k-1/2} + external, m = N_{k+1/2} - N_{k-1/2} + (dX_{k+1/2} x F_{k+1/2} +
+// dX_{k-1/2} x F_{k-1/2}) / 2 + external, written as source records into
+// rec[point], or with AOS (row-major state and loads) into E.g_out, E.m_out.
+// BLOCK threads walk the filament in chunks of BLOCK - 1 nodes: thread t
+// computes segment c0 - 1 + t into LDS, then node c0 + t combines its two
+// neighbouring segments (a node's result does not depend on the chunking).
+// Every thread of the block must call it.
+template <int BLOCK, bool AOS>
 __device__ __forceinline__ void rod_filament(int prec, int stage_state, int elastic, int scheme, int stage,
-                                             double dt, const EnsDesc &E, int fil, void *rec) {
+                                             double dt, const EnsDesc &E, int k0, int M, void *rec) {
     FP_STRICT;
     __shared__ double sF[3][BLOCK], sN[3][BLOCK], sX[3][BLOCK];
     const int N = E.N;
     const double *__restrict__ X = stage_state ? E.Xs : E.X;
     const double *__restrict__ D = stage_state ? E.Ds : E.D;
-    const int k0 = E.off[fil];
-    const int M = E.off[fil + 1] - k0;
     const int tid = threadIdx.x;
     if (elastic < 0) elastic = E.elastic;
     // waveform time of this stage: step start + c_stage dt
@@ -253,17 +260,19 @@ __device__ __forceinline__ void rod_filament(int prec, int stage_state, int elas
         if (node) {
 #pragma unroll
             for (int c = 0; c < 3; c++) {
-                if (E.fext) g[c] = E.fext[(size_t)c * N + p];
-                if (E.next) m[c] = E.next[(size_t)c * N + p];
-                if (E.has_lj) g[c] += E.flj[(size_t)c * N + p];
-                xp[c] = X[(size_t)c * N + p];
+                if (E.fext) g[c] = E.fext[at<AOS>(N, 3, c, p)];
+                if (E.next) m[c] = E.next[at<AOS>(N, 3, c, p)];
+                if (!AOS) {
+                    if (E.has_lj) g[c] += E.flj[(size_t)c * N + p];
+                    xp[c] = X[(size_t)c * N + p];
+                }
             }
         }
         if (elastic) {
             const int s = c0 - 1 + tid;
             double F[3] = {0.0, 0.0, 0.0}, Nv[3] = {0.0, 0.0, 0.0}, dX[3] = {0.0, 0.0, 0.0};
             if (s >= 0 && s <= M - 2)
-                rod_segment(E, X, D, N, k0 + s, k0 + s + 1, (s + 0.5) * E.ds, t, F, Nv, dX);
+                rod_segment<AOS>(E, X, D, N, k0 + s, k0 + s + 1, (s + 0.5) * E.ds, t, F, Nv, dX);
 #pragma unroll
             for (int c = 0; c < 3; c++) {
                 sF[c][tid] = F[c];
@@ -289,13 +298,14 @@ __device__ __forceinline__ void rod_filament(int prec, int stage_state, int elas
                     m[c] += (sN[c][tid + 1] - sN[c][tid]) + 0.5 * (cp[c] + cm[c]);
                 }
             }
-            store_rec(prec, rec, p, xp[0], xp[1], xp[2], g[0], g[1], g[2], m[0], m[1], m[2], E.inv_eps);
-            if (E.g_out) {
+            if (AOS) {
 #pragma unroll
                 for (int c = 0; c < 3; c++) {
                     E.g_out[3 * (size_t)p + c] = g[c];
                     E.m_out[3 * (size_t)p + c] = m[c];
                 }
+            } else {
+                store_rec(prec, rec, p, xp[0], xp[1], xp[2], g[0], g[1], g[2], m[0], m[1], m[2], E.inv_eps);
             }
         }
         if (elastic) __syncthreads();

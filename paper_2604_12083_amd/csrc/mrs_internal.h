@@ -74,7 +74,7 @@ struct EnsDesc {
     float4 *wanch;
     float *blk;
     double *part;      // split-K partial sums [K][6][N]
-    double *g_out, *m_out;  // optional AoS copies of the rod loads (tests)
+    double *g_out, *m_out;  // rod loads, row-major (k_rod_forces_aos)
     double eps, inv_eps, mu;
     double cU, cW;     // 1/(8 pi mu) and the Omega scale of the record form
     double a[3], b[3], om0[3], ds;
@@ -115,6 +115,17 @@ struct RodItem {
     int32_t ens, fil;
 };
 
+// Filament offsets of k_rod_forces_aos: filaments of `step` points each, or
+// (step = 0) the offsets themselves, up to kRodArgOffsets of them in the
+// kernel's arguments (argument blocks end at 4 KiB), more in a device list.
+constexpr int kRodArgOffsets = 800;
+struct RodOffsets {
+    const int32_t *list;  // device, or null
+    int32_t step;
+    int32_t v[kRodArgOffsets];
+};
+static_assert(sizeof(EnsDesc) + sizeof(RodOffsets) <= 4096, "kernel arguments of k_rod_forces_aos");
+
 // Points per block of the reduction/epilogue kernel, and its threads: the
 // block's waves split the source chunks of its points.
 constexpr int kReducePoints = 64;
@@ -153,6 +164,9 @@ hipError_t launch_pack_aos(int prec, const EnsDesc *d_desc, const EnsDesc &h_des
 // `scheme` (0 for stage 0); dt = NaN: every ensemble uses its own dt.
 hipError_t launch_rod_forces(int prec, int stage_state, int elastic, int scheme, int stage, double dt,
                              const EnsDesc *d_desc, const RodItem *d_items, int n_items, hipStream_t s);
+// Rod forces of h_desc.n_fil >= 1 filaments on row-major arrays (h_desc.X, D,
+// fext, next; g_out, m_out).
+hipError_t launch_rod_forces_aos(const EnsDesc &h_desc, const RodOffsets &off, hipStream_t s);
 // Lennard-Jones forces of the ensembles with has_lj: the box of every LJ
 // source block (box items: (ensemble, first of kBlock / 64 blocks)), then the
 // force on every point and the LJ masks (target items: (ensemble, first of

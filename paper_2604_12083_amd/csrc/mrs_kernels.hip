@@ -76,7 +76,21 @@ __global__ __launch_bounds__(kBlock) void k_rod_forces(int prec, int stage_state
         if (b * kDescPoints < E.N) block_desc_from_x(E, stage_state ? E.Xs : E.X, false, b);
         return;
     }
-    rod_filament<kBlock>(prec, stage_state, elastic, scheme, stage, dt, E, it.fil, E.rec);
+    const int k0 = E.off[it.fil];
+    rod_filament<kBlock, false>(prec, stage_state, elastic, scheme, stage, dt, E, k0, E.off[it.fil + 1] - k0, E.rec);
+}
+
+// mrs_rod_forces_device: one block per filament on the caller's row-major
+// arrays, with the descriptor and the offsets as kernel arguments.  Bound by
+// latency (one chain of square roots and divisions per segment, 192 B per
+// point).  The call took 150 us for 200 filaments of 128 points when it
+// staged its arrays as SoA (18 strided copies of 8-byte rows, 49 us, and an
+// allocation, a synchronisation and a free per call), 7 us so (MI355X).
+__global__ __launch_bounds__(kBlock) void k_rod_forces_aos(const EnsDesc E, const RodOffsets off) {
+    const int f = blockIdx.x;
+    const int k0 = off.list ? off.list[f] : (off.step ? f * off.step : off.v[f]);
+    const int k1 = off.list ? off.list[f + 1] : (off.step ? k0 + off.step : off.v[f + 1]);
+    rod_filament<kBlock, true>(0, 0, 1, 0, 0, 0.0, E, k0, k1 - k0, nullptr);
 }
 
 // ------------------------------------------------------------ Lennard-Jones
@@ -362,6 +376,11 @@ hipError_t launch_rod_forces(int prec, int stage_state, int elastic, int scheme,
     if (n_items == 0) return hipSuccess;
     hipLaunchKernelGGL(k_rod_forces, dim3(n_items), dim3(kBlock), 0, s, prec, stage_state, elastic, scheme,
                        stage, dt, d_desc, d_items);
+    return hipGetLastError();
+}
+
+hipError_t launch_rod_forces_aos(const EnsDesc &h_desc, const RodOffsets &off, hipStream_t s) {
+    hipLaunchKernelGGL(k_rod_forces_aos, dim3(h_desc.n_fil), dim3(kBlock), 0, s, h_desc, off);
     return hipGetLastError();
 }
 

@@ -154,7 +154,6 @@ static EnsDesc ensemble_desc(mrs_ensemble *E, int prec, const PairCfg &c) {
     d.Xin_aos = nullptr;
     set_records(d, E->rec.p, E->N, prec == MRS_FP32C);
     d.part = E->part.as<double>();
-    d.g_out = d.m_out = nullptr;
     d.eps = E->eps;
     d.inv_eps = 1.0 / E->eps;
     d.mu = E->mu;
@@ -599,10 +598,12 @@ mrs_status mrs_context_create(int device, mrs_context **out) {
     if (hipStreamCreateWithFlags(&ctx->own_stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->stage_event, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->eval_done, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&ctx->rod_done, hipEventDisableTiming) != hipSuccess ||
         hipHostMalloc(&flag, 256, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
         hipHostGetDevicePointer(reinterpret_cast<void **>(&ctx->flag_dev), flag, 0) != hipSuccess) {
         if (flag) (void)hipHostFree(flag);
         if (ctx->eval_done) (void)hipEventDestroy(ctx->eval_done);
+        if (ctx->rod_done) (void)hipEventDestroy(ctx->rod_done);
         if (ctx->stage_event) (void)hipEventDestroy(ctx->stage_event);
         if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);
         delete ctx;
@@ -633,6 +634,7 @@ void mrs_context_destroy(mrs_context *ctx) {
     if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
     if (ctx->stage_event) (void)hipEventDestroy(ctx->stage_event);
     if (ctx->eval_done) (void)hipEventDestroy(ctx->eval_done);
+    if (ctx->rod_done) (void)hipEventDestroy(ctx->rod_done);
     if (ctx->flag_host) (void)hipHostFree(ctx->flag_host);
     ctx->eval_rec.release();
     ctx->eval_part.release();
@@ -897,69 +899,72 @@ mrs_status mrs_rod_forces_device(mrs_context *ctx, int32_t n_fil, const int32_t 
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
     hipStream_t s = pick_stream(ctx, stream);
     const int64_t n = offsets[n_fil];
-    // The rod kernel reads SoA state; stage the caller's AoS arrays as SoA
-    // through a temporary ensemble-shaped descriptor.
-    DevBuf soa, offb;
-    HIPCHK(ctx, soa.reserve((size_t)n * (3 + 9 + 6) * sizeof(double) + (size_t)n * sizeof(RecF64)));
-    HIPCHK(ctx, offb.reserve((size_t)(n_fil + 1) * sizeof(int32_t)));
-    double *Xs = soa.as<double>(), *Ds = Xs + 3 * n, *E6 = Ds + 9 * n;
-    void *rec = E6 + 6 * n;
-    // transpose on the host side of a device copy would need a kernel; use
-    // 2D strided copies instead: component c of AoS -> row c of SoA
-    for (int c = 0; c < 3; c++)
-        HIPCHK(ctx, hipMemcpy2DAsync(Xs + c * n, sizeof(double), dX + c, 3 * sizeof(double), sizeof(double), n,
-                                     hipMemcpyDeviceToDevice, s));
-    for (int c = 0; c < 9; c++)
-        HIPCHK(ctx, hipMemcpy2DAsync(Ds + c * n, sizeof(double), dD + c, 9 * sizeof(double), sizeof(double), n,
-                                     hipMemcpyDeviceToDevice, s));
-    const bool ext = dfext || dnext;
-    if (ext) {
-        HIPCHK(ctx, hipMemsetAsync(E6, 0, 6 * n * sizeof(double), s));
-        for (int c = 0; c < 3; c++) {
-            if (dfext)
-                HIPCHK(ctx, hipMemcpy2DAsync(E6 + c * n, sizeof(double), dfext + c, 3 * sizeof(double),
-                                             sizeof(double), n, hipMemcpyDeviceToDevice, s));
-            if (dnext)
-                HIPCHK(ctx, hipMemcpy2DAsync(E6 + (3 + c) * n, sizeof(double), dnext + c, 3 * sizeof(double),
-                                             sizeof(double), n, hipMemcpyDeviceToDevice, s));
+    // Outputs may replace the external loads (a thread reads its point's loads
+    // before it writes them); other inputs under an output are copied first,
+    // since neighbouring points read them.
+    const size_t b3 = (size_t)n * 3 * sizeof(double);
+    DevBuf copy;
+    auto under_output = [&](const double *p, size_t bytes, bool loads) {
+        for (const double *o : {dg, dm}) {
+            const char *x = reinterpret_cast<const char *>(p), *y = reinterpret_cast<const char *>(o);
+            if (p && !(loads && x == y) && x < y + b3 && y < x + bytes) return true;
+        }
+        return false;
+    };
+    const bool stage = under_output(dX, b3, false) || under_output(dD, 3 * b3, false) ||
+                       under_output(dfext, b3, true) || under_output(dnext, b3, true);
+    if (stage) {
+        HIPCHK(ctx, copy.reserve(6 * b3));
+        char *c = copy.as<char>();
+        for (auto in : {std::make_pair(&dX, b3), std::make_pair(&dD, 3 * b3), std::make_pair(&dfext, b3),
+                        std::make_pair(&dnext, b3)}) {
+            if (!*in.first) continue;
+            HIPCHK(ctx, hipMemcpyAsync(c, *in.first, in.second, hipMemcpyDeviceToDevice, s));
+            *in.first = reinterpret_cast<const double *>(c);
+            c += in.second;
         }
     }
-    HIPCHK(ctx, hipMemcpyAsync(offb.p, offsets, (size_t)(n_fil + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
     EnsDesc d{};
     d.N = (int32_t)n;
     d.n_fil = n_fil;
-    d.K = 1;
-    d.off = offb.as<int32_t>();
-    d.X = Xs;
-    d.D = Ds;
-    d.fext = ext ? E6 : nullptr;
-    d.next = ext ? E6 + 3 * n : nullptr;
-    d.rec = rec;
+    d.X = const_cast<double *>(dX);  // read only
+    d.D = const_cast<double *>(dD);
+    d.fext = dfext;
+    d.next = dnext;
     d.g_out = dg;
     d.m_out = dm;
-    d.eps = 1.0;
-    d.inv_eps = 1.0;
-    d.mu = 1.0;
     for (int i = 0; i < 3; i++) {
         d.a[i] = rod->a[i];
         d.b[i] = rod->b[i];
         d.om0[i] = rod->omega0[i];
     }
     d.ds = rod->ds;
-    std::vector<RodItem> items;
-    for (int f = 0; f < n_fil; f++) items.push_back({0, f});
-    const size_t items_off = (sizeof(EnsDesc) + 255) & ~size_t(255);
-    std::vector<char> blob(items_off + items.size() * sizeof(RodItem));
-    std::memcpy(blob.data(), &d, sizeof d);
-    std::memcpy(blob.data() + items_off, items.data(), items.size() * sizeof(RodItem));
-    HIPCHK(ctx, ctx->eval_rod.reserve(blob.size()));
-    HIPCHK(ctx, upload(ctx, ctx->eval_rod.p, blob.data(), blob.size(), s));
-    HIPCHK(ctx, timed(ctx, "rod_forces", s, [&] {
-        return launch_rod_forces(MRS_FP64, 0, 1, 0, 0, 0.0, ctx->eval_rod.as<EnsDesc>(),
-                                 reinterpret_cast<const RodItem *>(ctx->eval_rod.as<char>() + items_off), n_fil, s);
-    }));
-    // temporaries are freed by DevBuf destructors: wait for the kernel first
-    HIPCHK(ctx, hipStreamSynchronize(s));
+    RodOffsets off{};
+    bool even = true;
+    for (int32_t f = 1; f < n_fil && even; f++) even = offsets[f + 1] - offsets[f] == offsets[1];
+    if (even) {
+        off.step = offsets[1];
+    } else if (n_fil + 1 <= kRodArgOffsets) {
+        std::memcpy(off.v, offsets, (size_t)(n_fil + 1) * sizeof(int32_t));
+    } else {
+        // the list is shared by the context's calls: wait on the stream for
+        // the last kernel that reads it (any stream), and on the host before
+        // it is replaced by a larger one
+        const size_t bytes = (size_t)(n_fil + 1) * sizeof(int32_t);
+        if (ctx->rod_pending) {
+            if (bytes > ctx->eval_rod.bytes) HIPCHK(ctx, hipEventSynchronize(ctx->rod_done));
+            HIPCHK(ctx, hipStreamWaitEvent(s, ctx->rod_done, 0));
+        }
+        HIPCHK(ctx, ctx->eval_rod.reserve(bytes));
+        HIPCHK(ctx, upload(ctx, ctx->eval_rod.p, offsets, bytes, s));
+        off.list = ctx->eval_rod.as<int32_t>();
+    }
+    HIPCHK(ctx, timed(ctx, "rod_forces", s, [&] { return launch_rod_forces_aos(d, off, s); }));
+    if (off.list) {
+        HIPCHK(ctx, hipEventRecord(ctx->rod_done, s));
+        ctx->rod_pending = true;
+    }
+    if (stage) HIPCHK(ctx, hipStreamSynchronize(s));  // the copies are freed on return
     return MRS_OK;
 }
 

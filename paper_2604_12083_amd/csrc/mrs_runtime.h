@@ -128,6 +128,10 @@ struct mrs_context {
     // evaluation scratch, whatever stream it is queued on
     hipEvent_t eval_done = nullptr;
     bool eval_pending = false;
+    // end of the last mrs_rod_forces_device call that read eval_rod (a list
+    // of filament offsets too long for the kernel's arguments)
+    hipEvent_t rod_done = nullptr;
+    bool rod_pending = false;
     // pinned staging for small uploads, reused after its event completes
     void *stage_host = nullptr;
     size_t stage_bytes = 0;
