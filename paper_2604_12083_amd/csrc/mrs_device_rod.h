@@ -61,6 +61,18 @@ __device__ __forceinline__ void store_rec(int prec, void *rec, int i, double x, 
     }
 }
 
+// The record of point i of a one-shot evaluation, from the caller's row-major
+// arrays.
+__device__ __forceinline__ RecF32 input_rec_f32(const EnsDesc &E, int i) {
+    const double *X = E.Xin_aos + 3 * (size_t)i, *f = E.fext + 3 * (size_t)i, *n = E.next + 3 * (size_t)i;
+    return make_rec_f32(X[0], X[1], X[2], f[0], f[1], f[2], n[0], n[1], n[2], E.inv_eps);
+}
+
+__device__ __forceinline__ RecF64 input_rec_f64(const EnsDesc &E, int i) {
+    const double *X = E.Xin_aos + 3 * (size_t)i, *f = E.fext + 3 * (size_t)i, *n = E.next + 3 * (size_t)i;
+    return {X[0], X[1], X[2], f[0], f[1], f[2], n[0], n[1], n[2], 0.0};
+}
+
 // ------------------------------------------------------------- rotations
 
 // Unit quaternion (w, x, y, z), w >= 0, of a proper rotation A (row-major),

@@ -55,10 +55,11 @@ __device__ __forceinline__ void block_desc_from_x(const EnsDesc &E, const double
 __global__ __launch_bounds__(kBlock) void k_pack_aos(int prec, const EnsDesc *__restrict__ desc) {
     const EnsDesc &E = desc[0];
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    const double *X = E.Xin_aos, *f = E.fext, *n = E.next;
-    if (i < E.N)
-        store_rec(prec, E.rec, i, X[3 * i], X[3 * i + 1], X[3 * i + 2], f[3 * i], f[3 * i + 1],
-                  f[3 * i + 2], n[3 * i], n[3 * i + 1], n[3 * i + 2], E.inv_eps);
+    const double *X = E.Xin_aos;
+    if (i < E.N) {
+        if (prec == 1) reinterpret_cast<RecF32 *>(E.rec)[i] = input_rec_f32(E, i);
+        else reinterpret_cast<RecF64 *>(E.rec)[i] = input_rec_f64(E, i);
+    }
     const int b = i / kDescPoints;  // wave-uniform
     if (prec == 1 && E.blk && b * kDescPoints < E.N) block_desc_from_x(E, X, true, b);
 }

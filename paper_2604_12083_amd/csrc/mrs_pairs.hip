@@ -7,6 +7,8 @@
 //   k_pairs_split     small-ensemble form: a wave owns a few targets, its lanes
 //                     stride over the sources and the sums are combined with
 //                     wave shuffles
+//   k_eval_direct     the same for a small one-shot evaluation, from the
+//                     caller's arrays to the velocities in one launch
 //
 // Kernel functions.  With R^2 = r^2 + eps^2, Q = 1/R and H_i the kernel
 // functions of the blob phi_eps (Sec. II.C), 8 pi H_i are
@@ -23,6 +25,7 @@
 #include <algorithm>
 
 #include "mrs_device_pairs.h"
+#include "mrs_device_rod.h"
 #include "mrs_internal.h"
 
 namespace mrs {
@@ -512,14 +515,16 @@ __global__ __launch_bounds__(kBlock) void k_pairs_tile_f64(const EnsDesc *__rest
 constexpr int kSplitPerLane = 16;  // FP32C: sources per lane between compensated updates
 constexpr int kSplitRoundF32 = 64 * kSplitPerLane, kSplitRoundF64 = kBlock;
 
-template <int PREC>
-__global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restrict__ desc,
-                                                        const PairItem *__restrict__ items) {
+//
+// DIRECT: the whole of a one-shot evaluation (one source chunk): the records
+// are formed from the caller's row-major arrays as they are staged and U,
+// Omega are written in place of the partial sums, with the same operations as
+// the pack and reduction kernels.
+template <int PREC, bool DIRECT>
+__device__ __forceinline__ void split_item(const EnsDesc &E, const PairItem it) {
     constexpr int TW = kSplitTargetsPerWave;
     static_assert(sizeof(RecF32) == 48 && sizeof(RecF64) == 80, "record layouts");
     __shared__ float4 sBuf[PREC == 1 ? 3 * kSplitRoundF32 : 5 * kSplitRoundF64];
-    const PairItem it = items[blockIdx.x];
-    const EnsDesc &E = desc[it.ens];
     const int tid = threadIdx.x, lane = tid & 63;
     const int tb = (tid >> 6) * TW;
     // a wave without targets still stages sources and meets every barrier
@@ -527,12 +532,13 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
     double out[TW][6];
     if (PREC == 1) {
         const RecF32 *__restrict__ rec = reinterpret_cast<const RecF32 *>(E.rec);
+        const auto load = [&](int i) { return DIRECT ? input_rec_f32(E, i) : rec[i]; };
         RecF32 *sRec = reinterpret_cast<RecF32 *>(sBuf);
         float thx[TW], thy[TW], thz[TW], tlx[TW], tly[TW], tlz[TW], s[TW][6], c[TW][6];
         double pn[TW][6];
 #pragma unroll
         for (int t = 0; t < TW; t++) {
-            const RecF32 r = rec[it.tgt0 + min(tb + t, it.ntgt - 1)];
+            const RecF32 r = load(it.tgt0 + min(tb + t, it.ntgt - 1));
             thx[t] = r.a.x; thy[t] = r.a.y; thz[t] = r.a.z;
             tlx[t] = r.b.x; tly[t] = r.b.y; tlz[t] = r.b.z;
 #pragma unroll
@@ -541,7 +547,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
         for (int j0 = 0; j0 < it.nsrc; j0 += kSplitRoundF32) {
             const int cnt = min(kSplitRoundF32, it.nsrc - j0);
             __syncthreads();
-            for (int q = tid; q < cnt; q += kBlock) sRec[q] = rec[it.src0 + j0 + q];
+            for (int q = tid; q < cnt; q += kBlock) sRec[q] = load(it.src0 + j0 + q);
             __syncthreads();
             if (!active) continue;
             float p[TW][6];
@@ -552,7 +558,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
                 for (int k = 0; k < 6; k++) p[t][k] = 0.f;
             for (int j = lane; j < cnt; j += 64) {
                 const int jg = it.src0 + j0 + j;
-                if (E.lj_mask && ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1)) {
+                if (!DIRECT && E.lj_mask && ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1)) {
                     rmin = 0.0f;  // a source with contact forces: FP64 below
                     continue;
                 }
@@ -569,7 +575,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
                 for (int j = lane; j < cnt; j += 64) {
                     const RecF32 r = sRec[j];
                     const int jg = it.src0 + j0 + j;
-                    const bool strong = E.lj_mask && ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1);
+                    const bool strong = !DIRECT && E.lj_mask && ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1);
 #pragma unroll
                     for (int t = 0; t < TW; t++) {
                         float rx, ry, rz;
@@ -589,12 +595,13 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
         wave_sum_n<6 * TW>(&out[0][0]);
     } else {
         const RecF64 *__restrict__ rec = reinterpret_cast<const RecF64 *>(E.rec);
+        const auto load = [&](int i) { return DIRECT ? input_rec_f64(E, i) : rec[i]; };
         RecF64 *sRec = reinterpret_cast<RecF64 *>(sBuf);
         const double e2 = E.eps * E.eps, c375e2 = 3.75 * e2;
         double tx[TW], ty[TW], tz[TW], acc[TW][6];
 #pragma unroll
         for (int t = 0; t < TW; t++) {
-            const RecF64 &r = rec[it.tgt0 + min(tb + t, it.ntgt - 1)];
+            const RecF64 r = load(it.tgt0 + min(tb + t, it.ntgt - 1));
             tx[t] = r.x; ty[t] = r.y; tz[t] = r.z;
 #pragma unroll
             for (int k = 0; k < 6; k++) acc[t][k] = 0.0;
@@ -602,7 +609,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
         for (int j0 = 0; j0 < it.nsrc; j0 += kSplitRoundF64) {
             const int cnt = min(kSplitRoundF64, it.nsrc - j0);
             __syncthreads();
-            for (int q = tid; q < cnt; q += kBlock) sRec[q] = rec[it.src0 + j0 + q];
+            for (int q = tid; q < cnt; q += kBlock) sRec[q] = load(it.src0 + j0 + q);
             __syncthreads();
             if (!active) continue;
             for (int j = lane; j < cnt; j += 64) {
@@ -627,13 +634,44 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
                 double v = out[t][0];
 #pragma unroll
                 for (int k = 1; k < 6; k++) v = (lane == k) ? out[t][k] : v;
-                E.part[((size_t)it.chunk * 6 + lane) * N + it.tgt0 + tb + t] = v;
+                if (DIRECT) {
+                    const size_t o = 3 * (size_t)(it.tgt0 + tb + t);
+                    if (lane < 3) E.U[o + lane] = v * E.cU;
+                    else E.W[o + lane - 3] = v * E.cW;
+                } else {
+                    E.part[((size_t)it.chunk * 6 + lane) * N + it.tgt0 + tb + t] = v;
+                }
             }
         }
     }
 }
 
+template <int PREC>
+__global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restrict__ desc,
+                                                        const PairItem *__restrict__ items) {
+    const PairItem it = items[blockIdx.x];
+    split_item<PREC, false>(desc[it.ens], it);
+}
+
+// One-shot evaluation of E.N <= kDirectMaxPoints points in one launch, with no
+// scratch and no work list: a 64-point FP64 call takes 12 us on one stream, 23 us on streams in
+// turn (each waits for the one before) instead of 36 with
+// pack, pair and reduction kernels and an uploaded list (MI355X).
+template <int PREC>
+__global__ __launch_bounds__(kBlock) void k_eval_direct(const EnsDesc E) {
+    const int t0 = (int)blockIdx.x * kSplitTargetsPerBlock;
+    split_item<PREC, true>(E, {0, t0, min(kSplitTargetsPerBlock, E.N - t0), 0, E.N, 0});
+}
+
 // --------------------------------------------------------- launch wrapper
+
+hipError_t launch_eval_direct(int prec, const EnsDesc &h_desc, hipStream_t s) {
+    if (h_desc.N == 0) return hipSuccess;
+    const dim3 g((h_desc.N + kSplitTargetsPerBlock - 1) / kSplitTargetsPerBlock), b(kBlock);
+    if (prec == 1) hipLaunchKernelGGL(k_eval_direct<1>, g, b, 0, s, h_desc);
+    else hipLaunchKernelGGL(k_eval_direct<0>, g, b, 0, s, h_desc);
+    return hipGetLastError();
+}
 
 template <int T, bool PERSIST>
 static void launch_tile(int prec, dim3 g, dim3 b, hipStream_t s, const EnsDesc *d_desc, const PairItem *d_items,

@@ -124,10 +124,11 @@ struct mrs_context {
     int32_t *flag_host = nullptr;
     int32_t *flag_dev = nullptr;
     // end of the last one-shot evaluation (mrs_eval_device / mrs_eval_host),
-    // recorded on its stream: the next one waits for it before it reuses the
-    // evaluation scratch, whatever stream it is queued on
+    // recorded on its stream: the next one, on another stream, waits for it
+    // before it reuses the evaluation scratch
     hipEvent_t eval_done = nullptr;
     bool eval_pending = false;
+    hipStream_t eval_stream = nullptr;  // stream of the last one (with eval_pending)
     // end of the last mrs_rod_forces_device call that read eval_rod (a list
     // of filament offsets too long for the kernel's arguments)
     hipEvent_t rod_done = nullptr;
