@@ -188,7 +188,10 @@ mrs_status mrs_ensemble_create(mrs_context *ctx, int32_t n_fil, const int32_t *o
                                const double *X, const double *D, const double *f_ext,
                                const double *n_ext, double eps, double mu,
                                const mrs_rod_params *rod, mrs_ensemble **out);
-/* Replace the state (host arrays; either may be NULL to keep it). */
+/* Replace the state (host arrays, copied; either may be NULL to keep it).
+ * This call, mrs_ensemble_set_external and mrs_ensemble_set_time return once
+ * the caller's values have been read; their way to the device is queued on
+ * the context stream ahead of every later call. */
 mrs_status mrs_ensemble_set_state(mrs_ensemble *ens, const double *X, const double *D);
 /* Replace the external point force f_ext and torque n_ext exerted on the
  * fluid at every point (Sec. II.C, Eq. superposition: the loads the MRS sum

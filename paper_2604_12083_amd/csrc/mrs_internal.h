@@ -196,6 +196,24 @@ hipError_t launch_clock_probe(int64_t cycles, uint64_t *out, hipStream_t s);
 hipError_t launch_parareal_correct(int N, const double *Xf, const double *Df, const double *Xg, const double *Dg,
                                   const double *Xo, const double *Do, double *X, double *D, hipStream_t s);
 
+// Row-major host arrays to and from stored SoA arrays: rows [0, n_rows) of the
+// chunk are the caller's points i0.., stored at inv[i0 + row].
+struct RowArray {
+    double *soa;   // device, component c of stored point k at [c N + k]
+    double *rows;  // pinned host memory mapped on the device, row-major; null (in): zeros
+    int32_t w;     // components, 3 or 9
+};
+struct RowArrays {
+    RowArray a[4];
+    int32_t count;
+};
+hipError_t launch_rows_in(const RowArrays &ra, const int32_t *inv, int64_t N, int64_t i0, int64_t n_rows,
+                          hipStream_t s);
+// Sets *nonfinite to 1 (plain vector store) when a value copied out is not finite.
+hipError_t launch_rows_out(const RowArrays &ra, const int32_t *inv, int64_t N, int64_t i0, int64_t n_rows,
+                           int32_t *nonfinite, hipStream_t s);
+hipError_t launch_set_value(double *p, double v, hipStream_t s);
+
 // Pair-kernel modes.
 // PAIR_QUAD (FP32C): tiles of 64 targets whose four waves split the sources.
 enum PairMode : int { PAIR_TILE = 0, PAIR_SPLIT = 1, PAIR_QUAD = 2 };

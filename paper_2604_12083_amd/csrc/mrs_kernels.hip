@@ -312,6 +312,41 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(int stage, int scheme
     epilogue_point<EPI>(E, N, i, acc, xv, dv, uav, wav, kv, stage, scheme, dt);
 }
 
+// ------------------------------------------------- caller arrays in and out
+
+// State in and out of an ensemble.  The host side is pinned memory that the
+// kernels access themselves, so a call is one launch: consecutive threads take
+// consecutive doubles of the rows (whole PCIe bursts), the gather or scatter to
+// the stored order happens in device memory.  Bound by PCIe and the host's own
+// copy; against a copy per array and the transposition on the host, 12,800
+// points take 78 instead of 137 us in (X, D, with the wait) and 87 instead of
+// 204 us out (X, D, U, Omega), 64 points 16 instead of 53 us out (MI355X).
+template <bool OUT, int W>
+__device__ __forceinline__ void copy_rows(const RowArray &A, const int32_t *__restrict__ inv, int64_t N, int64_t i0,
+                                          int64_t n_rows, int32_t *nonfinite) {
+    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t row = q / W;
+    if (row >= n_rows) return;
+    double *v = A.soa + (q - row * W) * N + inv[i0 + row];
+    if (OUT) {
+        const double x = *v;
+        A.rows[q] = x;
+        if (!isfinite(x)) *nonfinite = 1;
+    } else {
+        *v = A.rows ? A.rows[q] : 0.0;
+    }
+}
+
+template <bool OUT>
+__global__ __launch_bounds__(kBlock) void k_rows(const RowArrays ra, const int32_t *__restrict__ inv, int64_t N,
+                                                 int64_t i0, int64_t n_rows, int32_t *nonfinite) {
+    const RowArray &A = ra.a[blockIdx.y];
+    if (A.w == 9) copy_rows<OUT, 9>(A, inv, N, i0, n_rows, nonfinite);
+    else copy_rows<OUT, 3>(A, inv, N, i0, n_rows, nonfinite);
+}
+
+__global__ void k_set_value(double *p, double v) { *p = v; }
+
 // ------------------------------------------------------ Parareal correction
 
 // X = Xf + Xg - Xo and D = reorth(Df + Dg - Do) for every point (SoA state).
@@ -412,6 +447,32 @@ hipError_t launch_parareal_correct(int N, const double *Xf, const double *Df, co
                                   const double *Xo, const double *Do, double *X, double *D, hipStream_t s) {
     if (N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_parareal_correct, dim3(blocks_for(N)), dim3(kBlock), 0, s, N, Xf, Df, Xg, Dg, Xo, Do, X, D);
+    return hipGetLastError();
+}
+
+template <bool OUT>
+static hipError_t launch_rows(const RowArrays &ra, const int32_t *inv, int64_t N, int64_t i0, int64_t n_rows,
+                              int32_t *nonfinite, hipStream_t s) {
+    if (n_rows == 0 || ra.count == 0) return hipSuccess;
+    int w = 0;
+    for (int k = 0; k < ra.count; k++) w = ra.a[k].w > w ? ra.a[k].w : w;
+    hipLaunchKernelGGL(k_rows<OUT>, dim3(blocks_for(n_rows * w), ra.count), dim3(kBlock), 0, s, ra, inv, N, i0, n_rows,
+                       nonfinite);
+    return hipGetLastError();
+}
+
+hipError_t launch_rows_in(const RowArrays &ra, const int32_t *inv, int64_t N, int64_t i0, int64_t n_rows,
+                          hipStream_t s) {
+    return launch_rows<false>(ra, inv, N, i0, n_rows, nullptr, s);
+}
+
+hipError_t launch_rows_out(const RowArrays &ra, const int32_t *inv, int64_t N, int64_t i0, int64_t n_rows,
+                           int32_t *nonfinite, hipStream_t s) {
+    return launch_rows<true>(ra, inv, N, i0, n_rows, nonfinite, s);
+}
+
+hipError_t launch_set_value(double *p, double v, hipStream_t s) {
+    hipLaunchKernelGGL(k_set_value, dim3(1), dim3(1), 0, s, p, v);
     return hipGetLastError();
 }
 

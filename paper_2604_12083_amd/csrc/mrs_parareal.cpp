@@ -115,7 +115,9 @@ struct Solve {
         // slice boundary times, accumulated step by step exactly as the
         // device clock of a serial fine run accumulates them
         T.assign(ns + 1, 0.0);
-        if (hipMemcpy(&T[0], E->clock.p, sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
+        // a new time may still be queued on the context stream
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess ||
+            hipMemcpy(&T[0], E->clock.p, sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
             return fail(ctx, MRS_EDEVICE, "parareal clock read");
         for (int n = 1; n <= ns; n++) {
             T[n] = T[n - 1];

@@ -599,11 +599,13 @@ mrs_status mrs_context_create(int device, mrs_context **out) {
         hipEventCreateWithFlags(&ctx->stage_event, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->eval_done, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->rod_done, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&ctx->in_event, hipEventDisableTiming) != hipSuccess ||
         hipHostMalloc(&flag, 256, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
         hipHostGetDevicePointer(reinterpret_cast<void **>(&ctx->flag_dev), flag, 0) != hipSuccess) {
         if (flag) (void)hipHostFree(flag);
         if (ctx->eval_done) (void)hipEventDestroy(ctx->eval_done);
         if (ctx->rod_done) (void)hipEventDestroy(ctx->rod_done);
+        if (ctx->in_event) (void)hipEventDestroy(ctx->in_event);
         if (ctx->stage_event) (void)hipEventDestroy(ctx->stage_event);
         if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);
         delete ctx;
@@ -632,9 +634,14 @@ void mrs_context_destroy(mrs_context *ctx) {
     }
     for (auto ev : ctx->event_pool) (void)hipEventDestroy(ev);
     if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
+    for (int i = 0; i < 2; i++) {
+        if (ctx->row_host[i]) (void)hipHostFree(ctx->row_host[i]);
+        if (ctx->row_event[i]) (void)hipEventDestroy(ctx->row_event[i]);
+    }
     if (ctx->stage_event) (void)hipEventDestroy(ctx->stage_event);
     if (ctx->eval_done) (void)hipEventDestroy(ctx->eval_done);
     if (ctx->rod_done) (void)hipEventDestroy(ctx->rod_done);
+    if (ctx->in_event) (void)hipEventDestroy(ctx->in_event);
     if (ctx->flag_host) (void)hipHostFree(ctx->flag_host);
     ctx->eval_rec.release();
     ctx->eval_part.release();
@@ -651,7 +658,14 @@ const char *mrs_last_error(const mrs_context *ctx) { return ctx ? ctx->err.c_str
 
 mrs_status mrs_context_set_stream(mrs_context *ctx, void *stream) {
     CHECK_CTX(ctx);
-    ctx->stream = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->own_stream;
+    hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->own_stream;
+    // new state, loads or time may still be on their way in on the old stream
+    // (which the caller may have destroyed since)
+    if (s != ctx->stream && ctx->in_pending) {
+        HIPCHK(ctx, hipEventSynchronize(ctx->in_event));
+        ctx->in_pending = false;
+    }
+    ctx->stream = s;
     return MRS_OK;
 }
 
@@ -1056,20 +1070,138 @@ void soa_to_aos(const double *src, double *dst, int64_t n, int w, const std::vec
 
 }  // namespace mrs
 
-extern "C" {
+namespace mrs {
 
-static mrs_status put_soa(mrs_context *ctx, DevBuf &d, const double *src, int64_t n, int w,
-                          const std::vector<int64_t> &perm) {
-    std::vector<double> tmp((size_t)n * w);
-    aos_to_soa(src, tmp.data(), n, w, perm);
-    HIPCHK(ctx, hipMemcpy(d.p, tmp.data(), tmp.size() * sizeof(double), hipMemcpyHostToDevice));
-    return MRS_OK;
+// Rows per pinned slot (4.5 MiB at 18 doubles a row): larger ensembles go
+// through the two slots in turn, so that the host copies one while the device
+// works on the other.
+constexpr int64_t kRowSlotRows = 32768;
+
+struct HostRows {
+    double *soa;  // device
+    double *host; // caller's rows, or null (in: zeros)
+    int w;
+};
+
+// A free slot of at least `bytes` (waits for its last use).
+static hipError_t row_slot(mrs_context *ctx, size_t bytes, int *slot) {
+    hipError_t e;
+    if (bytes > ctx->row_bytes || ctx->row_bytes == 0) {
+        size_t nb = 1 << 16;
+        while (nb < bytes) nb *= 2;
+        nb = std::min(nb, (size_t)kRowSlotRows * 18 * sizeof(double));
+        for (int i = 0; i < 2; i++) {
+            if (ctx->row_pending[i] && (e = hipEventSynchronize(ctx->row_event[i])) != hipSuccess) return e;
+            ctx->row_pending[i] = false;
+            if (ctx->row_host[i]) (void)hipHostFree(ctx->row_host[i]);
+            ctx->row_host[i] = nullptr;
+        }
+        ctx->row_bytes = 0;
+        for (int i = 0; i < 2; i++) {
+            if (!ctx->row_event[i] &&
+                (e = hipEventCreateWithFlags(&ctx->row_event[i], hipEventDisableTiming)) != hipSuccess)
+                return e;
+            if ((e = hipHostMalloc(&ctx->row_host[i], nb, hipHostMallocMapped)) != hipSuccess ||
+                (e = hipHostGetDevicePointer(reinterpret_cast<void **>(&ctx->row_dev[i]), ctx->row_host[i], 0)) !=
+                    hipSuccess)
+                return e;
+        }
+        ctx->row_bytes = nb;
+    }
+    const int i = ctx->row_next;
+    ctx->row_next = 1 - i;
+    if (ctx->row_pending[i]) {
+        if ((e = hipEventSynchronize(ctx->row_event[i])) != hipSuccess) return e;
+        ctx->row_pending[i] = false;
+    }
+    *slot = i;
+    return hipSuccess;
 }
 
-// 21-bit spread for a 63-bit Morton key.
-}  // extern "C"
+static size_t row_width(const std::vector<HostRows> &arrays) {
+    size_t w = 0;
+    for (auto &r : arrays) w += r.host ? r.w : 0;
+    return w;
+}
 
-namespace mrs {
+// Marks values of the caller as queued on the context stream.
+static hipError_t in_queued(mrs_context *ctx) {
+    ctx->in_pending = true;
+    return hipEventRecord(ctx->in_event, ctx->stream);
+}
+
+// Queues the caller's rows of E (any null host array: zeros) on the context
+// stream; the caller's arrays have been read when it returns.  Every later
+// call on E queues on the same stream (mrs_context_set_stream waits for the
+// one it replaces), so nothing waits here: 12 us less per call.
+static hipError_t rows_in(mrs_ensemble *E, const std::vector<HostRows> &arrays) {
+    mrs_context *ctx = E->ctx;
+    hipError_t e;
+    for (int64_t i0 = 0; i0 < E->N; i0 += kRowSlotRows) {
+        const int64_t n = std::min(kRowSlotRows, E->N - i0);
+        int slot;
+        if ((e = row_slot(ctx, (size_t)n * row_width(arrays) * sizeof(double), &slot)) != hipSuccess) return e;
+        RowArrays ra{};
+        size_t at = 0;
+        for (auto &r : arrays) {
+            ra.a[ra.count++] = {r.soa, r.host ? ctx->row_dev[slot] + at : nullptr, r.w};
+            if (!r.host) continue;
+            std::memcpy(static_cast<double *>(ctx->row_host[slot]) + at, r.host + (size_t)i0 * r.w,
+                        (size_t)n * r.w * sizeof(double));
+            at += (size_t)n * r.w;
+        }
+        if ((e = launch_rows_in(ra, E->inv.as<int32_t>(), E->N, i0, n, ctx->stream)) != hipSuccess ||
+            (e = hipEventRecord(ctx->row_event[slot], ctx->stream)) != hipSuccess)
+            return e;
+        ctx->row_pending[slot] = true;
+    }
+    return in_queued(ctx);
+}
+
+// Copies stored arrays of E to the caller's rows and waits for them; *finite
+// tells whether every value is.
+static hipError_t rows_out(mrs_ensemble *E, const std::vector<HostRows> &arrays, bool *finite) {
+    mrs_context *ctx = E->ctx;
+    hipError_t e;
+    volatile int32_t *flag = ctx->flag_host + 1;
+    *flag = 0;
+    struct Chunk {
+        int slot;
+        int64_t i0, n;
+    };
+    auto finish = [&](const Chunk &c) {
+        hipError_t r = hipEventSynchronize(ctx->row_event[c.slot]);
+        if (r != hipSuccess) return r;
+        ctx->row_pending[c.slot] = false;
+        const double *h = static_cast<const double *>(ctx->row_host[c.slot]);
+        for (auto &a : arrays) {
+            std::memcpy(a.host + (size_t)c.i0 * a.w, h, (size_t)c.n * a.w * sizeof(double));
+            h += (size_t)c.n * a.w;
+        }
+        return hipSuccess;
+    };
+    Chunk last{-1, 0, 0};
+    for (int64_t i0 = 0; i0 < E->N; i0 += kRowSlotRows) {
+        Chunk c{0, i0, std::min(kRowSlotRows, E->N - i0)};
+        if ((e = row_slot(ctx, (size_t)c.n * row_width(arrays) * sizeof(double), &c.slot)) != hipSuccess) return e;
+        RowArrays ra{};
+        size_t at = 0;
+        for (auto &r : arrays) {
+            ra.a[ra.count++] = {r.soa, ctx->row_dev[c.slot] + at, r.w};
+            at += (size_t)c.n * r.w;
+        }
+        if ((e = launch_rows_out(ra, E->inv.as<int32_t>(), E->N, c.i0, c.n, ctx->flag_dev + 1, ctx->stream)) !=
+                hipSuccess ||
+            (e = hipEventRecord(ctx->row_event[c.slot], ctx->stream)) != hipSuccess)
+            return e;
+        ctx->row_pending[c.slot] = true;
+        if (last.slot >= 0 && (e = finish(last)) != hipSuccess) return e;
+        last = c;
+    }
+    if (last.slot >= 0 && (e = finish(last)) != hipSuccess) return e;
+    *finite = *flag == 0;
+    return hipSuccess;
+}
 
 static uint64_t spread3(uint64_t v) {
     v &= 0x1fffff;
@@ -1129,10 +1261,17 @@ void spatial_order(int32_t n_fil, const int32_t *off, const double *X, std::vect
 
 extern "C" {
 
+// x - x is 0 for finite x and NaN otherwise; eight sums, so that the compiler
+// may take them together (an early exit would keep it from that).
 static bool all_finite(const double *p, size_t n) {
-    for (size_t i = 0; i < n; i++)
-        if (!std::isfinite(p[i])) return false;
-    return true;
+    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    size_t i = 0;
+    for (; i + 8 <= n; i += 8)
+        for (int k = 0; k < 8; k++) s[k] += p[i + k] - p[i + k];
+    for (; i < n; i++) s[0] += p[i] - p[i];
+    double t = 0.0;
+    for (int k = 0; k < 8; k++) t += s[k];
+    return t == 0.0;
 }
 
 mrs_status mrs_ensemble_create(mrs_context *ctx, int32_t n_fil, const int32_t *offsets, const double *X,
@@ -1155,16 +1294,24 @@ mrs_status mrs_ensemble_create(mrs_context *ctx, int32_t n_fil, const int32_t *o
     std::vector<int64_t> perm;
     spatial_order(n_fil, offsets, X, soff, perm);
     std::unique_ptr<mrs_ensemble> E;
-    mrs_status st = ensemble_alloc(ctx, n_fil, soff.data(), eps, mu, rod, f_ext || n_ext, E);
+    mrs_status st = ensemble_alloc(ctx, n_fil, soff.data(), eps, mu, rod, f_ext || n_ext, E, nullptr, false);
     if (st != MRS_OK) return st;
     E->perm = std::move(perm);
-    if ((st = put_soa(ctx, E->X, X, n, 3, E->perm)) != MRS_OK) return st;
-    if ((st = put_soa(ctx, E->D, D, n, 9, E->perm)) != MRS_OK) return st;
-    if (E->has_ext) {
-        std::vector<double> z((size_t)3 * n, 0.0);
-        if ((st = put_soa(ctx, E->fext, f_ext ? f_ext : z.data(), n, 3, E->perm)) != MRS_OK) return st;
-        if ((st = put_soa(ctx, E->next, n_ext ? n_ext : z.data(), n, 3, E->perm)) != MRS_OK) return st;
-    }
+    std::vector<int32_t> inv((size_t)n);
+    for (int64_t k = 0; k < n; k++) inv[E->perm[k]] = (int32_t)k;
+    if (E->inv.reserve((size_t)n * sizeof(int32_t)) != hipSuccess)
+        return fail(ctx, MRS_ENOMEM, "ensemble allocation (%lld points)", (long long)n);
+    HIPCHK(ctx, hipMemcpy(E->off.p, soff.data(), (n_fil + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
+    HIPCHK(ctx, hipMemcpy(E->inv.p, inv.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
+    HIPCHK(ctx, launch_set_value(E->clock.as<double>(), 0.0, ctx->stream));
+    auto in = [](const double *p) { return const_cast<double *>(p); };
+    HIPCHK(ctx, rows_in(E.get(), {{E->X.as<double>(), in(X), 3},
+                                  {E->D.as<double>(), in(D), 9},
+                                  {E->U.as<double>(), nullptr, 3},
+                                  {E->W.as<double>(), nullptr, 3}}));
+    if (E->has_ext)
+        HIPCHK(ctx, rows_in(E.get(), {{E->fext.as<double>(), in(f_ext), 3}, {E->next.as<double>(), in(n_ext), 3}}));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     ctx->ensembles.push_back(E.get());
     *out = E.release();
     return MRS_OK;
@@ -1176,10 +1323,10 @@ mrs_status mrs_ensemble_set_state(mrs_ensemble *E, const double *X, const double
     if ((X && !all_finite(X, 3 * E->N)) || (D && !all_finite(D, 9 * E->N)))
         return fail(ctx, MRS_EINVAL, "non-finite state");
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    mrs_status st;
-    if (X && (st = put_soa(ctx, E->X, X, E->N, 3, E->perm)) != MRS_OK) return st;
-    if (D && (st = put_soa(ctx, E->D, D, E->N, 9, E->perm)) != MRS_OK) return st;
+    std::vector<HostRows> in;
+    if (X) in.push_back({E->X.as<double>(), const_cast<double *>(X), 3});
+    if (D) in.push_back({E->D.as<double>(), const_cast<double *>(D), 9});
+    if (!in.empty()) HIPCHK(ctx, rows_in(E, in));
     return MRS_OK;
 }
 
@@ -1233,8 +1380,8 @@ mrs_status mrs_ensemble_set_external(mrs_ensemble *E, const double *f_ext, const
     if ((f_ext && !all_finite(f_ext, 3 * n)) || (n_ext && !all_finite(n_ext, 3 * n)))
         return fail(ctx, MRS_EINVAL, "non-finite external load");
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     if (!E->has_ext) {
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
         if (!f_ext && !n_ext) return MRS_OK;  // the loads stay zero
         const size_t v3 = (size_t)n * 3 * sizeof(double);
         if (E->fext.reserve(v3) != hipSuccess || E->next.reserve(v3) != hipSuccess)
@@ -1242,11 +1389,10 @@ mrs_status mrs_ensemble_set_external(mrs_ensemble *E, const double *f_ext, const
         E->has_ext = true;
         invalidate_plans(E);  // the descriptors gain the load arrays
     }
-    std::vector<double> z(f_ext && n_ext ? 0 : (size_t)3 * n, 0.0);
-    mrs_status st;
     E->loads_gen++;
-    if ((st = put_soa(ctx, E->fext, f_ext ? f_ext : z.data(), n, 3, E->perm)) != MRS_OK) return st;
-    return put_soa(ctx, E->next, n_ext ? n_ext : z.data(), n, 3, E->perm);
+    HIPCHK(ctx, rows_in(E, {{E->fext.as<double>(), const_cast<double *>(f_ext), 3},
+                            {E->next.as<double>(), const_cast<double *>(n_ext), 3}}));
+    return MRS_OK;
 }
 
 mrs_status mrs_ensemble_set_time(mrs_ensemble *E, double t) {
@@ -1254,8 +1400,8 @@ mrs_status mrs_ensemble_set_time(mrs_ensemble *E, double t) {
     mrs_context *ctx = E->ctx;
     if (!std::isfinite(t)) return fail(ctx, MRS_EINVAL, "time must be finite");
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    HIPCHK(ctx, hipMemcpy(E->clock.p, &t, sizeof t, hipMemcpyHostToDevice));
+    HIPCHK(ctx, launch_set_value(E->clock.as<double>(), t, ctx->stream));
+    HIPCHK(ctx, in_queued(ctx));
     return MRS_OK;
 }
 
@@ -1311,18 +1457,18 @@ mrs_status mrs_ensemble_get(mrs_ensemble *E, double *X, double *D, double *U, do
     if (!E) return MRS_EINVAL;
     mrs_context *ctx = E->ctx;
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    const int64_t n = E->N;
-    std::vector<double> tmp((size_t)n * 9);
-    struct { double *dst; DevBuf *src; int w; } outs[4] = {{X, &E->X, 3}, {D, &E->D, 9}, {U, &E->U, 3}, {W, &E->W, 3}};
-    mrs_status st = MRS_OK;
-    for (auto &o : outs) {
-        if (!o.dst) continue;
-        HIPCHK(ctx, hipMemcpy(tmp.data(), o.src->p, (size_t)n * o.w * sizeof(double), hipMemcpyDeviceToHost));
-        soa_to_aos(tmp.data(), o.dst, n, o.w, E->perm);
-        if (st == MRS_OK) st = check_host_finite(ctx, tmp.data(), (size_t)n * o.w, "state or velocity");
+    std::vector<HostRows> out;
+    const HostRows all[4] = {{E->X.as<double>(), X, 3}, {E->D.as<double>(), D, 9}, {E->U.as<double>(), U, 3},
+                             {E->W.as<double>(), W, 3}};
+    for (auto &r : all)
+        if (r.host) out.push_back(r);
+    if (out.empty()) {
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        return MRS_OK;
     }
-    return st;
+    bool finite = true;
+    HIPCHK(ctx, rows_out(E, out, &finite));
+    return finite ? MRS_OK : fail(ctx, MRS_ENUMERIC, "non-finite state or velocity");
 }
 
 void mrs_ensemble_destroy(mrs_ensemble *E) {

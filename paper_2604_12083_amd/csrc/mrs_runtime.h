@@ -138,6 +138,18 @@ struct mrs_context {
     size_t stage_bytes = 0;
     hipEvent_t stage_event = nullptr;
     bool stage_pending = false;
+    // pinned, device-mapped slots through which ensemble state and loads go in
+    // and out (rows_in, rows_out): grow-only up to kRowSlotRows rows of 18
+    // doubles each; a slot is reused once its event has completed
+    void *row_host[2] = {nullptr, nullptr};
+    double *row_dev[2] = {nullptr, nullptr};
+    size_t row_bytes = 0;  // of each slot
+    hipEvent_t row_event[2] = {nullptr, nullptr};
+    bool row_pending[2] = {false, false};
+    int row_next = 0;
+    // end of the last queued copy of caller values (state, loads, time)
+    hipEvent_t in_event = nullptr;
+    bool in_pending = false;
     // profiling
     bool prof_on = false;
     std::string prof_sel;  // bracket only kernels whose name contains this (empty = all)
@@ -165,6 +177,7 @@ struct mrs_ensemble {
     // Point k of the stored order is point perm[k] of the caller's order
     // (filaments kept whole; see spatial_order in mrs_runtime.cpp).
     std::vector<int64_t> perm;
+    mrs::DevBuf inv;  // its inverse on the device (int32; ensembles of the caller)
     double eps = 0, mu = 0;
     mrs_rod_params rod{};
     bool has_ext = false;
