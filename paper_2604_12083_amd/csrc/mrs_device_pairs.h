@@ -151,7 +151,7 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Source blocks of the FP32C tiled kernels.  Boxes are taken over the hi
+// Source blocks of the tiled kernels.  Boxes are taken over the hi
 // parts of the positions and then widened by 2^-23 of their largest
 // coordinate magnitude on every side, which covers the lo parts
 // (|lo| <= 2^-24 |hi|), so box tests hold for the exact positions.
@@ -189,7 +189,7 @@ __device__ __forceinline__ void src_block_desc(float4 *__restrict__ wanch, float
         const float h = 0.5f * (hi[k] - lo[k]);
         hd2 = fmaf(h, h, hd2);
     }
-    if (real) wanch[i] = make_float4((hx - ctr[0]) + lx, (hy - ctr[1]) + ly, (hz - ctr[2]) + lz, 0.0f);
+    if (real && wanch) wanch[i] = make_float4((hx - ctr[0]) + lx, (hy - ctr[1]) + ly, (hz - ctr[2]) + lz, 0.0f);
     if ((threadIdx.x & 63) == 0) {
         float *d = blk + (size_t)kDescFloats * b;
 #pragma unroll

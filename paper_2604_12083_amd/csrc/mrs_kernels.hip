@@ -50,7 +50,7 @@ __device__ __forceinline__ void block_desc_from_x(const EnsDesc &E, const double
     src_block_desc(E.wanch, E.blk, b, i, real, h[0], h[1], h[2], l[0], l[1], l[2]);
 }
 
-// One thread per point; with FP32C block descriptors (E.blk set) every wave
+// One thread per point; with block descriptors (E.blk set) every wave
 // (64 consecutive points, block-aligned) also writes its block's descriptor.
 __global__ __launch_bounds__(kBlock) void k_pack_aos(int prec, const EnsDesc *__restrict__ desc) {
     const EnsDesc &E = desc[0];
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_aos(int prec, const EnsDesc *__
         else reinterpret_cast<RecF64 *>(E.rec)[i] = input_rec_f64(E, i);
     }
     const int b = i / kDescPoints;  // wave-uniform
-    if (prec == 1 && E.blk && b * kDescPoints < E.N) block_desc_from_x(E, X, true, b);
+    if (E.blk && b * kDescPoints < E.N) block_desc_from_x(E, X, true, b);
 }
 
 // One block per filament (rod_filament), or one wave per source-block

@@ -446,11 +446,91 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
     if (PERSIST) leave_queue(queue);
 }
 
+// FP64 blocks whose box lies at least four half-diagonals from the wave's
+// targets take the split cross products (below) with u, w relative to the
+// box's centre: |w| <= |r|/4, so (sum H3 n) x u and the sum of H3 (w x n)
+// cancel by at most a factor 1.5 and leave the rounding error where it was
+// (2-norm and worst relative errors equal to the direct form's to two digits
+// at 3,000 to 51,200 points).
+constexpr float kSplitGapRatio2F64 = 16.0f;
+
+// Sources of one staged round of the FP64 kernel: x, y | z, fx | fy, fz |
+// nx, ny | nz, m | k with m = w x n, k = w x f.
+struct SrcStageF64 {
+    double2 a[kSrcTile], b[kSrcTile], c[kSrcTile], d[kSrcTile], e[kSrcTile], f[kSrcTile], g[kSrcTile];
+    double h[kSrcTile];
+};
+
+// Sums of the staged sources [sb, se) into acc for targets at (tx, ty, tz), by
+// split cross products (as in far_block, with H4 = eps^2 u - H3/2): 51
+// instructions per pair and one v_rsq_f64 against 57 for the direct form.  FP64
+// instructions issue at one per 4.1 clocks and SIMD from two waves on, so the
+// registers of the further sums (149 VGPRs and three blocks per CU with two
+// targets per lane, 124 and four before) cost nothing: pair kernel 4.72 ->
+// 4.42 ms at 51,200 points, 308 -> 296 us at 12,800 (MI355X; there the last of
+// its 1.6 rounds of blocks weighs more).
+template <int T>
+__device__ __forceinline__ void far_block_f64(const SrcStageF64 &S, int sb, int se, const double (&tx)[T],
+                                              const double (&ty)[T], const double (&tz)[T], double cx, double cy,
+                                              double cz, double e2, double (&acc)[T][6]) {
+    const double c15e2 = 1.5 * e2, c375e2 = 3.75 * e2;
+    double sn[T][3], sf[T][3], su[T][3];
+#pragma unroll
+    for (int t = 0; t < T; t++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) { sn[t][k] = 0.0; sf[t][k] = 0.0; su[t][k] = 0.0; }
+#pragma unroll 2
+    for (int jj = sb; jj < se; jj++) {
+        const double2 A = S.a[jj], B = S.b[jj], C = S.c[jj], Dd = S.d[jj], Ee = S.e[jj], F = S.f[jj], G = S.g[jj];
+        const double kz = S.h[jj];
+        const double fx = B.y, fy = C.x, fz = C.y, nx = Dd.x, ny = Dd.y, nz = Ee.x;
+#pragma unroll
+        for (int t = 0; t < T; t++) {
+            const double rx = tx[t] - A.x, ry = ty[t] - A.y, rz = tz[t] - B.x;
+            const double q = rsq_f64(fma(rz, rz, fma(ry, ry, fma(rx, rx, e2))));
+            const double q2 = q * q, q3 = q2 * q, q5 = q3 * q2, q7 = q5 * q2;
+            const double h1 = fma(e2, q3, q);
+            const double h3 = fma(c15e2, q5, q3);
+            const double u = c375e2 * q7;
+            const double h5 = fma(1.5, q5, u);
+            const double fr = fma(fz, rz, fma(fy, ry, fx * rx));
+            const double nr = fma(nz, rz, fma(ny, ry, nx * rx));
+            const double a = q3 * fr, b = h5 * nr;
+            acc[t][0] = fma(h3, Ee.y, fma(a, rx, fma(h1, fx, acc[t][0])));
+            acc[t][1] = fma(h3, F.x, fma(a, ry, fma(h1, fy, acc[t][1])));
+            acc[t][2] = fma(h3, F.y, fma(a, rz, fma(h1, fz, acc[t][2])));
+            acc[t][3] = fma(h3, G.x, fma(b, rx, acc[t][3]));
+            acc[t][4] = fma(h3, G.y, fma(b, ry, acc[t][4]));
+            acc[t][5] = fma(h3, kz, fma(b, rz, acc[t][5]));
+            su[t][0] = fma(u, nx, su[t][0]);  // H4 = eps^2 u - H3/2
+            su[t][1] = fma(u, ny, su[t][1]);
+            su[t][2] = fma(u, nz, su[t][2]);
+            sn[t][0] = fma(h3, nx, sn[t][0]);
+            sn[t][1] = fma(h3, ny, sn[t][1]);
+            sn[t][2] = fma(h3, nz, sn[t][2]);
+            sf[t][0] = fma(h3, fx, sf[t][0]);
+            sf[t][1] = fma(h3, fy, sf[t][1]);
+            sf[t][2] = fma(h3, fz, sf[t][2]);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < T; t++) {
+        const double ux = tx[t] - cx, uy = ty[t] - cy, uz = tz[t] - cz;
+        acc[t][0] += fma(sn[t][1], uz, -(sn[t][2] * uy));
+        acc[t][1] += fma(sn[t][2], ux, -(sn[t][0] * uz));
+        acc[t][2] += fma(sn[t][0], uy, -(sn[t][1] * ux));
+        acc[t][3] += fma(e2, su[t][0], fma(-0.5, sn[t][0], fma(sf[t][1], uz, -(sf[t][2] * uy))));
+        acc[t][4] += fma(e2, su[t][1], fma(-0.5, sn[t][1], fma(sf[t][2], ux, -(sf[t][0] * uz))));
+        acc[t][5] += fma(e2, su[t][2], fma(-0.5, sn[t][2], fma(sf[t][0], uy, -(sf[t][1] * ux))));
+    }
+}
+
+// Blocks per CU the register budget allows: 4 with one target per lane, 3 with two.
 template <int T, bool PERSIST>
-__global__ __launch_bounds__(kBlock) void k_pairs_tile_f64(const EnsDesc *__restrict__ desc,
+__global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const EnsDesc *__restrict__ desc,
                                                            const PairItem *__restrict__ items, int n_items,
                                                            uint32_t *queue) {
-    __shared__ double2 s0[kSrcTile], s1[kSrcTile], s2[kSrcTile], s3[kSrcTile], s4[kSrcTile];
+    __shared__ SrcStageF64 S;
     __shared__ int sNext;
     int idx = PERSIST ? claim_item(queue, &sNext) : (int)blockIdx.x;
     while (idx < n_items) {
@@ -458,34 +538,64 @@ __global__ __launch_bounds__(kBlock) void k_pairs_tile_f64(const EnsDesc *__rest
     const EnsDesc &E = desc[it.ens];
     const RecF64 *__restrict__ rec = reinterpret_cast<const RecF64 *>(E.rec);
     const int tid = threadIdx.x;
-    const double e2 = E.eps * E.eps, c375e2 = 3.75 * e2;
+    const double eps = E.eps, e2 = eps * eps, c375e2 = 3.75 * e2;
     double tx[T], ty[T], tz[T], acc[T][6];
+    const desc_float *tbox[T];  // descriptors of the blocks this wave's targets lie in (wave-uniform)
 #pragma unroll
     for (int t = 0; t < T; t++) {
         const int li = min(tid + t * kBlock, it.ntgt - 1);
         const RecF64 &r = rec[it.tgt0 + li];
         tx[t] = r.x; ty[t] = r.y; tz[t] = r.z;
+        const int wb = (it.tgt0 + min((tid & ~63) + t * kBlock, it.ntgt - 1)) / kDescPoints;
+        tbox[t] = desc_at(E.blk, __builtin_amdgcn_readfirstlane(wb));
 #pragma unroll
         for (int k = 0; k < 6; k++) acc[t][k] = 0.0;
     }
     const double2 *__restrict__ rw = reinterpret_cast<const double2 *>(rec);
     for (int base = 0; base < it.nsrc; base += kSrcTile) {
         __syncthreads();
+        // this wave stages the source block tid / 64 of the round
         const int j = base + tid;
-        double2 w0 = make_double2(0.0, 0.0), w1 = w0, w2 = w0, w3 = w0, w4 = w0;
         if (j < it.nsrc) {
             const double2 *src = rw + (size_t)(it.src0 + j) * 5;
-            w0 = src[0]; w1 = src[1]; w2 = src[2]; w3 = src[3]; w4 = src[4];
+            const double2 w0 = src[0], w1 = src[1], w2 = src[2], w3 = src[3], w4 = src[4];
+            const desc_float *d = desc_at(E.blk, __builtin_amdgcn_readfirstlane((it.src0 + j) / kDescPoints));
+            const double wx = w0.x - (double)d[6] * eps, wy = w0.y - (double)d[7] * eps, wz = w1.x - (double)d[8] * eps;
+            const double fx = w1.y, fy = w2.x, fz = w2.y, nx = w3.x, ny = w3.y, nz = w4.x;
+            S.a[tid] = w0; S.b[tid] = w1; S.c[tid] = w2; S.d[tid] = w3;
+            S.e[tid] = make_double2(nz, fma(wy, nz, -(wz * ny)));
+            S.f[tid] = make_double2(fma(wz, nx, -(wx * nz)), fma(wx, ny, -(wy * nx)));
+            S.g[tid] = make_double2(fma(wy, fz, -(wz * fy)), fma(wz, fx, -(wx * fz)));
+            S.h[tid] = fma(wx, fy, -(wy * fx));
         }
-        s0[tid] = w0; s1[tid] = w1; s2[tid] = w2; s3[tid] = w3; s4[tid] = w4;
         __syncthreads();
         const int cnt = min(kSrcTile, it.nsrc - base);
-#pragma unroll 2
-        for (int jj = 0; jj < cnt; jj++) {
-            const double2 a = s0[jj], b = s1[jj], cc = s2[jj], d = s3[jj], e = s4[jj];
+        for (int sb = 0; sb < cnt; sb += kDescPoints) {
+            const int se = min(sb + kDescPoints, cnt);
+            const desc_float *d = desc_at(E.blk, (it.src0 + base + sb) / kDescPoints);
+            float slo[3], shi[3], gap2 = INFINITY;
 #pragma unroll
-            for (int t = 0; t < T; t++)
-                pair_f64(tx[t], ty[t], tz[t], a.x, a.y, b.x, b.y, cc.x, cc.y, d.x, d.y, e.x, e2, c375e2, acc[t]);
+            for (int k = 0; k < 3; k++) { slo[k] = d[k]; shi[k] = d[3 + k]; }
+#pragma unroll
+            for (int t = 0; t < T; t++) {
+                float lo[3], hi[3];
+#pragma unroll
+                for (int k = 0; k < 3; k++) { lo[k] = tbox[t][k]; hi[k] = tbox[t][3 + k]; }
+                gap2 = fminf(gap2, box_gap2(lo, hi, slo, shi));
+            }
+            if (gap2 > kFarBoxGap2 && gap2 > kSplitGapRatio2F64 * d[9]) {  // wave-uniform
+                far_block_f64<T>(S, sb, se, tx, ty, tz, (double)d[6] * eps, (double)d[7] * eps, (double)d[8] * eps, e2,
+                                 acc);
+            } else {
+#pragma unroll 2
+                for (int jj = sb; jj < se; jj++) {
+                    const double2 A = S.a[jj], B = S.b[jj], C = S.c[jj], D = S.d[jj];
+                    const double nz = S.e[jj].x;
+#pragma unroll
+                    for (int t = 0; t < T; t++)
+                        pair_f64(tx[t], ty[t], tz[t], A.x, A.y, B.x, B.y, C.x, C.y, D.x, D.y, nz, e2, c375e2, acc[t]);
+                }
+            }
         }
     }
     const int N = E.N;

@@ -152,7 +152,7 @@ static EnsDesc ensemble_desc(mrs_ensemble *E, int prec, const PairCfg &c) {
     d.fext = E->has_ext ? E->fext.as<double>() : nullptr;
     d.next = E->has_ext ? E->next.as<double>() : nullptr;
     d.Xin_aos = nullptr;
-    set_records(d, E->rec.p, E->N, prec == MRS_FP32C);
+    set_records(d, E->rec.p, E->N, prec == MRS_FP32C, c.mode != PAIR_SPLIT);
     d.part = E->part.as<double>();
     d.eps = E->eps;
     d.inv_eps = 1.0 / E->eps;
@@ -741,8 +741,8 @@ static void eval_layout(EvalLayout &L, int64_t n, const EnsDesc &args, int p, co
     EnsDesc &d = L.d;
     d = args;
     d.K = c.K;
-    // FP32C block descriptors only for the tiled kernels (k_pack_aos writes them)
-    set_records(d, sc.rec, n, p == MRS_FP32C && c.mode != PAIR_SPLIT);
+    // block descriptors only for the tiled kernels (k_pack_aos writes them)
+    set_records(d, sc.rec, n, p == MRS_FP32C, c.mode != PAIR_SPLIT);
     d.part = sc.part;
     L.P.prec = p;
     add_items(L.P, 0, n, 0, c);

@@ -46,3 +46,24 @@ def test_block_paths_match_oracle(mrs, gap):
     finally:
         mrs.mrs_context_destroy(c)
 
+
+
+@pytest.mark.parametrize("gap", [0.0, 20.0, 30.0, 500.0])
+def test_fp64_block_paths_match_oracle(mrs, gap):
+    """FP64 (1e-12): blocks nearer and farther than four half-diagonals (about
+    7 eps each here), one and two targets per lane, both schedules; also at a
+    large offset from the origin."""
+    c = mrs.mrs_context_create(0)
+    try:
+        for shift in (0.0, 100.0):
+            X, f, n = _clusters(gap, 50 + int(gap))
+            X = X + shift
+            Uo, Wo = oracle.mrs_eval(X, f, n, EPS, 1.0)
+            for cfg in [(0, 1, 0, 0), (0, 2, 0, 0), (0, 2, 0, 1), (0, 1, 7, 0)]:
+                mrs.mrs_tune_set(c, len(X), 0, *cfg)
+                U, W = eval_dev(mrs, c, X, f, n, EPS, 1.0, 0)
+                eu, ew = oracle.rel_err(U, Uo), oracle.rel_err(W, Wo)
+                say(f"fp64 gap {gap} shift {shift} cfg {cfg}: U {eu:.2e} W {ew:.2e}")
+                assert eu <= 1e-12 and ew <= 1e-12, cfg
+    finally:
+        mrs.mrs_context_destroy(c)
