@@ -76,17 +76,6 @@ __device__ __forceinline__ void pair_core_f32(float rx, float ry, float rz, floa
     p[5] = fmaf(-fy, gx, fmaf(fx, gy, fmaf(b, rz, fmaf(h4, nz, p[5]))));
 }
 
-// The same for a source record (a = hi + fx, b = lo + fy, c = fz, n); returns R^2.
-template <bool MASK>
-__device__ __forceinline__ float pair_f32(float thx, float thy, float thz, float tlx, float tly,
-                                          float tlz, const float4 A, const float4 B,
-                                          const float4 C, float *p) {
-    float rx, ry, rz;
-    const float R2 = sep_f32(thx, thy, thz, tlx, tly, tlz, A.x, A.y, A.z, B.x, B.y, B.z, rx, ry, rz);
-    pair_core_f32<MASK>(rx, ry, rz, R2, A.w, B.w, C.x, C.y, C.z, C.w, p);
-    return R2;
-}
-
 // Same in FP64 for the separation r = x_target - X_source:
 // p += (8 pi mu U, 8 pi mu Omega) in unscaled units (e2 = eps^2, c375e2 =
 // 3.75 eps^2), or the eps-unit form with e2 = 1, c375e2 = 3.75.
@@ -105,7 +94,7 @@ __device__ __forceinline__ void pair_f64_r(double rx, double ry, double rz, doub
     const double fr = fma(fz, rz, fma(fy, ry, fx * rx));
     const double nr = fma(nz, rz, fma(ny, ry, nx * rx));
     const double a = q3 * fr, b = h5 * nr;
-    const double gx = h3 * rx, gy = h3 * ry, gz = h3 * rz;  // see pair_f32
+    const double gx = h3 * rx, gy = h3 * ry, gz = h3 * rz;  // see pair_core_f32
     p[0] = fma(-nz, gy, fma(ny, gz, fma(a, rx, fma(h1, fx, p[0]))));
     p[1] = fma(-nx, gz, fma(nz, gx, fma(a, ry, fma(h1, fy, p[1]))));
     p[2] = fma(-ny, gx, fma(nx, gy, fma(a, rz, fma(h1, fz, p[2]))));

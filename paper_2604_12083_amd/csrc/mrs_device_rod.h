@@ -45,20 +45,22 @@ __device__ __forceinline__ RecF32 make_rec_f32(double x, double y, double z, dou
     return r;
 }
 
-__device__ __forceinline__ void store_rec(int prec, void *rec, int i, double x, double y, double z,
-                                          double fx, double fy, double fz, double nx, double ny,
-                                          double nz, double inv_eps) {
+// An FP32C record in FP64 form: hi + lo has at most 49 significant bits.
+__device__ __forceinline__ RecF64 widen(const RecF32 &r) {
     FP_STRICT;
-    if (prec == 1) {
-        reinterpret_cast<RecF32 *>(rec)[i] = make_rec_f32(x, y, z, fx, fy, fz, nx, ny, nz, inv_eps);
-    } else {
-        RecF64 r;
-        r.x = x; r.y = y; r.z = z;
-        r.fx = fx; r.fy = fy; r.fz = fz;
-        r.nx = nx; r.ny = ny; r.nz = nz;
-        r.pad = 0.0;
-        reinterpret_cast<RecF64 *>(rec)[i] = r;
+    return {(double)r.a.x + (double)r.b.x, (double)r.a.y + (double)r.b.y, (double)r.a.z + (double)r.b.z,
+            (double)r.a.w, (double)r.b.w, (double)r.c.x, (double)r.c.y, (double)r.c.z, (double)r.c.w, 0.0};
+}
+
+__device__ __forceinline__ void store_rec(const EnsDesc &E, int i, double x, double y, double z, double fx, double fy,
+                                          double fz, double nx, double ny, double nz) {
+    if (E.form == REC_F64) {
+        reinterpret_cast<RecF64 *>(E.rec)[i] = {x, y, z, fx, fy, fz, nx, ny, nz, 0.0};
+        return;
     }
+    const RecF32 r = make_rec_f32(x, y, z, fx, fy, fz, nx, ny, nz, E.inv_eps);
+    if (E.form == REC_F32) reinterpret_cast<RecF32 *>(E.rec)[i] = r;
+    else reinterpret_cast<RecF64 *>(E.rec)[i] = widen(r);
 }
 
 // The record of point i of a one-shot evaluation, from the caller's row-major
@@ -69,6 +71,7 @@ __device__ __forceinline__ RecF32 input_rec_f32(const EnsDesc &E, int i) {
 }
 
 __device__ __forceinline__ RecF64 input_rec_f64(const EnsDesc &E, int i) {
+    if (E.form == REC_WIDE) return widen(input_rec_f32(E, i));
     const double *X = E.Xin_aos + 3 * (size_t)i, *f = E.fext + 3 * (size_t)i, *n = E.next + 3 * (size_t)i;
     return {X[0], X[1], X[2], f[0], f[1], f[2], n[0], n[1], n[2], 0.0};
 }
@@ -240,15 +243,14 @@ __device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__re
 // Rod forces of one filament (nodes k0 .. k0 + M - 1; Sec. II.B, Alg. 1): for
 // every node, the point force and torque on the fluid, g = F_{k+1/2} -
 // F_{k-1/2} + external, m = N_{k+1/2} - N_{k-1/2} + (dX_{k+1/2} x F_{k+1/2} +
-// dX_{k-1/2} x F_{k-1/2}) / 2 + external, written as source records into
-// rec[point], or with AOS (row-major state and loads) into E.g_out, E.m_out.
+// dX_{k-1/2} x F_{k-1/2}) / 2 + external, written as source records, or with AOS (row-major state and loads) into E.g_out, E.m_out.
 // BLOCK threads walk the filament in chunks of BLOCK - 1 nodes: thread t
 // computes segment c0 - 1 + t into LDS, then node c0 + t combines its two
 // neighbouring segments (a node's result does not depend on the chunking).
 // Every thread of the block must call it.
 template <int BLOCK, bool AOS>
-__device__ __forceinline__ void rod_filament(int prec, int stage_state, int elastic, int scheme, int stage,
-                                             double dt, const EnsDesc &E, int k0, int M, void *rec) {
+__device__ __forceinline__ void rod_filament(int stage_state, int elastic, int scheme, int stage,
+                                             double dt, const EnsDesc &E, int k0, int M) {
     FP_STRICT;
     __shared__ double sF[3][BLOCK], sN[3][BLOCK], sX[3][BLOCK];
     const int N = E.N;
@@ -317,7 +319,7 @@ __device__ __forceinline__ void rod_filament(int prec, int stage_state, int elas
                     E.m_out[3 * (size_t)p + c] = m[c];
                 }
             } else {
-                store_rec(prec, rec, p, xp[0], xp[1], xp[2], g[0], g[1], g[2], m[0], m[1], m[2], E.inv_eps);
+                store_rec(E, p, xp[0], xp[1], xp[2], g[0], g[1], g[2], m[0], m[1], m[2]);
             }
         }
         if (elastic) __syncthreads();

@@ -33,6 +33,12 @@ struct alignas(16) RecF64 {
     double x, y, z, fx, fy, fz, nx, ny, nz, pad;
 };
 
+// Form of an ensemble's source records.  REC_WIDE holds the values of the
+// FP32C records (hi + lo, which is exact in double, and the FP32 loads) in
+// FP64 records, for FP32C ensembles that the FP64 kernels sum faster; units of
+// eps, like REC_F32.
+enum RecForm : int { REC_F64 = 0, REC_F32 = 1, REC_WIDE = 2 };
+
 // Source-block descriptor of the tiled pair kernels (one per aligned 64-point
 // block, in units of eps), padded to 64 bytes.
 constexpr int kDescFloats = 16;
@@ -64,6 +70,7 @@ struct EnsDesc {
     const double *fext, *next;  // external loads (SoA, or AoS when aos_io), may be null
     const double *Xin_aos;      // AoS positions when aos_io
     void *rec;         // source records (RecF32 or RecF64), N entries
+    int32_t form;      // RecForm of the records
     // tiled pair kernels: per aligned 64-point block the descriptor
     // (kDescFloats floats, in units of eps: widened hi-part box lo[3], hi[3],
     // centre[3], squared half-diagonal), and for FP32C per point its position
@@ -75,6 +82,7 @@ struct EnsDesc {
     double *part;      // split-K partial sums [K][6][N]
     double *g_out, *m_out;  // rod loads, row-major (k_rod_forces_aos)
     double eps, inv_eps, mu;
+    double rec_eps;    // eps in the units of FP64-kind records: eps (REC_F64) or 1 (REC_WIDE)
     double cU, cW;     // 1/(8 pi mu) and the Omega scale of the record form
     double a[3], b[3], om0[3], ds;
     double dt;         // step size used when a launch passes dt = NaN
@@ -146,25 +154,27 @@ enum Epilogue : int {
 enum RkScheme : int { RK_SCHEME_RK4 = 0, RK_SCHEME_RK2 = 1 };
 
 // Points the records of an ensemble of n points at rec (a buffer of
-// rec_buffer_bytes(n)); with desc the block descriptors and (FP32C) the
-// anchored positions follow them, otherwise both are null (no tiled kernel
-// reads them).
-inline void set_records(EnsDesc &d, void *rec, int64_t n, bool fp32c, bool desc) {
+// rec_buffer_bytes(n)) in the given form; with desc the block descriptors and
+// (REC_F32) the anchored positions follow them, otherwise both are null (no
+// tiled kernel reads them).
+inline void set_records(EnsDesc &d, void *rec, int64_t n, RecForm form, bool desc) {
     d.rec = rec;
+    d.form = form;
+    d.rec_eps = form == REC_F64 ? d.eps : 1.0;
     char *b = static_cast<char *>(rec);
-    const size_t r = (size_t)n * (fp32c ? sizeof(RecF32) : sizeof(RecF64));
-    const size_t w = fp32c ? (size_t)n * sizeof(float4) : 0;
-    d.wanch = desc && fp32c ? reinterpret_cast<float4 *>(b + r) : nullptr;
+    const bool f32 = form == REC_F32;
+    const size_t r = (size_t)n * (f32 ? sizeof(RecF32) : sizeof(RecF64));
+    const size_t w = f32 ? (size_t)n * sizeof(float4) : 0;
+    d.wanch = desc && f32 ? reinterpret_cast<float4 *>(b + r) : nullptr;
     d.blk = desc ? reinterpret_cast<float *>(b + r + w) : nullptr;
 }
 
 // Launch wrappers (mrs_pairs.hip, mrs_kernels.hip).  All return the launch's hipError_t.
-hipError_t launch_pack_aos(int prec, const EnsDesc *d_desc, const EnsDesc &h_desc,
-                           hipStream_t s);
+hipError_t launch_pack_aos(const EnsDesc *d_desc, const EnsDesc &h_desc, hipStream_t s);
 // elastic < 0: every ensemble uses its own EnsDesc::elastic.  The waveform
 // time of the launch is clock + c dt, c the node of RK stage `stage` of
 // `scheme` (0 for stage 0); dt = NaN: every ensemble uses its own dt.
-hipError_t launch_rod_forces(int prec, int stage_state, int elastic, int scheme, int stage, double dt,
+hipError_t launch_rod_forces(int stage_state, int elastic, int scheme, int stage, double dt,
                              const EnsDesc *d_desc, const RodItem *d_items, int n_items, hipStream_t s);
 // Rod forces of h_desc.n_fil >= 1 filaments on row-major arrays (h_desc.X, D,
 // fext, next; g_out, m_out).
@@ -185,7 +195,7 @@ hipError_t launch_pairs(int prec, int mode, int tpl, const EnsDesc *d_desc, cons
 // inputs.  Up to kDirectMaxPoints points every block forms all records again
 // for little (at 2,048 points a fortieth of its pair work).
 constexpr int kDirectMaxPoints = 2048;
-hipError_t launch_eval_direct(int prec, const EnsDesc &h_desc, hipStream_t s);
+hipError_t launch_eval_direct(const EnsDesc &h_desc, hipStream_t s);
 // Resident blocks per CU of the persistent tiled pair kernel.
 int pairs_resident_blocks(int prec, int tpl);
 // dt = NaN: every ensemble uses its own EnsDesc::dt.

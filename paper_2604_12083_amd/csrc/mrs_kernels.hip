@@ -52,12 +52,12 @@ __device__ __forceinline__ void block_desc_from_x(const EnsDesc &E, const double
 
 // One thread per point; with block descriptors (E.blk set) every wave
 // (64 consecutive points, block-aligned) also writes its block's descriptor.
-__global__ __launch_bounds__(kBlock) void k_pack_aos(int prec, const EnsDesc *__restrict__ desc) {
+__global__ __launch_bounds__(kBlock) void k_pack_aos(const EnsDesc *__restrict__ desc) {
     const EnsDesc &E = desc[0];
     const int i = blockIdx.x * kBlock + threadIdx.x;
     const double *X = E.Xin_aos;
     if (i < E.N) {
-        if (prec == 1) reinterpret_cast<RecF32 *>(E.rec)[i] = input_rec_f32(E, i);
+        if (E.form == REC_F32) reinterpret_cast<RecF32 *>(E.rec)[i] = input_rec_f32(E, i);
         else reinterpret_cast<RecF64 *>(E.rec)[i] = input_rec_f64(E, i);
     }
     const int b = i / kDescPoints;  // wave-uniform
@@ -67,8 +67,8 @@ __global__ __launch_bounds__(kBlock) void k_pack_aos(int prec, const EnsDesc *__
 // One block per filament (rod_filament), or one wave per source-block
 // descriptor (RodItem with fil < 0): the descriptors depend only on the
 // positions, so they are written beside the filaments' records.
-__global__ __launch_bounds__(kBlock) void k_rod_forces(int prec, int stage_state, int elastic, int scheme,
-                                                       int stage, double dt, const EnsDesc *__restrict__ desc,
+__global__ __launch_bounds__(kBlock) void k_rod_forces(int stage_state, int elastic, int scheme, int stage,
+                                                        double dt, const EnsDesc *__restrict__ desc,
                                                        const RodItem *__restrict__ items) {
     const RodItem it = items[blockIdx.x];
     const EnsDesc &E = desc[it.ens];
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kBlock) void k_rod_forces(int prec, int stage_state
         return;
     }
     const int k0 = E.off[it.fil];
-    rod_filament<kBlock, false>(prec, stage_state, elastic, scheme, stage, dt, E, k0, E.off[it.fil + 1] - k0, E.rec);
+    rod_filament<kBlock, false>(stage_state, elastic, scheme, stage, dt, E, k0, E.off[it.fil + 1] - k0);
 }
 
 // mrs_rod_forces_device: one block per filament on the caller's row-major
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kBlock) void k_rod_forces_aos(const EnsDesc E, cons
     const int f = blockIdx.x;
     const int k0 = off.list ? off.list[f] : (off.step ? f * off.step : off.v[f]);
     const int k1 = off.list ? off.list[f + 1] : (off.step ? k0 + off.step : off.v[f + 1]);
-    rod_filament<kBlock, true>(0, 0, 1, 0, 0, 0.0, E, k0, k1 - k0, nullptr);
+    rod_filament<kBlock, true>(0, 1, 0, 0, 0.0, E, k0, k1 - k0);
 }
 
 // ------------------------------------------------------------ Lennard-Jones
@@ -401,17 +401,17 @@ hipError_t launch_clock_probe(int64_t cycles, uint64_t *out, hipStream_t s) {
 
 static inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-hipError_t launch_pack_aos(int prec, const EnsDesc *d_desc, const EnsDesc &h_desc, hipStream_t s) {
+hipError_t launch_pack_aos(const EnsDesc *d_desc, const EnsDesc &h_desc, hipStream_t s) {
     if (h_desc.N == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pack_aos, dim3(blocks_for(h_desc.N)), dim3(kBlock), 0, s, prec, d_desc);
+    hipLaunchKernelGGL(k_pack_aos, dim3(blocks_for(h_desc.N)), dim3(kBlock), 0, s, d_desc);
     return hipGetLastError();
 }
 
-hipError_t launch_rod_forces(int prec, int stage_state, int elastic, int scheme, int stage, double dt,
+hipError_t launch_rod_forces(int stage_state, int elastic, int scheme, int stage, double dt,
                              const EnsDesc *d_desc, const RodItem *d_items, int n_items, hipStream_t s) {
     if (n_items == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rod_forces, dim3(n_items), dim3(kBlock), 0, s, prec, stage_state, elastic, scheme,
-                       stage, dt, d_desc, d_items);
+    hipLaunchKernelGGL(k_rod_forces, dim3(n_items), dim3(kBlock), 0, s, stage_state, elastic, scheme, stage, dt,
+                       d_desc, d_items);
     return hipGetLastError();
 }
 

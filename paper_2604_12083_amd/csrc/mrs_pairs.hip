@@ -109,17 +109,43 @@ __device__ __forceinline__ void wave_sync() {
 // source at a time, as broadcasts).  w is the anchored position, m = 1.5 w x n
 // and k = w x f the source's parts of the split cross products (far_block),
 // h + l the position in units of eps.
+template <int SLOTS>
 struct SrcStage {
-    float4 W[kSrcTile];   // w, fx
-    float4 F[kSrcTile];   // fy, fz, nx, ny
-    float4 M[kSrcTile];   // nz, m
-    float4 K[kSrcTile];   // k, lx
-    float4 H[kSrcTile];   // h, ly
-    float lz[kSrcTile];
+    float4 W[SLOTS];   // w, fx
+    float4 F[SLOTS];   // fy, fz, nx, ny
+    float4 M[SLOTS];   // nz, m
+    float4 K[SLOTS];   // k, lx
+    float4 H[SLOTS];   // h, ly
+    float lz[SLOTS];
+    // Stages source i of E at slot j; absent (i < 0): zero loads at the anchor
+    // and the origin.  A source with contact forces enters the FP32 sums with
+    // zero loads; the FP64 pass evaluates it with its own loads.
+    __device__ __forceinline__ void put(const EnsDesc &E, int j, int i) {
+        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, c = a, w = a;
+        if (i >= 0) {
+            const RecF32 r = reinterpret_cast<const RecF32 *>(E.rec)[i];
+            a = r.a; b = r.b; c = r.c;
+            w = E.wanch[i];
+            if (E.lj_mask && ((E.lj_mask[i / kLjMaskPoints] >> (i % kLjMaskPoints)) & 1)) {
+                a.w = 0.0f; b.w = 0.0f;
+                c = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+        const float fx = a.w, fy = b.w, fz = c.x, nx = c.y, ny = c.z, nz = c.w;
+        W[j] = make_float4(w.x, w.y, w.z, fx);
+        F[j] = make_float4(fy, fz, nx, ny);
+        // |w| < |r| in the blocks that use them: m and k overflow no earlier
+        // (up to their factor) than the products n . r and f . r
+        M[j] = make_float4(nz, 1.5f * fmaf(w.y, nz, -(w.z * ny)), 1.5f * fmaf(w.z, nx, -(w.x * nz)),
+                           1.5f * fmaf(w.x, ny, -(w.y * nx)));
+        K[j] = make_float4(fmaf(w.y, fz, -(w.z * fy)), fmaf(w.z, fx, -(w.x * fz)), fmaf(w.x, fy, -(w.y * fx)), b.x);
+        H[j] = make_float4(a.x, a.y, a.z, b.y);
+        lz[j] = b.z;
+    }
 };
 
-// Sums of the 64 staged sources from sb on into p, for targets at u relative
-// to the block's anchor (no near pair in the block).
+// Sums of the staged sources [sb, se) (of one block, an even number) into p,
+// for targets at u relative to the block's anchor (no near pair in the block).
 //
 // The loop is bound by VALU issue (the launch issues one instruction per 2.4
 // clocks and SIMD, its instruction mix allows one per 2.35) and by the clock
@@ -139,8 +165,8 @@ struct SrcStage {
 // -> 151.5 us at 12,800 (one target per lane, MI355X).  Two sources at a time
 // with their reciprocal roots together: 0.7% faster than one at a time at
 // 256,000 points, 2% at 51,000 (swimmers); four at a time spills.
-template <int T, bool REMOTE>
-__device__ __forceinline__ void far_block(const SrcStage &S, int sb, const float (&ux)[T], const float (&uy)[T],
+template <int T, bool REMOTE, class STAGE>
+__device__ __forceinline__ void far_block(const STAGE &S, int sb, int se, const float (&ux)[T], const float (&uy)[T],
                                           const float (&uz)[T], float (&p)[T][6]) {
     constexpr int G = 2;
     float sn[T][3], sf[T][3], o[T][3];
@@ -149,7 +175,7 @@ __device__ __forceinline__ void far_block(const SrcStage &S, int sb, const float
 #pragma unroll
         for (int k = 0; k < 3; k++) { sn[t][k] = 0.0f; sf[t][k] = 0.0f; o[t][k] = 0.0f; }
 #pragma unroll 2
-    for (int j0 = sb; j0 < sb + kKahanBlock; j0 += G) {
+    for (int j0 = sb; j0 < se; j0 += G) {
         float rx[G][T], ry[G][T], rz[G][T], q[G][T], fx[G];
 #pragma unroll
         for (int g = 0; g < G; g++) {
@@ -230,7 +256,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
                                                            const PairItem *__restrict__ items, int n_items,
                                                            uint32_t *queue) {
     static_assert(!QUAD || T == 1, "four-wave source split: one target per lane");
-    __shared__ SrcStage S;
+    __shared__ SrcStage<kSrcTile> S;
     static_assert(kSrcTile / kKahanBlock == kBlock / 64 && kKahanBlock == kDescPoints,
                   "one source block (one descriptor) per wave");
     __shared__ int sNext;
@@ -271,33 +297,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
         }
         // this wave stages source block tid / 64 (its anchored positions
         // from the descriptors); padding lanes stage zero loads
-        const int j = base + tid;
-        const bool real = j < it.nsrc;
-        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, cc = a, w = a;
-        if (real) {
-            const RecF32 r = rec[it.src0 + j];
-            a = r.a; b = r.b; cc = r.c;
-            w = E.wanch[it.src0 + j];
-        }
-        // a source with contact forces enters the FP32 sums with zero loads;
-        // the FP64 pass evaluates it with its own loads
-        if (E.lj_mask && real) {
-            const int jg = it.src0 + j;
-            if ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1) {
-                a.w = 0.0f; b.w = 0.0f;
-                cc = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-        }
-        const float fx = a.w, fy = b.w, fz = cc.x, nx = cc.y, ny = cc.z, nz = cc.w;
-        S.W[tid] = make_float4(w.x, w.y, w.z, fx);
-        S.F[tid] = make_float4(fy, fz, nx, ny);
-        // |w| < |r| in the blocks that use them: m and k overflow no earlier
-        // (up to their factor) than the products n . r and f . r
-        S.M[tid] = make_float4(nz, 1.5f * fmaf(w.y, nz, -(w.z * ny)), 1.5f * fmaf(w.z, nx, -(w.x * nz)),
-                               1.5f * fmaf(w.x, ny, -(w.y * nx)));
-        S.K[tid] = make_float4(fmaf(w.y, fz, -(w.z * fy)), fmaf(w.z, fx, -(w.x * fz)), fmaf(w.x, fy, -(w.y * fx)), b.x);
-        S.H[tid] = make_float4(a.x, a.y, a.z, b.y);
-        S.lz[tid] = b.z;
+        S.put(E, tid, base + tid < it.nsrc ? it.src0 + base + tid : -1);
         if (QUAD) wave_sync();
         else __syncthreads();
         const int cnt = min(kSrcTile, it.nsrc - base);
@@ -348,8 +348,8 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
                     uy[t] = (thy[t] - bx[7]) + tly[t];
                     uz[t] = (thz[t] - bx[8]) + tlz[t];
                 }
-                if (gap2 > kRemoteBoxGap2) far_block<T, true>(S, sb, ux, uy, uz, p);
-                else far_block<T, false>(S, sb, ux, uy, uz, p);
+                if (gap2 > kRemoteBoxGap2) far_block<T, true>(S, sb, sb + kKahanBlock, ux, uy, uz, p);
+                else far_block<T, false>(S, sb, sb + kKahanBlock, ux, uy, uz, p);
             } else if (gap2 > kFarBoxGap2) {
                 // wave-uniform: no near pair, exact hi/lo separation
 #pragma unroll 2
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
         // the four waves' sums for the same targets, added in wave order (the
         // staged sources are no longer needed)
         double *sum = reinterpret_cast<double *>(&S);  // [6][kBlock]
-        static_assert(sizeof(SrcStage) >= 6 * kBlock * sizeof(double), "sums of four waves");
+        static_assert(sizeof(S) >= 6 * kBlock * sizeof(double), "sums of four waves");
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 6; k++) sum[k * kBlock + tid] = pn[0][k];
@@ -456,9 +456,24 @@ constexpr float kSplitGapRatio2F64 = 16.0f;
 
 // Sources of one staged round of the FP64 kernel: x, y | z, fx | fy, fz |
 // nx, ny | nz, m | k with m = w x n, k = w x f.
+template <int SLOTS>
 struct SrcStageF64 {
-    double2 a[kSrcTile], b[kSrcTile], c[kSrcTile], d[kSrcTile], e[kSrcTile], f[kSrcTile], g[kSrcTile];
-    double h[kSrcTile];
+    double2 a[SLOTS], b[SLOTS], c[SLOTS], d[SLOTS], e[SLOTS], f[SLOTS], g[SLOTS];
+    double h[SLOTS];
+    // Stages source i of E at slot j; its block's descriptor is wave-uniform.
+    __device__ __forceinline__ void put(const EnsDesc &E, int j, int i) {
+        const double2 *src = reinterpret_cast<const double2 *>(E.rec) + (size_t)i * 5;
+        const double2 w0 = src[0], w1 = src[1], w2 = src[2], w3 = src[3], w4 = src[4];
+        const desc_float *bd = desc_at(E.blk, __builtin_amdgcn_readfirstlane(i / kDescPoints));
+        const double wx = w0.x - (double)bd[6] * E.rec_eps, wy = w0.y - (double)bd[7] * E.rec_eps,
+                     wz = w1.x - (double)bd[8] * E.rec_eps;
+        const double fx = w1.y, fy = w2.x, fz = w2.y, nx = w3.x, ny = w3.y, nz = w4.x;
+        a[j] = w0; b[j] = w1; c[j] = w2; d[j] = w3;
+        e[j] = make_double2(nz, fma(wy, nz, -(wz * ny)));
+        f[j] = make_double2(fma(wz, nx, -(wx * nz)), fma(wx, ny, -(wy * nx)));
+        g[j] = make_double2(fma(wy, fz, -(wz * fy)), fma(wz, fx, -(wx * fz)));
+        h[j] = fma(wx, fy, -(wy * fx));
+    }
 };
 
 // Sums of the staged sources [sb, se) into acc for targets at (tx, ty, tz), by
@@ -469,8 +484,8 @@ struct SrcStageF64 {
 // targets per lane, 124 and four before) cost nothing: pair kernel 4.72 ->
 // 4.42 ms at 51,200 points, 308 -> 296 us at 12,800 (MI355X; there the last of
 // its 1.6 rounds of blocks weighs more).
-template <int T>
-__device__ __forceinline__ void far_block_f64(const SrcStageF64 &S, int sb, int se, const double (&tx)[T],
+template <int T, class STAGE>
+__device__ __forceinline__ void far_block_f64(const STAGE &S, int sb, int se, const double (&tx)[T],
                                               const double (&ty)[T], const double (&tz)[T], double cx, double cy,
                                               double cz, double e2, double (&acc)[T][6]) {
     const double c15e2 = 1.5 * e2, c375e2 = 3.75 * e2;
@@ -530,7 +545,7 @@ template <int T, bool PERSIST>
 __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const EnsDesc *__restrict__ desc,
                                                            const PairItem *__restrict__ items, int n_items,
                                                            uint32_t *queue) {
-    __shared__ SrcStageF64 S;
+    __shared__ SrcStageF64<kSrcTile> S;
     __shared__ int sNext;
     int idx = PERSIST ? claim_item(queue, &sNext) : (int)blockIdx.x;
     while (idx < n_items) {
@@ -538,7 +553,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
     const EnsDesc &E = desc[it.ens];
     const RecF64 *__restrict__ rec = reinterpret_cast<const RecF64 *>(E.rec);
     const int tid = threadIdx.x;
-    const double eps = E.eps, e2 = eps * eps, c375e2 = 3.75 * e2;
+    const double eps = E.rec_eps, e2 = eps * eps, c375e2 = 3.75 * e2;
     double tx[T], ty[T], tz[T], acc[T][6];
     const desc_float *tbox[T];  // descriptors of the blocks this wave's targets lie in (wave-uniform)
 #pragma unroll
@@ -551,23 +566,10 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
 #pragma unroll
         for (int k = 0; k < 6; k++) acc[t][k] = 0.0;
     }
-    const double2 *__restrict__ rw = reinterpret_cast<const double2 *>(rec);
     for (int base = 0; base < it.nsrc; base += kSrcTile) {
         __syncthreads();
         // this wave stages the source block tid / 64 of the round
-        const int j = base + tid;
-        if (j < it.nsrc) {
-            const double2 *src = rw + (size_t)(it.src0 + j) * 5;
-            const double2 w0 = src[0], w1 = src[1], w2 = src[2], w3 = src[3], w4 = src[4];
-            const desc_float *d = desc_at(E.blk, __builtin_amdgcn_readfirstlane((it.src0 + j) / kDescPoints));
-            const double wx = w0.x - (double)d[6] * eps, wy = w0.y - (double)d[7] * eps, wz = w1.x - (double)d[8] * eps;
-            const double fx = w1.y, fy = w2.x, fz = w2.y, nx = w3.x, ny = w3.y, nz = w4.x;
-            S.a[tid] = w0; S.b[tid] = w1; S.c[tid] = w2; S.d[tid] = w3;
-            S.e[tid] = make_double2(nz, fma(wy, nz, -(wz * ny)));
-            S.f[tid] = make_double2(fma(wz, nx, -(wx * nz)), fma(wx, ny, -(wy * nx)));
-            S.g[tid] = make_double2(fma(wy, fz, -(wz * fy)), fma(wz, fx, -(wx * fz)));
-            S.h[tid] = fma(wx, fy, -(wy * fx));
-        }
+        if (base + tid < it.nsrc) S.put(E, tid, it.src0 + base + tid);
         __syncthreads();
         const int cnt = min(kSrcTile, it.nsrc - base);
         for (int sb = 0; sb < cnt; sb += kDescPoints) {
@@ -615,135 +617,64 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
 
 // Small-ensemble pair kernel: each wave owns kSplitTargetsPerWave targets and
 // its 64 lanes stride over the item's sources; per-lane sums are combined in
-// FP64 with a butterfly of wave shuffles in a fixed order.
-// Sources staged through LDS per round by the whole block (its waves share
-// them): FP32C rounds are the 1,024-source compensated chunks of the loop
-// below (48 KB), FP64 rounds 256 sources (20 KB).  A lane reads its sources
-// in the same order as straight from the records, so the staging changes no
-// result; it replaces one dependent global load per lane and 64 sources by
-// one per round.
-constexpr int kSplitPerLane = 16;  // FP32C: sources per lane between compensated updates
-constexpr int kSplitRoundF32 = 64 * kSplitPerLane, kSplitRoundF64 = kBlock;
-
+// FP64 with a butterfly of wave shuffles in a fixed order.  Sources are staged
+// through LDS 256 at a time by the whole block (its waves share them).
+//
+// The records are of the FP64 kind in both precisions (REC_WIDE for FP32C).
+// The launch is bound by latency and by the FP64 pairs near the targets, so an
+// FP32 pass over the far sources only added to it (two passes, 1,020 points
+// in contact: 14.6 us; 9.1 us so, and 46.3 -> 27.0 us in a batch of eight;
+// 512 points of 128-point filaments 8.5 -> 6.6 and 14.7 -> 11.6 us; MI355X).
 //
 // DIRECT: the whole of a one-shot evaluation (one source chunk): the records
 // are formed from the caller's row-major arrays as they are staged and U,
 // Omega are written in place of the partial sums, with the same operations as
 // the pack and reduction kernels.
-template <int PREC, bool DIRECT>
+constexpr int kSplitRound = kBlock;
+
+template <bool DIRECT>
 __device__ __forceinline__ void split_item(const EnsDesc &E, const PairItem it) {
     constexpr int TW = kSplitTargetsPerWave;
     static_assert(sizeof(RecF32) == 48 && sizeof(RecF64) == 80, "record layouts");
-    __shared__ float4 sBuf[PREC == 1 ? 3 * kSplitRoundF32 : 5 * kSplitRoundF64];
+    __shared__ RecF64 sRec[kSplitRound];
     const int tid = threadIdx.x, lane = tid & 63;
     const int tb = (tid >> 6) * TW;
     // a wave without targets still stages sources and meets every barrier
     const bool active = tb < it.ntgt;  // wave-uniform
-    double out[TW][6];
-    if (PREC == 1) {
-        const RecF32 *__restrict__ rec = reinterpret_cast<const RecF32 *>(E.rec);
-        const auto load = [&](int i) { return DIRECT ? input_rec_f32(E, i) : rec[i]; };
-        RecF32 *sRec = reinterpret_cast<RecF32 *>(sBuf);
-        float thx[TW], thy[TW], thz[TW], tlx[TW], tly[TW], tlz[TW], s[TW][6], c[TW][6];
-        double pn[TW][6];
+    const RecF64 *__restrict__ rec = reinterpret_cast<const RecF64 *>(E.rec);
+    const auto load = [&](int i) { return DIRECT ? input_rec_f64(E, i) : rec[i]; };
+    const double e2 = E.rec_eps * E.rec_eps, c375e2 = 3.75 * e2;
+    double tx[TW], ty[TW], tz[TW], acc[TW][6];
 #pragma unroll
-        for (int t = 0; t < TW; t++) {
-            const RecF32 r = load(it.tgt0 + min(tb + t, it.ntgt - 1));
-            thx[t] = r.a.x; thy[t] = r.a.y; thz[t] = r.a.z;
-            tlx[t] = r.b.x; tly[t] = r.b.y; tlz[t] = r.b.z;
+    for (int t = 0; t < TW; t++) {
+        const RecF64 r = load(it.tgt0 + min(tb + t, it.ntgt - 1));
+        tx[t] = r.x; ty[t] = r.y; tz[t] = r.z;
 #pragma unroll
-            for (int k = 0; k < 6; k++) { s[t][k] = 0.f; c[t][k] = 0.f; pn[t][k] = 0.0; }
-        }
-        for (int j0 = 0; j0 < it.nsrc; j0 += kSplitRoundF32) {
-            const int cnt = min(kSplitRoundF32, it.nsrc - j0);
-            __syncthreads();
-            for (int q = tid; q < cnt; q += kBlock) sRec[q] = load(it.src0 + j0 + q);
-            __syncthreads();
-            if (!active) continue;
-            float p[TW][6];
-            float rmin = kNearR2;
-#pragma unroll
-            for (int t = 0; t < TW; t++)
-#pragma unroll
-                for (int k = 0; k < 6; k++) p[t][k] = 0.f;
-            for (int j = lane; j < cnt; j += 64) {
-                const int jg = it.src0 + j0 + j;
-                if (!DIRECT && E.lj_mask && ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1)) {
-                    rmin = 0.0f;  // a source with contact forces: FP64 below
-                    continue;
-                }
-                const RecF32 r = sRec[j];
-#pragma unroll
-                for (int t = 0; t < TW; t++)
-                    rmin = fminf(rmin, pair_f32<true>(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], r.a, r.b, r.c, p[t]));
-            }
-#pragma unroll
-            for (int t = 0; t < TW; t++)
-#pragma unroll
-                for (int k = 0; k < 6; k++) kahan_add(s[t][k], c[t][k], p[t][k]);
-            if (rmin < kNearR2) {  // near pairs and contact-force blocks of this lane's sources: FP64
-                for (int j = lane; j < cnt; j += 64) {
-                    const RecF32 r = sRec[j];
-                    const int jg = it.src0 + j0 + j;
-                    const bool strong = !DIRECT && E.lj_mask && ((E.lj_mask[jg / kLjMaskPoints] >> (jg % kLjMaskPoints)) & 1);
-#pragma unroll
-                    for (int t = 0; t < TW; t++) {
-                        float rx, ry, rz;
-                        if (strong || sep_f32(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], r.a.x, r.a.y, r.a.z, r.b.x,
-                                              r.b.y, r.b.z, rx, ry, rz) < kNearR2)
-                            near_pair_f64(thx[t], thy[t], thz[t], tlx[t], tly[t], tlz[t], r.a.x, r.a.y, r.a.z, r.b.x,
-                                          r.b.y, r.b.z, r.a.w, r.b.w, r.c.x, r.c.y, r.c.z, r.c.w, pn[t]);
-                    }
-                }
-            }
-        }
-        if (!active) return;  // no barrier follows
-#pragma unroll
-        for (int t = 0; t < TW; t++)
-#pragma unroll
-            for (int k = 0; k < 6; k++) out[t][k] = ((double)s[t][k] - (double)c[t][k]) + pn[t][k];
-        wave_sum_n<6 * TW>(&out[0][0]);
-    } else {
-        const RecF64 *__restrict__ rec = reinterpret_cast<const RecF64 *>(E.rec);
-        const auto load = [&](int i) { return DIRECT ? input_rec_f64(E, i) : rec[i]; };
-        RecF64 *sRec = reinterpret_cast<RecF64 *>(sBuf);
-        const double e2 = E.eps * E.eps, c375e2 = 3.75 * e2;
-        double tx[TW], ty[TW], tz[TW], acc[TW][6];
-#pragma unroll
-        for (int t = 0; t < TW; t++) {
-            const RecF64 r = load(it.tgt0 + min(tb + t, it.ntgt - 1));
-            tx[t] = r.x; ty[t] = r.y; tz[t] = r.z;
-#pragma unroll
-            for (int k = 0; k < 6; k++) acc[t][k] = 0.0;
-        }
-        for (int j0 = 0; j0 < it.nsrc; j0 += kSplitRoundF64) {
-            const int cnt = min(kSplitRoundF64, it.nsrc - j0);
-            __syncthreads();
-            for (int q = tid; q < cnt; q += kBlock) sRec[q] = load(it.src0 + j0 + q);
-            __syncthreads();
-            if (!active) continue;
-            for (int j = lane; j < cnt; j += 64) {
-                const RecF64 r = sRec[j];
-#pragma unroll
-                for (int t = 0; t < TW; t++)
-                    pair_f64(tx[t], ty[t], tz[t], r.x, r.y, r.z, r.fx, r.fy, r.fz, r.nx, r.ny, r.nz, e2, c375e2, acc[t]);
-            }
-        }
-        if (!active) return;  // no barrier follows
-#pragma unroll
-        for (int t = 0; t < TW; t++)
-#pragma unroll
-            for (int k = 0; k < 6; k++) out[t][k] = acc[t][k];
-        wave_sum_n<6 * TW>(&out[0][0]);
+        for (int k = 0; k < 6; k++) acc[t][k] = 0.0;
     }
+    for (int j0 = 0; j0 < it.nsrc; j0 += kSplitRound) {
+        const int cnt = min(kSplitRound, it.nsrc - j0);
+        __syncthreads();
+        for (int q = tid; q < cnt; q += kBlock) sRec[q] = load(it.src0 + j0 + q);
+        __syncthreads();
+        if (!active) continue;
+        for (int j = lane; j < cnt; j += 64) {
+            const RecF64 r = sRec[j];
+#pragma unroll
+            for (int t = 0; t < TW; t++)
+                pair_f64(tx[t], ty[t], tz[t], r.x, r.y, r.z, r.fx, r.fy, r.fz, r.nx, r.ny, r.nz, e2, c375e2, acc[t]);
+        }
+    }
+    if (!active) return;  // no barrier follows
+    wave_sum_n<6 * TW>(&acc[0][0]);
     if (lane < 6) {
         const int N = E.N;
 #pragma unroll
         for (int t = 0; t < TW; t++) {
             if (tb + t < it.ntgt) {
-                double v = out[t][0];
+                double v = acc[t][0];
 #pragma unroll
-                for (int k = 1; k < 6; k++) v = (lane == k) ? out[t][k] : v;
+                for (int k = 1; k < 6; k++) v = (lane == k) ? acc[t][k] : v;
                 if (DIRECT) {
                     const size_t o = 3 * (size_t)(it.tgt0 + tb + t);
                     if (lane < 3) E.U[o + lane] = v * E.cU;
@@ -756,30 +687,27 @@ __device__ __forceinline__ void split_item(const EnsDesc &E, const PairItem it) 
     }
 }
 
-template <int PREC>
 __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restrict__ desc,
                                                         const PairItem *__restrict__ items) {
     const PairItem it = items[blockIdx.x];
-    split_item<PREC, false>(desc[it.ens], it);
+    split_item<false>(desc[it.ens], it);
 }
 
 // One-shot evaluation of E.N <= kDirectMaxPoints points in one launch, with no
-// scratch and no work list: a 64-point FP64 call takes 12 us on one stream, 23 us on streams in
-// turn (each waits for the one before) instead of 36 with
+// scratch and no work list: a 64-point FP64 call takes 12 us on one stream,
+// 23 us on streams in turn (each waits for the one before) instead of 36 with
 // pack, pair and reduction kernels and an uploaded list (MI355X).
-template <int PREC>
 __global__ __launch_bounds__(kBlock) void k_eval_direct(const EnsDesc E) {
     const int t0 = (int)blockIdx.x * kSplitTargetsPerBlock;
-    split_item<PREC, true>(E, {0, t0, min(kSplitTargetsPerBlock, E.N - t0), 0, E.N, 0});
+    split_item<true>(E, {0, t0, min(kSplitTargetsPerBlock, E.N - t0), 0, E.N, 0});
 }
 
 // --------------------------------------------------------- launch wrapper
 
-hipError_t launch_eval_direct(int prec, const EnsDesc &h_desc, hipStream_t s) {
+hipError_t launch_eval_direct(const EnsDesc &h_desc, hipStream_t s) {
     if (h_desc.N == 0) return hipSuccess;
     const dim3 g((h_desc.N + kSplitTargetsPerBlock - 1) / kSplitTargetsPerBlock), b(kBlock);
-    if (prec == 1) hipLaunchKernelGGL(k_eval_direct<1>, g, b, 0, s, h_desc);
-    else hipLaunchKernelGGL(k_eval_direct<0>, g, b, 0, s, h_desc);
+    hipLaunchKernelGGL(k_eval_direct, g, b, 0, s, h_desc);
     return hipGetLastError();
 }
 
@@ -814,8 +742,7 @@ hipError_t launch_pairs(int prec, int mode, int tpl, const EnsDesc *d_desc, cons
     const dim3 b(kBlock);  // the pair kernels index LDS by threadIdx.x < kBlock
     if (mode == PAIR_SPLIT) {
         const dim3 g(n_items);
-        if (prec == 1) hipLaunchKernelGGL(k_pairs_split<1>, g, b, 0, s, d_desc, d_items);
-        else hipLaunchKernelGGL(k_pairs_split<0>, g, b, 0, s, d_desc, d_items);
+        hipLaunchKernelGGL(k_pairs_split, g, b, 0, s, d_desc, d_items);
     } else if (mode == PAIR_QUAD) {  // FP32C only (the plan never makes FP64 QUAD items)
         if (queue && resident > 0)
             hipLaunchKernelGGL((k_pairs_tile_f32<1, true, true>), dim3((unsigned)std::min(n_items, resident)), b, 0, s,

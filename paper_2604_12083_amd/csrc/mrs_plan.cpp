@@ -123,6 +123,24 @@ PairCfg choose_cfg_for(const PairCfg *tuned, int64_t N, int prec, int n_cu) {
     return c;
 }
 
+// FP32C ensembles that the FP64 kernels sum faster (with REC_WIDE records, so
+// no value loses precision).  Wave-split configurations always: the launch is
+// bound by latency and its near pairs are FP64 anyway (1,020 points in
+// contact 14.6 -> 9.1 us, 46 -> 27 us in batches of eight; 512 points of long
+// filaments 8.5 -> 6.6 and 14.7 -> 11.6 us).  One target per lane with contact
+// forces up to kWideContactPoints: every contact source is summed in FP64 for
+// every target, lane by lane after the FP32 pass (swimmers, pair kernel alone
+// and in batches of eight: 1,275 points 28.4 -> 13.6 and 49 -> 38 us, 3,060
+// points 58.6 -> 36.7 and 151 -> 147 us; 4,080 points 49 -> 39 but 214 -> 256
+// us).  Without contact forces the FP32C kernel wins in batches (1,152 points:
+// 23 us against 31).
+constexpr int64_t kWideContactPoints = 3200;
+
+bool wide_records(const PairCfg &c, int64_t N, int prec, bool has_lj) {
+    if (prec != MRS_FP32C) return false;
+    return c.mode == PAIR_SPLIT || (c.mode == PAIR_TILE && c.tpl == 1 && has_lj && N <= kWideContactPoints);
+}
+
 void add_items(Plan &P, int e, int64_t N, int n_fil, const PairCfg &c) {
     if (c.mode != PAIR_SPLIT && c.sched == SCHED_PERSISTENT) P.sched = SCHED_PERSISTENT;
     if (c.mode == PAIR_SPLIT) {
@@ -131,8 +149,8 @@ void add_items(Plan &P, int e, int64_t N, int n_fil, const PairCfg &c) {
     } else {
         const bool quad = c.mode == PAIR_QUAD;
         const int64_t tile = quad ? 64 : (int64_t)kBlock * c.tpl;
-        auto &dst = quad ? P.quad : (c.tpl == 2 ? P.tile2 : P.tile1);
-        auto &tail = quad ? P.tailq : (c.tpl == 2 ? P.tail2 : P.tail1);
+        auto &dst = quad ? P.quad : (c.wide ? P.wide1 : (c.tpl == 2 ? P.tile2 : P.tile1));
+        auto &tail = quad ? P.tailq : (c.wide ? P.tailw : (c.tpl == 2 ? P.tail2 : P.tail1));
         // chunk-major: consecutive blocks share a source chunk, so every XCD
         // (blocks go to the 8 XCDs in turn) reads each chunk once into its L2
         const int64_t B = c.tail_start > 0 ? c.tail_start : N;  // end of the regular chunks
@@ -173,12 +191,15 @@ void order_items(Plan &P) {
     near_blocks_first(P.tile1);
     near_blocks_first(P.tile2);
     near_blocks_first(P.quad);
+    near_blocks_first(P.wide1);
     P.tile1.insert(P.tile1.end(), P.tail1.begin(), P.tail1.end());
     P.tile2.insert(P.tile2.end(), P.tail2.begin(), P.tail2.end());
     P.quad.insert(P.quad.end(), P.tailq.begin(), P.tailq.end());
+    P.wide1.insert(P.wide1.end(), P.tailw.begin(), P.tailw.end());
     P.tail1.clear();
     P.tail2.clear();
     P.tailq.clear();
+    P.tailw.clear();
 }
 
 }  // namespace mrs

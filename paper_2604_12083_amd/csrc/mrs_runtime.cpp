@@ -81,7 +81,7 @@ DevPool::~DevPool() {
 }
 
 void plan_use_pool(Plan &P, DevPool *pool) {
-    for (DevBuf *b : {&P.d_desc, &P.d_split, &P.d_tile1, &P.d_tile2, &P.d_quad, &P.d_rods, &P.d_pts, &P.d_lj,
+    for (DevBuf *b : {&P.d_desc, &P.d_split, &P.d_tile1, &P.d_tile2, &P.d_quad, &P.d_wide1, &P.d_rods, &P.d_pts, &P.d_lj,
                       &P.d_ljb, &P.d_queue})
         b->pool = pool;
 }
@@ -127,6 +127,7 @@ hipError_t finalize_plan(Plan &P) {
     if ((e = upload_vec(P.d_tile1, P.tile1)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_tile2, P.tile2)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_quad, P.quad)) != hipSuccess) return e;
+    if ((e = upload_vec(P.d_wide1, P.wide1)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_rods, P.rods)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_lj, P.lj)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_ljb, P.ljb)) != hipSuccess) return e;
@@ -152,10 +153,10 @@ static EnsDesc ensemble_desc(mrs_ensemble *E, int prec, const PairCfg &c) {
     d.fext = E->has_ext ? E->fext.as<double>() : nullptr;
     d.next = E->has_ext ? E->next.as<double>() : nullptr;
     d.Xin_aos = nullptr;
-    set_records(d, E->rec.p, E->N, prec == MRS_FP32C, c.mode != PAIR_SPLIT);
     d.part = E->part.as<double>();
     d.eps = E->eps;
     d.inv_eps = 1.0 / E->eps;
+    set_records(d, E->rec.p, E->N, rec_form(prec, c), c.mode != PAIR_SPLIT);
     d.mu = E->mu;
     d.cU = 1.0 / (8.0 * kPi * E->mu);
     d.cW = prec == MRS_FP32C ? 1.0 / (8.0 * kPi * E->mu * E->eps) : d.cU;
@@ -197,6 +198,7 @@ mrs_status ensemble_plan(mrs_ensemble *E, int prec, Plan **out, bool may_tune) {
         P->prec = prec;
         P->n_ens = 1;
         PairCfg c = choose_cfg(ctx, E->N, prec);
+        c.wide = wide_records(c, E->N, prec, E->has_lj);
         size_t need = (size_t)c.K * 6 * (size_t)E->N * sizeof(double);
         if (E->part.reserve(need) != hipSuccess) return fail(ctx, MRS_ENOMEM, "partial buffer (%zu bytes)", need);
         P->cfg = c;
@@ -237,12 +239,18 @@ static const char *pair_name(int prec, int mode) {
 // counters when the plan runs the persistent schedule.
 static hipError_t pair_launches(mrs_context *ctx, int prec, int sched, const EnsDesc *dd, const PairItem *split,
                                 int n_split, const PairItem *t1, int n_t1, const PairItem *t2, int n_t2,
-                                const PairItem *tq, int n_tq, uint32_t *queue, hipStream_t s) {
+                                const PairItem *tq, int n_tq, const PairItem *tw, int n_tw, uint32_t *queue,
+                                hipStream_t s) {
     hipError_t e = hipSuccess;
     const bool pers = sched == SCHED_PERSISTENT && queue;
     if (n_split)
         e = timed(ctx, pair_name(prec, PAIR_SPLIT), s,
                   [&] { return launch_pairs(prec, PAIR_SPLIT, 1, dd, split, n_split, s); });
+    if (e == hipSuccess && n_tw)  // records of the FP64 kind
+        e = timed(ctx, pair_name(prec, PAIR_TILE), s, [&] {
+            return launch_pairs(MRS_FP64, PAIR_TILE, 1, dd, tw, n_tw, s, pers ? queue + 6 : nullptr,
+                                pers ? pairs_resident_blocks(MRS_FP64, 1) * ctx->n_cu : 0);
+        });
     if (e == hipSuccess && n_t1)
         e = timed(ctx, pair_name(prec, PAIR_TILE), s, [&] {
             return launch_pairs(prec, PAIR_TILE, 1, dd, t1, n_t1, s, pers ? queue : nullptr,
@@ -264,8 +272,8 @@ static hipError_t pair_launches(mrs_context *ctx, int prec, int sched, const Ens
 hipError_t run_pairs(mrs_context *ctx, Plan &P, hipStream_t s) {
     return pair_launches(ctx, P.prec, P.sched, P.d_desc.as<EnsDesc>(), P.d_split.as<PairItem>(), (int)P.split.size(),
                          P.d_tile1.as<PairItem>(), (int)P.tile1.size(), P.d_tile2.as<PairItem>(),
-                         (int)P.tile2.size(), P.d_quad.as<PairItem>(), (int)P.quad.size(), P.d_queue.as<uint32_t>(),
-                         s);
+                         (int)P.tile2.size(), P.d_quad.as<PairItem>(), (int)P.quad.size(),
+                         P.d_wide1.as<PairItem>(), (int)P.wide1.size(), P.d_queue.as<uint32_t>(), s);
 }
 
 const char *epi_name(int epi) {
@@ -288,7 +296,7 @@ hipError_t run_stage(mrs_context *ctx, Plan &P, int stage_state, int elastic, in
         if (e != hipSuccess) return e;
     }
     e = timed(ctx, "rod_forces", s, [&] {
-        return launch_rod_forces(P.prec, stage_state, elastic, scheme, stage, dt, P.d_desc.as<EnsDesc>(),
+        return launch_rod_forces(stage_state, elastic, scheme, stage, dt, P.d_desc.as<EnsDesc>(),
                                  P.d_rods.as<RodItem>(), (int)P.rods.size(), s);
     });
     if (e != hipSuccess) return e;
@@ -742,7 +750,7 @@ static void eval_layout(EvalLayout &L, int64_t n, const EnsDesc &args, int p, co
     d = args;
     d.K = c.K;
     // block descriptors only for the tiled kernels (k_pack_aos writes them)
-    set_records(d, sc.rec, n, p == MRS_FP32C, c.mode != PAIR_SPLIT);
+    set_records(d, sc.rec, n, rec_form(p, c), c.mode != PAIR_SPLIT);
     d.part = sc.part;
     L.P.prec = p;
     add_items(L.P, 0, n, 0, c);
@@ -767,12 +775,12 @@ static void eval_layout(EvalLayout &L, int64_t n, const EnsDesc &args, int p, co
 static hipError_t eval_launch(mrs_context *ctx, const EvalLayout &L, int p, const char *base, hipStream_t s) {
     const Plan &P = L.P;
     const EnsDesc *dd = reinterpret_cast<const EnsDesc *>(base + L.o_desc);
-    hipError_t e = timed(ctx, "pack_aos", s, [&] { return launch_pack_aos(p, dd, L.d, s); });
+    hipError_t e = timed(ctx, "pack_aos", s, [&] { return launch_pack_aos(dd, L.d, s); });
     if (e == hipSuccess)
         e = pair_launches(ctx, p, P.sched, dd, reinterpret_cast<const PairItem *>(base + L.o_split),
                           (int)P.split.size(), reinterpret_cast<const PairItem *>(base + L.o_t1), (int)P.tile1.size(),
                           reinterpret_cast<const PairItem *>(base + L.o_t2), (int)P.tile2.size(),
-                          reinterpret_cast<const PairItem *>(base + L.o_tq), (int)P.quad.size(),
+                          reinterpret_cast<const PairItem *>(base + L.o_tq), (int)P.quad.size(), nullptr, 0,
                           reinterpret_cast<uint32_t *>(const_cast<char *>(base) + L.o_queue), s);
     if (e == hipSuccess)
         e = timed(ctx, "reduce_write", s, [&] {
@@ -815,10 +823,11 @@ static hipError_t eval_end(mrs_context *ctx, hipStream_t s) {
 
 // A small evaluation keeps its place in the order of the context's
 // evaluations, though it shares no scratch with them.
-static mrs_status eval_direct(mrs_context *ctx, const EnsDesc &args, int p, hipStream_t s) {
+static mrs_status eval_direct(mrs_context *ctx, EnsDesc args, int p, const PairCfg &c, hipStream_t s) {
+    set_records(args, nullptr, args.N, rec_form(p, c), false);
     HIPCHK(ctx, eval_begin(ctx, s));
     HIPCHK(ctx, timed(ctx, p == MRS_FP32C ? "pairs_split_f32c" : "pairs_split_f64", s,
-                      [&] { return launch_eval_direct(p, args, s); }));
+                      [&] { return launch_eval_direct(args, s); }));
     HIPCHK(ctx, eval_end(ctx, s));
     return MRS_OK;
 }
@@ -834,8 +843,9 @@ mrs_status mrs_eval_device(mrs_context *ctx, int64_t n, const double *dX, const 
     hipStream_t s = pick_stream(ctx, stream);
     const int p = (int)prec;
     PairCfg c = choose_cfg(ctx, n, p);
+    c.wide = wide_records(c, n, p, false);
     const EnsDesc args = eval_desc(n, dX, df, dt, eps, mu, p, dU, dW);
-    if (eval_is_direct(args, c)) return eval_direct(ctx, args, p, s);
+    if (eval_is_direct(args, c)) return eval_direct(ctx, args, p, c, s);
     // the scratch below is shared by every evaluation of the context: this
     // one waits on its stream for the previous one (any stream) to finish,
     // and growing a buffer (which frees the old one) first waits on the host
@@ -884,8 +894,9 @@ mrs_status mrs_eval_device_noalloc(mrs_context *ctx, int64_t n, const double *dX
     const size_t per_chunk = (size_t)n * 6 * sizeof(double);
     const int64_t k_room = (int64_t)((kNoallocBytes - part_off) / per_chunk);
     PairCfg c = choose_cfg(ctx, n, p);
+    c.wide = wide_records(c, n, p, false);
     const EnsDesc args = eval_desc(n, dX, df, dt, eps, mu, p, dU, dW);
-    if (eval_is_direct(args, c)) return eval_direct(ctx, args, p, s);
+    if (eval_is_direct(args, c)) return eval_direct(ctx, args, p, c, s);
     if (c.K > k_room) {
         PairCfg t;
         t.mode = c.mode;

@@ -77,6 +77,7 @@ struct PairCfg {
     // partial slots k_big.. (tail_start = 0: none, every chunk is `chunk`)
     int tail_start = 0, tail_chunk = 0, k_big = 0;
     int sched = SCHED_GRID;  // schedule of the tiled kernel (PairSched)
+    bool wide = false;       // FP32C on records of the FP64 kind (REC_WIDE)
 };
 
 // Work lists of one launch sequence over a set of ensembles.
@@ -84,13 +85,13 @@ struct Plan {
     int prec = 0;
     int n_ens = 0;
     std::vector<EnsDesc> h_desc;
-    std::vector<PairItem> split, tile1, tile2, quad;
-    std::vector<PairItem> tail1, tail2, tailq;  // tail-split items, dispatched after tile1 / tile2 / quad
+    std::vector<PairItem> split, tile1, tile2, quad, wide1;  // wide1: tile1 on REC_WIDE records (FP64 kernel)
+    std::vector<PairItem> tail1, tail2, tailq, tailw;  // tail-split items, dispatched after tile1 / tile2 / quad / wide1
     std::vector<RodItem> rods;
     std::vector<PointItem> pts;
     std::vector<PointItem> lj;   // 64-point target blocks of the ensembles with LJ repulsion
     std::vector<PointItem> ljb;  // their LJ source blocks, kBlock / 64 per item
-    DevBuf d_desc, d_split, d_tile1, d_tile2, d_quad, d_rods, d_pts, d_lj, d_ljb;
+    DevBuf d_desc, d_split, d_tile1, d_tile2, d_quad, d_wide1, d_rods, d_pts, d_lj, d_ljb;
     int sched = SCHED_GRID;  // persistent if any ensemble of the plan asks for it
     DevBuf d_queue;          // kQueueWords uint32, zero between launches
     // cached graphs: key = (integrator, dt bits, steps, elastic)
@@ -262,6 +263,11 @@ PairCfg choose_cfg(mrs_context *ctx, int64_t N, int prec);
 // The configuration for N points: `tuned` (a tuning-table entry) or, if null,
 // the automatic one for a device with n_cu compute units.  Host only.
 PairCfg choose_cfg_for(const PairCfg *tuned, int64_t N, int prec, int n_cu);
+// FP32C: whether the kernels of configuration c read REC_WIDE records.
+bool wide_records(const PairCfg &c, int64_t N, int prec, bool has_lj);
+inline RecForm rec_form(int prec, const PairCfg &c) {
+    return prec == MRS_FP64 ? REC_F64 : (c.wide ? REC_WIDE : REC_F32);
+}
 // Reorders tiled pair blocks so that those with near pairs along a filament
 // (source range overlapping the target range) are dispatched first.
 void near_blocks_first(std::vector<PairItem> &v);
