@@ -52,15 +52,19 @@ __device__ __forceinline__ RecF64 widen(const RecF32 &r) {
             (double)r.a.w, (double)r.b.w, (double)r.c.x, (double)r.c.y, (double)r.c.z, (double)r.c.w, 0.0};
 }
 
+// The FP64-kind record (REC_F64, REC_WIDE) of a point.
+__device__ __forceinline__ RecF64 rec_f64(const EnsDesc &E, double x, double y, double z, double fx, double fy,
+                                          double fz, double nx, double ny, double nz) {
+    if (E.form == REC_WIDE) return widen(make_rec_f32(x, y, z, fx, fy, fz, nx, ny, nz, E.inv_eps));
+    return {x, y, z, fx, fy, fz, nx, ny, nz, 0.0};
+}
+
 __device__ __forceinline__ void store_rec(const EnsDesc &E, int i, double x, double y, double z, double fx, double fy,
                                           double fz, double nx, double ny, double nz) {
-    if (E.form == REC_F64) {
-        reinterpret_cast<RecF64 *>(E.rec)[i] = {x, y, z, fx, fy, fz, nx, ny, nz, 0.0};
-        return;
-    }
-    const RecF32 r = make_rec_f32(x, y, z, fx, fy, fz, nx, ny, nz, E.inv_eps);
-    if (E.form == REC_F32) reinterpret_cast<RecF32 *>(E.rec)[i] = r;
-    else reinterpret_cast<RecF64 *>(E.rec)[i] = widen(r);
+    if (E.form == REC_F32)
+        reinterpret_cast<RecF32 *>(E.rec)[i] = make_rec_f32(x, y, z, fx, fy, fz, nx, ny, nz, E.inv_eps);
+    else
+        reinterpret_cast<RecF64 *>(E.rec)[i] = rec_f64(E, x, y, z, fx, fy, fz, nx, ny, nz);
 }
 
 // The record of point i of a one-shot evaluation, from the caller's row-major
@@ -240,6 +244,27 @@ __device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__re
     }
 }
 
+// Adds the point force and torque of the node between slots q (segment before)
+// and q + 1 (segment after) of the segment arrays to g and m.
+template <int SLOTS>
+__device__ __forceinline__ void rod_node(const double (*sF)[SLOTS], const double (*sN)[SLOTS],
+                                         const double (*sX)[SLOTS], int q, double *g, double *m) {
+    FP_STRICT;
+    const double Fp[3] = {sF[0][q + 1], sF[1][q + 1], sF[2][q + 1]};
+    const double Fm[3] = {sF[0][q], sF[1][q], sF[2][q]};
+    const double Xp[3] = {sX[0][q + 1], sX[1][q + 1], sX[2][q + 1]};
+    const double Xm[3] = {sX[0][q], sX[1][q], sX[2][q]};
+    const double cp[3] = {Xp[1] * Fp[2] - Xp[2] * Fp[1], Xp[2] * Fp[0] - Xp[0] * Fp[2],
+                          Xp[0] * Fp[1] - Xp[1] * Fp[0]};
+    const double cm[3] = {Xm[1] * Fm[2] - Xm[2] * Fm[1], Xm[2] * Fm[0] - Xm[0] * Fm[2],
+                          Xm[0] * Fm[1] - Xm[1] * Fm[0]};
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        g[c] += Fp[c] - Fm[c];
+        m[c] += (sN[c][q + 1] - sN[c][q]) + 0.5 * (cp[c] + cm[c]);
+    }
+}
+
 // Rod forces of one filament (nodes k0 .. k0 + M - 1; Sec. II.B, Alg. 1): for
 // every node, the point force and torque on the fluid, g = F_{k+1/2} -
 // F_{k-1/2} + external, m = N_{k+1/2} - N_{k-1/2} + (dX_{k+1/2} x F_{k+1/2} +
@@ -296,22 +321,8 @@ __device__ __forceinline__ void rod_filament(int stage_state, int elastic, int s
             __syncthreads();
         }
         if (node) {
-            if (elastic) {
-                // segment k+1/2 sits at LDS slot tid + 1, segment k-1/2 at slot tid
-                const double Fp[3] = {sF[0][tid + 1], sF[1][tid + 1], sF[2][tid + 1]};
-                const double Fm[3] = {sF[0][tid], sF[1][tid], sF[2][tid]};
-                const double Xp[3] = {sX[0][tid + 1], sX[1][tid + 1], sX[2][tid + 1]};
-                const double Xm[3] = {sX[0][tid], sX[1][tid], sX[2][tid]};
-                const double cp[3] = {Xp[1] * Fp[2] - Xp[2] * Fp[1], Xp[2] * Fp[0] - Xp[0] * Fp[2],
-                                      Xp[0] * Fp[1] - Xp[1] * Fp[0]};
-                const double cm[3] = {Xm[1] * Fm[2] - Xm[2] * Fm[1], Xm[2] * Fm[0] - Xm[0] * Fm[2],
-                                      Xm[0] * Fm[1] - Xm[1] * Fm[0]};
-#pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    g[c] += Fp[c] - Fm[c];
-                    m[c] += (sN[c][tid + 1] - sN[c][tid]) + 0.5 * (cp[c] + cm[c]);
-                }
-            }
+            // segment k+1/2 sits at LDS slot tid + 1, segment k-1/2 at slot tid
+            if (elastic) rod_node<BLOCK>(sF, sN, sX, tid, g, m);
             if (AOS) {
 #pragma unroll
                 for (int c = 0; c < 3; c++) {

@@ -201,6 +201,12 @@ int pairs_resident_blocks(int prec, int tpl);
 // dt = NaN: every ensemble uses its own EnsDesc::dt.
 hipError_t launch_reduce(int epi, int stage, int scheme, double dt, const EnsDesc *d_desc,
                          const PointItem *d_items, int n_items, hipStream_t s);
+// nsteps steps (kSmallEval: the velocities) of n_ens ensembles of at most
+// kSmallPoints points, one workgroup each; scheme: as for launch_rod_forces,
+// or one of the two below.
+constexpr int kSmallPoints = 64, kSmallThreads = 512, kSmallEuler = -1, kSmallEval = -2;
+hipError_t launch_small_steps(int scheme, int nsteps, int elastic, double dt, const EnsDesc *d_desc, int n_ens,
+                              hipStream_t s);
 hipError_t launch_rotsqrt(int64_t count, const double *R, double *S, hipStream_t s);
 // out[0] = shader-clock ticks, out[1] = reference-clock ticks of a spin of `cycles` ticks.
 hipError_t launch_clock_probe(int64_t cycles, uint64_t *out, hipStream_t s);

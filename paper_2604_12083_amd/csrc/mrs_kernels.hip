@@ -9,6 +9,7 @@
 //                     pair kernel's source records
 //   k_reduce<EPI>     fixed-order FP64 sum of the split-K partials, scaling,
 //                     and the element-wise step epilogue (Eqs. newx, newD)
+//   k_small_steps     whole steps of ensembles of at most 64 points
 //   k_parareal_correct  Parareal correction of one slice boundary
 //   k_rotsqrt         batched principal 3x3 rotation square root
 //
@@ -312,6 +313,186 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(int stage, int scheme
     epilogue_point<EPI>(E, N, i, acc, xv, dv, uav, wav, kv, stage, scheme, dt);
 }
 
+// ------------------------------------------------- steps of small ensembles
+
+// Whole steps of an ensemble of at most kSmallPoints points by one workgroup,
+// its state in LDS from the first stage to the last: the rod loads (a thread
+// per point), the pair sum (lane = target, the waves split the sources) and the
+// epilogue, with barriers where the general path has launches.  SCHEME:
+// kSmallEval writes U, Omega of the state, kSmallEuler steps by Euler, 0 and 1
+// by the Runge-Kutta scheme of that number.
+//
+// Such a step is a chain of latencies, and three launches of 3 to 4 us each
+// against 1.8 us of pair arithmetic on one CU: 64 FP64 points take 4.9 instead
+// of 10.6 us per Euler step, 256 such ensembles 6.9 instead of 27 us (MI355X).
+// At 128 points one CU has four times the pairs, a step takes 10.6 instead of
+// 11.2 us and a call of one step 25 instead of 23, so those go by stages.
+//
+// Every operation and every sum is that of k_rod_forces, k_pairs_split and
+// k_reduce in the same order, so the bits are the same: small_pairs<MOD> sums
+// the sources j (mod MOD) as the first levels of wave_sum_n do, and the waves'
+// sums are combined as its last ones.  Sources are padded by points without
+// loads at the first point, whose terms are zeros.  Eight waves, not sixteen:
+// at the 128 registers of sixteen the loop spills.
+template <int MOD>
+__device__ __forceinline__ void small_pairs(const RecF64 *sRec, int j, double tx, double ty, double tz, double e2,
+                                            double c375e2, double *acc) {
+    if constexpr (MOD == kSmallPoints) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) acc[k] = 0.0;
+        const RecF64 r = sRec[j];
+        pair_f64(tx, ty, tz, r.x, r.y, r.z, r.fx, r.fy, r.fz, r.nx, r.ny, r.nz, e2, c375e2, acc);
+    } else {
+        double o[6];
+        small_pairs<2 * MOD>(sRec, j, tx, ty, tz, e2, c375e2, acc);
+        small_pairs<2 * MOD>(sRec, j + MOD, tx, ty, tz, e2, c375e2, o);
+#pragma unroll
+        for (int k = 0; k < 6; k++) acc[k] += o[k];
+    }
+}
+
+template <int SCHEME>
+__global__ __launch_bounds__(kSmallThreads) void k_small_steps(int nsteps, int elastic, double dt,
+                                                              const EnsDesc *__restrict__ desc) {
+    constexpr int kWaves = kSmallThreads / 64, P = kSmallPoints;
+    static_assert(P == 64 && kWaves <= 64 && (kWaves & (kWaves - 1)) == 0, "one lane per target, wave_sum_n's order");
+    constexpr int kStateVecs = SCHEME >= 0 ? 39 : 18;
+    constexpr int kStages = SCHEME == 0 ? 4 : (SCHEME == 1 ? 2 : 1);
+    __shared__ double sState[kStateVecs * P];
+    __shared__ RecF64 sRec[P];
+    __shared__ double sF[3][P + 1], sN[3][P + 1], sX[3][P + 1];
+    __shared__ double sPart[kWaves][6][P];
+    __shared__ double sClock;
+    const EnsDesc &G0 = desc[blockIdx.x];
+    const int N = G0.N;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (elastic < 0) elastic = G0.elastic;
+    if (dt != dt) dt = G0.dt;
+    // the descriptor with the state in LDS (SoA with stride N, as in memory)
+    EnsDesc E = G0;
+    double *sx = sState, *sd = sx + 3 * P, *su = sd + 9 * P, *sw = su + 3 * P;
+    E.X = sx; E.D = sd; E.U = su; E.W = sw;
+    if (SCHEME >= 0) {
+        E.Xs = sw + 3 * P; E.Ds = E.Xs + 3 * P; E.Ua = E.Ds + 9 * P; E.Wa = E.Ua + 3 * P; E.Ks = E.Wa + 3 * P;
+    }
+    E.clock = &sClock;
+    for (int q = tid; q < 12 * N; q += kSmallThreads) {
+        if (q < 3 * N) sx[q] = G0.X[q];
+        else sd[q - 3 * N] = G0.D[q - 3 * N];
+    }
+    // this thread's node: its place in its filament and its external loads
+    const bool node = tid < N;
+    int seg = 0;
+    bool last = true;
+    double g0[3] = {0.0, 0.0, 0.0}, m0[3] = {0.0, 0.0, 0.0};
+    if (node) {
+        int k0 = 0, k1 = N;
+        for (int f = 0; f < G0.n_fil; f++) {
+            const int a = G0.off[f], b = G0.off[f + 1];
+            if (tid >= a && tid < b) { k0 = a; k1 = b; }
+        }
+        seg = tid - k0;
+        last = tid == k1 - 1;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            if (G0.fext) g0[c] = G0.fext[(size_t)c * N + tid];
+            if (G0.next) m0[c] = G0.next[(size_t)c * N + tid];
+        }
+    }
+    if (tid == 0) sClock = G0.clock ? *G0.clock : 0.0;
+    if (tid < 9) (tid < 3 ? sF[tid] : (tid < 6 ? sN[tid - 3] : sX[tid - 6]))[0] = 0.0;
+    const double e2 = G0.rec_eps * G0.rec_eps, c375e2 = 3.75 * e2;
+    __syncthreads();
+    for (int step = 0; step < nsteps; step++) {
+#pragma unroll 1
+        for (int st = 0; st < kStages; st++) {
+            const double *X = SCHEME >= 0 && st > 0 ? E.Xs : E.X;
+            const double *D = SCHEME >= 0 && st > 0 ? E.Ds : E.D;
+            // rod loads -> records
+            if (elastic) {
+                if (node) {
+                    double F[3] = {0.0, 0.0, 0.0}, Nv[3] = {0.0, 0.0, 0.0}, dX[3] = {0.0, 0.0, 0.0};
+                    double t = 0.0;
+                    if (E.has_wave) t = sClock + (SCHEME >= 0 && st > 0 ? kRkNextNode[SCHEME & 1][st - 1] : 0.0) * dt;
+                    if (!last)
+                        rod_segment<false>(E, X, D, N, tid, tid + 1, (seg + 0.5) * E.ds, t, F, Nv, dX);
+#pragma unroll
+                    for (int c = 0; c < 3; c++) {
+                        sF[c][tid + 1] = F[c];
+                        sN[c][tid + 1] = Nv[c];
+                        sX[c][tid + 1] = dX[c];
+                    }
+                }
+                __syncthreads();
+            }
+            if (node) {
+                double g[3] = {g0[0], g0[1], g0[2]}, m[3] = {m0[0], m0[1], m0[2]};
+                if (elastic) rod_node<P + 1>(sF, sN, sX, tid, g, m);
+                sRec[tid] = rec_f64(E, X[tid], X[N + tid], X[2 * N + tid], g[0], g[1], g[2], m[0], m[1], m[2]);
+            }
+            if (tid >= N && tid < P) sRec[tid] = rec_f64(E, X[0], X[N], X[2 * N], 0.0, 0.0, 0.0, 0.0, 0.0, 0.0);
+            __syncthreads();
+            // pair sum
+            double part[6];
+            const RecF64 &tgt = sRec[min(lane, N - 1)];
+            small_pairs<kWaves>(sRec, w, tgt.x, tgt.y, tgt.z, e2, c375e2, part);
+#pragma unroll
+            for (int k = 0; k < 6; k++) sPart[w][k][lane] = part[k];
+            __syncthreads();
+            if (node) {
+                double acc[6];
+#pragma unroll
+                for (int k = 0; k < 6; k++) {
+                    double v[kWaves];
+#pragma unroll
+                    for (int q = 0; q < kWaves; q++) v[q] = sPart[q][k][tid];
+#pragma unroll
+                    for (int off = kWaves / 2; off >= 1; off >>= 1)
+#pragma unroll
+                        for (int q = 0; q < off; q++) v[q] += v[q + off];
+                    acc[k] = 0.0 + v[0];  // as k_reduce, from zero
+                }
+                double xv[3], dv[9], uav[3] = {0.0, 0.0, 0.0}, wav[3] = {0.0, 0.0, 0.0}, kv[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                for (int c = 0; c < 3; c++) xv[c] = E.X[c * N + tid];
+#pragma unroll
+                for (int k = 0; k < 9; k++) dv[k] = E.D[k * N + tid];
+                if (SCHEME >= 0 && st > 0) {
+#pragma unroll
+                    for (int c = 0; c < 3; c++) {
+                        uav[c] = E.Ua[c * N + tid];
+                        wav[c] = E.Wa[c * N + tid];
+                        if (SCHEME == 0) kv[c] = E.Ks[c * N + tid];
+                    }
+                }
+                const bool final_stage = st == kStages - 1;
+                if (SCHEME != kSmallEval && final_stage && tid == 0) sClock += dt;
+                if (SCHEME == kSmallEval)
+                    epilogue_point<EPI_WRITE>(E, N, tid, acc, xv, dv, uav, wav, kv, 0, 0, dt);
+                else if (SCHEME == kSmallEuler)
+                    epilogue_point<EPI_EULER>(E, N, tid, acc, xv, dv, uav, wav, kv, 0, 0, dt);
+                else if (!final_stage)
+                    epilogue_point<EPI_RK_STAGE>(E, N, tid, acc, xv, dv, uav, wav, kv, st, SCHEME & 1, dt);
+                else
+                    epilogue_point<EPI_RK_FINAL>(E, N, tid, acc, xv, dv, uav, wav, kv, st, SCHEME & 1, dt);
+            }
+            __syncthreads();
+        }
+    }
+    for (int q = tid; q < 18 * N; q += kSmallThreads) {
+        if (q < 12 * N) {
+            if (SCHEME == kSmallEval) continue;
+            if (q < 3 * N) G0.X[q] = sx[q];
+            else G0.D[q - 3 * N] = sd[q - 3 * N];
+        } else if (q < 15 * N) {
+            G0.U[q - 12 * N] = su[q - 12 * N];
+        } else {
+            G0.W[q - 15 * N] = sw[q - 15 * N];
+        }
+    }
+    if (SCHEME != kSmallEval && tid == 0 && G0.clock) *G0.clock = sClock;
+}
+
 // ------------------------------------------------- caller arrays in and out
 
 // State in and out of an ensemble.  The host side is pinned memory that the
@@ -473,6 +654,18 @@ hipError_t launch_rows_out(const RowArrays &ra, const int32_t *inv, int64_t N, i
 
 hipError_t launch_set_value(double *p, double v, hipStream_t s) {
     hipLaunchKernelGGL(k_set_value, dim3(1), dim3(1), 0, s, p, v);
+    return hipGetLastError();
+}
+
+hipError_t launch_small_steps(int scheme, int nsteps, int elastic, double dt, const EnsDesc *d_desc, int n_ens,
+                              hipStream_t s) {
+    const dim3 g(n_ens), b(kSmallThreads);
+    switch (scheme) {
+        case kSmallEval: hipLaunchKernelGGL(k_small_steps<kSmallEval>, g, b, 0, s, 1, elastic, dt, d_desc); break;
+        case kSmallEuler: hipLaunchKernelGGL(k_small_steps<kSmallEuler>, g, b, 0, s, nsteps, elastic, dt, d_desc); break;
+        case 0: hipLaunchKernelGGL(k_small_steps<0>, g, b, 0, s, nsteps, elastic, dt, d_desc); break;
+        default: hipLaunchKernelGGL(k_small_steps<1>, g, b, 0, s, nsteps, elastic, dt, d_desc); break;
+    }
     return hipGetLastError();
 }
 

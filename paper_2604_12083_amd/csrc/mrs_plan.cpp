@@ -202,6 +202,15 @@ void order_items(Plan &P) {
     P.tailw.clear();
 }
 
+// Ensembles of at most kSmallPoints points (the limit's reason: k_small_steps)
+// in wave-split configurations, whose sums that kernel repeats; the repulsion
+// has passes of its own.
+bool small_plan(const Plan &P) {
+    for (const EnsDesc &d : P.h_desc)
+        if (d.N > kSmallPoints || d.K != 1 || d.has_lj) return false;
+    return !P.split.empty() && P.tile1.empty() && P.tile2.empty() && P.quad.empty() && P.wide1.empty();
+}
+
 }  // namespace mrs
 
 using namespace mrs;

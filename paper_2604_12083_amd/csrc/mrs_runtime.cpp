@@ -119,6 +119,7 @@ void add_lj_items(Plan &P, int e, const mrs_ensemble *E) {
 
 hipError_t finalize_plan(Plan &P) {
     order_items(P);
+    P.small = small_plan(P);
     hipError_t e;
     if ((e = P.d_queue.reserve(kQueueWords * sizeof(uint32_t))) != hipSuccess) return e;
     if ((e = hipMemset(P.d_queue.p, 0, kQueueWords * sizeof(uint32_t))) != hipSuccess) return e;
@@ -307,9 +308,29 @@ hipError_t run_stage(mrs_context *ctx, Plan &P, int stage_state, int elastic, in
     });
 }
 
+// U, Omega of the state of plan P's ensembles.
+static hipError_t queue_eval(mrs_context *ctx, Plan &P, int elastic, hipStream_t s) {
+    if (P.small && !ctx->prof_on)
+        return launch_small_steps(kSmallEval, 1, elastic, 0.0, P.d_desc.as<EnsDesc>(), P.n_ens, s);
+    return run_stage(ctx, P, 0, elastic, EPI_WRITE, 0, 0, 0.0, s);
+}
+
+// Steps per launch of k_small_steps: 0.2 ms (Euler) to 0.7 ms (RK4), against
+// which the launch is small, and no launch keeps its CU for long.
+static constexpr int kSmallSteps = 32;
+
 // Queue nsteps steps of plan P on stream s (no synchronisation).
 static hipError_t queue_steps(mrs_context *ctx, Plan &P, int integ, double dt, int nsteps, int elastic,
                               hipStream_t s) {
+    if (P.small && !ctx->prof_on) {  // profiles name the stages' kernels
+        const int scheme = integ == MRS_EULER ? kSmallEuler : rk_scheme(integ);
+        for (int step = 0; step < nsteps; step += kSmallSteps) {
+            const hipError_t e = launch_small_steps(scheme, std::min(kSmallSteps, nsteps - step), elastic, dt,
+                                                    P.d_desc.as<EnsDesc>(), P.n_ens, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     for (int step = 0; step < nsteps; step++) {
         hipError_t e;
         if (integ == MRS_EULER) {
@@ -1434,7 +1455,7 @@ mrs_status mrs_ensemble_eval(mrs_ensemble *E, mrs_precision prec, int include_el
     mrs_status st = ensemble_plan(E, (int)prec, &P);
     if (st != MRS_OK) return st;
     numeric_reset(ctx);
-    HIPCHK(ctx, run_stage(ctx, *P, 0, include_elastic ? 1 : 0, EPI_WRITE, 0, 0, 0.0, ctx->stream));
+    HIPCHK(ctx, queue_eval(ctx, *P, include_elastic ? 1 : 0, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return numeric_check(ctx);
 }
@@ -1590,7 +1611,7 @@ mrs_status mrs_batch_eval(mrs_context *ctx, int32_t n_ens, mrs_ensemble *const *
     Plan *P;
     if ((st = batch_plan(ctx, n_ens, ens, (int)prec, &P)) != MRS_OK) return st;
     numeric_reset(ctx);
-    HIPCHK(ctx, run_stage(ctx, *P, 0, include_elastic ? 1 : 0, EPI_WRITE, 0, 0, 0.0, ctx->stream));
+    HIPCHK(ctx, queue_eval(ctx, *P, include_elastic ? 1 : 0, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return numeric_check(ctx);
 }

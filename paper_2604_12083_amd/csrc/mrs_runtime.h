@@ -98,6 +98,7 @@ struct Plan {
     std::map<std::tuple<int, uint64_t, int, int>, hipGraphExec_t> graphs;
     int64_t pairs_per_eval = 0;
     PairCfg cfg;  // configuration of a single-ensemble plan
+    bool small = false;  // stepped by k_small_steps, not by stages (small_plan)
     ~Plan();
 };
 
@@ -274,6 +275,8 @@ void near_blocks_first(std::vector<PairItem> &v);
 // Dispatch order of a plan's tiled blocks: near blocks first, the short
 // tail-split blocks last (moved from tail1 / tail2 to the end of tile1 / tile2).
 void order_items(Plan &P);
+// Whether k_small_steps takes the plan's steps whole.
+bool small_plan(const Plan &P);
 // Power-of-two size class of the tuning table.
 int size_bucket(int64_t N);
 size_t ensemble_bytes(int64_t N, int n_fil, bool has_ext, int K64, int K32);
