@@ -269,11 +269,11 @@ __device__ __forceinline__ void rod_node(const double (*sF)[SLOTS], const double
 // every node, the point force and torque on the fluid, g = F_{k+1/2} -
 // F_{k-1/2} + external, m = N_{k+1/2} - N_{k-1/2} + (dX_{k+1/2} x F_{k+1/2} +
 // dX_{k-1/2} x F_{k-1/2}) / 2 + external, written as source records, or with AOS (row-major state and loads) into E.g_out, E.m_out.
-// BLOCK threads walk the filament in chunks of BLOCK - 1 nodes: thread t
+// The first BLOCK of THREADS threads walk the filament in chunks of BLOCK - 1 nodes: thread t
 // computes segment c0 - 1 + t into LDS, then node c0 + t combines its two
 // neighbouring segments (a node's result does not depend on the chunking).
 // Every thread of the block must call it.
-template <int BLOCK, bool AOS>
+template <int BLOCK, bool AOS, int THREADS = BLOCK>
 __device__ __forceinline__ void rod_filament(int stage_state, int elastic, int scheme, int stage,
                                              double dt, const EnsDesc &E, int k0, int M) {
     FP_STRICT;
@@ -308,15 +308,17 @@ __device__ __forceinline__ void rod_filament(int stage_state, int elastic, int s
             }
         }
         if (elastic) {
-            const int s = c0 - 1 + tid;
-            double F[3] = {0.0, 0.0, 0.0}, Nv[3] = {0.0, 0.0, 0.0}, dX[3] = {0.0, 0.0, 0.0};
-            if (s >= 0 && s <= M - 2)
-                rod_segment<AOS>(E, X, D, N, k0 + s, k0 + s + 1, (s + 0.5) * E.ds, t, F, Nv, dX);
+            if (THREADS == BLOCK || tid < BLOCK) {
+                const int s = c0 - 1 + tid;
+                double F[3] = {0.0, 0.0, 0.0}, Nv[3] = {0.0, 0.0, 0.0}, dX[3] = {0.0, 0.0, 0.0};
+                if (s >= 0 && s <= M - 2)
+                    rod_segment<AOS>(E, X, D, N, k0 + s, k0 + s + 1, (s + 0.5) * E.ds, t, F, Nv, dX);
 #pragma unroll
-            for (int c = 0; c < 3; c++) {
-                sF[c][tid] = F[c];
-                sN[c][tid] = Nv[c];
-                sX[c][tid] = dX[c];
+                for (int c = 0; c < 3; c++) {
+                    sF[c][tid] = F[c];
+                    sN[c][tid] = Nv[c];
+                    sX[c][tid] = dX[c];
+                }
             }
             __syncthreads();
         }

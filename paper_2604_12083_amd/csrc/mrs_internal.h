@@ -122,6 +122,10 @@ struct RodItem {
     int32_t ens, fil;
 };
 
+// Largest ensembles of k_lj_rods: points (their positions lie in LDS, 24 B
+// each) and LJ source blocks (one per lane).
+constexpr int kLjRodPoints = 3200, kLjRodBlocks = 64;
+
 // Filament offsets of k_rod_forces_aos: filaments of `step` points each, or
 // (step = 0) the offsets themselves, up to kRodArgOffsets of them in the
 // kernel's arguments (argument blocks end at 4 KiB), more in a device list.
@@ -183,6 +187,9 @@ hipError_t launch_rod_forces_aos(const EnsDesc &h_desc, const RodOffsets &off, h
 // source block (box items: (ensemble, first of kBlock / 64 blocks)), then the
 // force on every point and the LJ masks (target items: (ensemble, first of
 // kLjMaskPoints consecutive points)).
+// max_points <= kLjRodPoints: largest ensemble of the items.
+hipError_t launch_lj_rods(int stage_state, int elastic, int scheme, int stage, double dt, const EnsDesc *d_desc,
+                          const RodItem *d_items, int n_items, int max_points, hipStream_t s);
 hipError_t launch_lj(int stage_state, const EnsDesc *d_desc, const PointItem *d_box_items, int n_box_items,
                      const PointItem *d_items, int n_items, hipStream_t s);
 // queue (two uint32 that are zero before the launch and zero again after

@@ -7,6 +7,8 @@
 //                     per node: the point force and torque on the fluid
 //                     (Eqs. discrete_f, discrete_n) written straight into the
 //                     pair kernel's source records
+//   k_lj_boxes, k_lj_forces  Lennard-Jones repulsion between filaments (Sec. IV)
+//   k_lj_rods         both and the rod forces, for few points
 //   k_reduce<EPI>     fixed-order FP64 sum of the split-K partials, scaling,
 //                     and the element-wise step epilogue (Eqs. newx, newD)
 //   k_small_steps     whole steps of ensembles of at most 64 points
@@ -147,85 +149,141 @@ __global__ __launch_bounds__(kBlock) void k_lj_boxes(int stage_state, const EnsD
 
 // Lennard-Jones force on every point (Sec. IV): the sum over points of other
 // filaments closer than r_c of 24 e (2 (sig/r)^12 - (sig/r)^6) (x_i - x_j)/r^2.
-// A block owns 64 points (one per lane); its kLjWaves waves split the LJ
-// source blocks (wave w takes every kLjWaves-th staged box), visit a block
-// only when one of their lanes lies within r_c of its box, and their partial
-// forces are added in wave order.  Sixteen waves keep the chain of boxes a
-// wave visits short when there are few target blocks (25 swimmers of 51
-// points: 20 blocks).  The block also writes the LJ mask of its 64 points: the
-// FP32C pair kernels evaluate those sources in FP64, since the equal and
-// opposite contact forces largely cancel at a distance and FP32 terms would
-// leave their rounding behind.
-constexpr int kLjWaves = 16;
-constexpr int kLjStage = 256;  // LJ source-block boxes staged in LDS per pass
+// A block owns up to 64 targets (one per lane).  Boxes first, then points:
+// source blocks whose box comes within r_c of the targets are found one per
+// lane, their points within r_c of the targets' box likewise, and only those
+// few points are paired with the targets, by all kLjWaves waves, whose partial
+// forces are added in wave order.
+constexpr int kLjWaves = 8;
+constexpr uint64_t kLjShare = 0x0101010101010101;  // lanes (sources) of wave 0: every kLjWaves-th
+static_assert(kLjWaves == 8, "kLjShare");
+
+struct LjConst {
+    double rc2, sig2, c24;
+    __device__ __forceinline__ explicit LjConst(const EnsDesc &E)
+        : rc2(E.lj_rc * E.lj_rc), sig2(E.lj_sig * E.lj_sig), c24(24.0 * E.lj_e) {}
+};
+
+// r < r_c is tested as r^2 < r_c^2 and 1/r^2 is one reciprocal refined twice
+// (the force vanishes at r_c = 2^(1/6) sigma, so a decision that differs from
+// r < r_c by a rounding changes no force).
+__device__ __forceinline__ void lj_pair(const LjConst &L, double r0, double r1, double r2, bool other, double *acc) {
+    const double rr2 = fma(r2, r2, fma(r1, r1, r0 * r0));
+    if (!other || !(rr2 < L.rc2)) return;
+    double inv = __builtin_amdgcn_rcp(rr2);
+    inv = fma(inv, fma(-rr2, inv, 1.0), inv);
+    inv = fma(inv, fma(-rr2, inv, 1.0), inv);
+    const double s2 = L.sig2 * inv, s6 = s2 * s2 * s2;
+    const double cf = L.c24 * fma(2.0 * s6, s6, -s6) * inv;
+    acc[0] = fma(cf, r0, acc[0]);
+    acc[1] = fma(cf, r1, acc[1]);
+    acc[2] = fma(cf, r2, acc[2]);
+}
+
+// Squared distance of the box lo, hi to the box lo1, hi1 (or point, lo1 = hi1).
+__device__ __forceinline__ double lj_gap2(const double *lo, const double *hi, const double *lo1, const double *hi1) {
+    double gap2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const double g = fmax(0.0, fmax(lo[c] - hi1[c], lo1[c] - hi[c]));
+        gap2 += g * g;
+    }
+    return gap2;
+}
+
+// The waves' partial forces of a block's targets, added in wave order.
+__device__ __forceinline__ void lj_combine(const double (*sPart)[3][64], int lane, double *acc) {
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        double v = sPart[0][c][lane];
+#pragma unroll
+        for (int q = 1; q < kLjWaves; q++) v += sPart[q][c][lane];
+        acc[c] = v;
+    }
+}
+
+// General form: aligned blocks of 64 targets; also writes the LJ mask of its
+// points: the FP32C pair kernels evaluate those sources in FP64, since the
+// equal and opposite contact forces largely cancel at a distance and FP32
+// terms would leave their rounding behind.  The source blocks are tested one
+// per lane against the boxes of the targets' runs (targets of one filament; the
+// last of kLjRuns boxes holds all further runs), those left against each
+// target: neighbours in the order may lie far apart, so one box around all 64
+// targets would leave 175 of 1,000 blocks instead of 4.  1,000 swimmers of 51
+// points take 16 us, 62 when every target was tested against every block and a
+// visited block's points went to one wave (MI355X).
+constexpr int kLjRuns = 4;
+constexpr int kLjGroups = 256;  // groups of 64 source blocks per pass
 
 __global__ __launch_bounds__(64 * kLjWaves) void k_lj_forces(int stage_state, const EnsDesc *__restrict__ desc,
                                                              const PointItem *__restrict__ items) {
-    constexpr int kWaves = kLjWaves;
-    __shared__ double sBox[kLjStage][6];
-    __shared__ int sBlk[kLjStage][3];
-    __shared__ double sPart[kWaves][3][64];
+    __shared__ uint64_t sNear[kLjGroups];
+    __shared__ double sRun[kLjRuns][6];
+    __shared__ double sPart[kLjWaves][3][64];
     const PointItem it = items[blockIdx.x];
     const EnsDesc &E = desc[it.ens];
     const int N = E.N;
     const double *__restrict__ X = stage_state ? E.Xs : E.X;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t share = kLjShare << w;
     const int i = it.p0 + lane;
     const bool real = i < N;
     const int ii = real ? i : N - 1;
-    const double x0 = X[ii], x1 = X[(size_t)N + ii], x2 = X[2 * (size_t)N + ii];
+    const double x[3] = {X[ii], X[(size_t)N + ii], X[2 * (size_t)N + ii]};
     const int fi = E.fil[ii];
-    const double rc = E.lj_rc, rc2 = rc * rc, sig2 = E.lj_sig * E.lj_sig, c24 = 24.0 * E.lj_e;
+    const LjConst L(E);
     double acc[3] = {0.0, 0.0, 0.0};
     const int nblk = E.n_ljblk;
-    for (int b0 = 0; b0 < nblk; b0 += kLjStage) {
+    // boxes of the runs, six bounds each, shared by the waves
+    const uint64_t starts = __ballot(lane == 0 || fi != __shfl_up(fi, 1, 64) ? 1 : 0);
+    const int run = min(__popcll(starts & (~0ull >> (63 - lane))) - 1, kLjRuns - 1);
+    const int runs = min(__popcll(starts), kLjRuns);
+    for (int q = w; q < 6 * runs; q += kLjWaves) {
+        const int c = q % 6;
+        const double v = c % 3 == 0 ? x[0] : (c % 3 == 1 ? x[1] : x[2]);
+        const double m = c < 3 ? wave_min_d(run == q / 6 ? v : INFINITY) : wave_max_d(run == q / 6 ? v : -INFINITY);
+        if (lane == 0) sRun[q / 6][c] = m;
+    }
+    for (int b0 = 0; b0 < nblk; b0 += 64 * kLjGroups) {
         __syncthreads();
-        if (tid < kLjStage && b0 + tid < nblk) {
+        const int groups = min(kLjGroups, (nblk - b0 + 63) / 64);
+        for (int g = w; g < groups; g += kLjWaves) {
+            const int bq = b0 + 64 * g + lane, b = min(bq, nblk - 1);
+            const int fb = E.lj_blk[3 * b + 2];
+            double bx[6];
 #pragma unroll
-            for (int c = 0; c < 6; c++) sBox[tid][c] = E.lj_box[6 * (size_t)(b0 + tid) + c];
+            for (int c = 0; c < 6; c++) bx[c] = E.lj_box[6 * (size_t)b + c];
+            bool close = false;
+            for (int r = 0; r < runs; r++) close = close || lj_gap2(bx, bx + 3, sRun[r], sRun[r] + 3) < L.rc2;
+            uint64_t mask = 0;
+            for (uint64_t m = __ballot(close && bq < nblk ? 1 : 0); m; m &= m - 1) {
+                const int q = __builtin_ctzll(m);
+                double b1[6];
 #pragma unroll
-            for (int c = 0; c < 3; c++) sBlk[tid][c] = E.lj_blk[3 * (b0 + tid) + c];
+                for (int c = 0; c < 6; c++) b1[c] = readlane_d(bx[c], q);
+                const int f1 = __builtin_amdgcn_readlane(fb, q);
+                if (__any(real && f1 != fi && lj_gap2(b1, b1 + 3, x, x) < L.rc2 ? 1 : 0)) mask |= 1ull << q;
+            }
+            if (lane == 0) sNear[g] = mask;
         }
         __syncthreads();
-        const int cnt = min(kLjStage, nblk - b0);
-        for (int bb = w; bb < cnt; bb += kWaves) {
-            double gap2 = 0.0;
-            const double xs[3] = {x0, x1, x2};
+        for (int g = 0; g < groups; g++) {
+            for (uint64_t m = sNear[g]; m; m &= m - 1) {
+                const int *blk = E.lj_blk + 3 * (b0 + 64 * g + __builtin_ctzll(m));
+                const bool other = real && blk[2] != fi;
+                // lane = source; of those within r_c of a run's box wave w
+                // takes every kLjWaves-th lane, broadcast from lane registers
+                const int j0 = blk[0], jn = blk[1] - j0;  // jn <= kLjBlockPoints
+                double y[3];
 #pragma unroll
-            for (int c = 0; c < 3; c++) {
-                const double g = fmax(0.0, fmax(sBox[bb][c] - xs[c], xs[c] - sBox[bb][3 + c]));
-                gap2 += g * g;
-            }
-            const bool near = real && gap2 < rc2 && sBlk[bb][2] != fi;
-            if (!__any(near ? 1 : 0)) continue;  // wave-uniform
-            // the wave loads the block's points once (lane = point, coalesced)
-            // and broadcasts them from lane registers: no dependent global
-            // load per source point
-            const int j0 = sBlk[bb][0], jn = sBlk[bb][1] - j0;  // jn <= kLjBlockPoints = 64
-            double y0 = 0.0, y1 = 0.0, y2 = 0.0;
-            if (lane < jn) {
-                y0 = X[j0 + lane];
-                y1 = X[(size_t)N + j0 + lane];
-                y2 = X[2 * (size_t)N + j0 + lane];
-            }
-            // r < r_c is tested as r^2 < r_c^2 and 1/r^2 is one reciprocal
-            // refined twice (the force vanishes at r_c = 2^(1/6) sigma, so a
-            // decision that differs from r < r_c by a rounding changes no
-            // force); four sources per iteration keep independent chains in
-            // flight
-#pragma unroll 4
-            for (int jj = 0; jj < jn; jj++) {
-                const double r0 = x0 - readlane_d(y0, jj), r1 = x1 - readlane_d(y1, jj), r2 = x2 - readlane_d(y2, jj);
-                const double rr2 = fma(r2, r2, fma(r1, r1, r0 * r0));
-                if (!near || !(rr2 < rc2)) continue;
-                double inv = __builtin_amdgcn_rcp(rr2);
-                inv = fma(inv, fma(-rr2, inv, 1.0), inv);
-                inv = fma(inv, fma(-rr2, inv, 1.0), inv);
-                const double s2 = sig2 * inv, s6 = s2 * s2 * s2;
-                const double cf = c24 * fma(2.0 * s6, s6, -s6) * inv;
-                acc[0] = fma(cf, r0, acc[0]);
-                acc[1] = fma(cf, r1, acc[1]);
-                acc[2] = fma(cf, r2, acc[2]);
+                for (int c = 0; c < 3; c++) y[c] = X[(size_t)c * N + j0 + min(lane, jn - 1)];
+                bool close = false;
+                for (int r = 0; r < runs; r++) close = close || lj_gap2(y, y, sRun[r], sRun[r] + 3) < L.rc2;
+                for (uint64_t src = __ballot(close && lane < jn ? 1 : 0) & share; src; src &= src - 1) {
+                    const int q = __builtin_ctzll(src);
+                    lj_pair(L, x[0] - readlane_d(y[0], q), x[1] - readlane_d(y[1], q), x[2] - readlane_d(y[2], q),
+                            other, acc);
+                }
             }
         }
     }
@@ -233,13 +291,7 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_forces(int stage_state, co
     for (int c = 0; c < 3; c++) sPart[w][c][lane] = acc[c];
     __syncthreads();
     if (w != 0) return;
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        double v = sPart[0][c][lane];
-#pragma unroll
-        for (int q = 1; q < kWaves; q++) v += sPart[q][c][lane];
-        acc[c] = v;
-    }
+    lj_combine(sPart, lane, acc);
     if (real) {
 #pragma unroll
         for (int c = 0; c < 3; c++) E.flj[(size_t)c * N + i] = acc[c];
@@ -247,6 +299,120 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_forces(int stage_state, co
     const bool pushed = real && (acc[0] != 0.0 || acc[1] != 0.0 || acc[2] != 0.0);
     const uint64_t mask = __ballot(pushed ? 1 : 0);
     if (lane == 0 && it.p0 < N) E.lj_mask[it.p0 / kLjMaskPoints] = mask;
+}
+
+// Repulsion and rod forces of one filament in one launch, for ensembles of at
+// most kLjRodPoints points in kLjRodBlocks source blocks whose pair kernel
+// reads no LJ mask: every block takes all positions into LDS and makes the
+// boxes itself, so k_lj_boxes, k_lj_forces and k_rod_forces, each a chain of
+// memory latencies on a nearly idle chip, become one: 25 swimmers of 51 points
+// take 9.9 us instead of 4.2 + 12.8 + 5.5 (MI355X).
+__global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int elastic, int scheme, int stage,
+                                                           double dt, const EnsDesc *__restrict__ desc,
+                                                           const RodItem *__restrict__ items) {
+    extern __shared__ double sX[];  // positions, [3][N]
+    __shared__ double sBox[kLjRodBlocks][6];
+    __shared__ int sBlk[kLjRodBlocks][3];
+    __shared__ double sPart[kLjWaves][3][64];
+    constexpr int kThreads = 64 * kLjWaves, kRodThreads = 128, kLoads = 8;
+    static_assert(kLjRodBlocks <= 64, "one source block per lane");
+    const RodItem it = items[blockIdx.x];
+    const EnsDesc &E = desc[it.ens];
+    const int N = E.N, nblk = E.n_ljblk;
+    const double *__restrict__ X = stage_state ? E.Xs : E.X;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t share = kLjShare << w;
+    if (it.fil < 0) {  // the whole block takes this branch (RodItem: kBlock / 64 descriptors)
+        const int b = (-1 - it.fil) * (kBlock / 64) + w;
+        if (w < kBlock / 64 && b * kDescPoints < N) block_desc_from_x(E, X, false, b);
+        return;
+    }
+    const int k0 = E.off[it.fil], k1 = E.off[it.fil + 1];
+    // every load the block starts from is in flight before the first is waited
+    // for (each is an L2 miss: the last kernel wrote it on other XCDs); what
+    // rod_filament reads first goes to the L1
+    double pre[16];
+    if (w < kRodThreads / 64) {
+        const double *__restrict__ D = stage_state ? E.Ds : E.D;
+        const int p = max(min(k0 + tid, k1 - 1), 0);
+#pragma unroll
+        for (int c = 0; c < 9; c++) pre[c] = D[(size_t)c * N + p];
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            pre[9 + c] = E.fext ? E.fext[(size_t)c * N + p] : 0.0;
+            pre[12 + c] = E.next ? E.next[(size_t)c * N + p] : 0.0;
+        }
+        pre[15] = *E.clock;
+    }
+    const int blk = E.lj_blk[min(tid, 3 * nblk - 1)];
+    for (int q0 = 0; q0 < 3 * N; q0 += kLoads * kThreads) {
+        double v[kLoads];
+#pragma unroll
+        for (int u = 0; u < kLoads; u++) v[u] = X[min(q0 + u * kThreads + tid, 3 * N - 1)];
+#pragma unroll
+        for (int u = 0; u < kLoads; u++)
+            if (q0 + u * kThreads + tid < 3 * N) sX[q0 + u * kThreads + tid] = v[u];
+    }
+    if (tid < 3 * nblk) sBlk[tid / 3][tid % 3] = blk;
+    if (w < kRodThreads / 64) {
+#pragma unroll
+        for (int c = 0; c < 16; c++) asm volatile("" ::"v"(pre[c]));
+    }
+    __syncthreads();
+    // four lanes per box and coordinate
+    for (int q = tid >> 2; q < 3 * nblk; q += kThreads / 4) {
+        const int b = q / 3, c = q - 3 * b, j0 = sBlk[b][0], j1 = sBlk[b][1] - 1;
+        double lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < kLjBlockPoints; k += 4) {
+            const double v = sX[c * N + min(j0 + k + (tid & 3), j1)];
+            lo = fmin(lo, v);
+            hi = fmax(hi, v);
+        }
+#pragma unroll
+        for (int off = 1; off <= 2; off <<= 1) {
+            lo = fmin(lo, __shfl_xor(lo, off, 4));
+            hi = fmax(hi, __shfl_xor(hi, off, 4));
+        }
+        if ((tid & 3) == 0) { sBox[b][c] = lo; sBox[b][3 + c] = hi; }
+    }
+    __syncthreads();
+    const LjConst L(E);
+    for (int p0 = k0; p0 < k1; p0 += 64) {
+        const int i = p0 + lane;
+        const bool real = i < k1;
+        const int ii = real ? i : k1 - 1;
+        const double x[3] = {sX[ii], sX[N + ii], sX[2 * N + ii]};
+        double acc[3] = {0.0, 0.0, 0.0};
+        // the targets are themselves a source block: its box against the
+        // others', one per lane
+        const int own = __builtin_ctzll(__ballot(lane < nblk && sBlk[min(lane, nblk - 1)][0] == p0 ? 1 : 0));
+        const int q = min(lane, nblk - 1);
+        const bool close = lane < nblk && sBlk[q][2] != it.fil &&
+                           lj_gap2(sBox[q], sBox[q] + 3, sBox[own], sBox[own] + 3) < L.rc2;
+        for (uint64_t m = __ballot(close ? 1 : 0); m; m &= m - 1) {
+            const int bb = __builtin_ctzll(m);
+            // lane = source; of those within r_c of the targets' box wave w
+            // takes every kLjWaves-th lane
+            const int j0 = sBlk[bb][0], jn = sBlk[bb][1] - j0, jl = j0 + min(lane, jn - 1);
+            const double y[3] = {sX[jl], sX[N + jl], sX[2 * N + jl]};
+            const uint64_t in = __ballot(lane < jn && lj_gap2(y, y, sBox[own], sBox[own] + 3) < L.rc2 ? 1 : 0);
+            for (uint64_t src = in & share; src; src &= src - 1) {
+                const int q = __builtin_ctzll(src);
+                lj_pair(L, x[0] - readlane_d(y[0], q), x[1] - readlane_d(y[1], q), x[2] - readlane_d(y[2], q), real, acc);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; c++) sPart[w][c][lane] = acc[c];
+        __syncthreads();
+        if (w == 0 && real) {
+            lj_combine(sPart, lane, acc);
+#pragma unroll
+            for (int c = 0; c < 3; c++) E.flj[(size_t)c * N + i] = acc[c];
+        }
+        __syncthreads();
+    }
+    rod_filament<kRodThreads, false, kThreads>(stage_state, elastic, scheme, stage, dt, E, k0, k1 - k0);
 }
 
 // ------------------------------------------------------- reduce + epilogue
@@ -608,6 +774,14 @@ hipError_t launch_lj(int stage_state, const EnsDesc *d_desc, const PointItem *d_
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_lj_forces, dim3(n_items), dim3(64 * kLjWaves), 0, s, stage_state, d_desc, d_items);
+    return hipGetLastError();
+}
+
+hipError_t launch_lj_rods(int stage_state, int elastic, int scheme, int stage, double dt, const EnsDesc *d_desc,
+                          const RodItem *d_items, int n_items, int max_points, hipStream_t s) {
+    if (n_items == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_lj_rods, dim3(n_items), dim3(64 * kLjWaves), (size_t)max_points * 3 * sizeof(double), s,
+                       stage_state, elastic, scheme, stage, dt, d_desc, d_items);
     return hipGetLastError();
 }
 

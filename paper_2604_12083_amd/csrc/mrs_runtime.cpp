@@ -81,8 +81,8 @@ DevPool::~DevPool() {
 }
 
 void plan_use_pool(Plan &P, DevPool *pool) {
-    for (DevBuf *b : {&P.d_desc, &P.d_split, &P.d_tile1, &P.d_tile2, &P.d_quad, &P.d_wide1, &P.d_rods, &P.d_pts, &P.d_lj,
-                      &P.d_ljb, &P.d_queue})
+    for (DevBuf *b : {&P.d_desc, &P.d_split, &P.d_tile1, &P.d_tile2, &P.d_quad, &P.d_wide1, &P.d_rods, &P.d_ljrods, &P.d_pts,
+                      &P.d_lj, &P.d_ljb, &P.d_queue})
         b->pool = pool;
 }
 
@@ -110,8 +110,16 @@ static hipError_t upload_vec(DevBuf &d, const std::vector<T> &v) {
 }
 
 
+// After add_items of ensemble e, the plan's last.
 void add_lj_items(Plan &P, int e, const mrs_ensemble *E) {
     if (!E->has_lj) return;
+    if (E->N <= kLjRodPoints && E->n_ljblk <= kLjRodBlocks && P.h_desc[e].form != REC_F32) {
+        const auto own = std::find_if(P.rods.begin(), P.rods.end(), [e](const RodItem &r) { return r.ens == e; });
+        P.ljrods.insert(P.ljrods.end(), own, P.rods.end());
+        P.rods.erase(own, P.rods.end());
+        P.lj_points = std::max(P.lj_points, (int)E->N);
+        return;
+    }
     for (int64_t p0 = 0; p0 < E->N; p0 += kLjMaskPoints) P.lj.push_back({e, (int)p0});
     for (int b0 = 0; b0 < E->n_ljblk; b0 += kBlock / 64) P.ljb.push_back({e, b0});
 }
@@ -130,6 +138,7 @@ hipError_t finalize_plan(Plan &P) {
     if ((e = upload_vec(P.d_quad, P.quad)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_wide1, P.wide1)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_rods, P.rods)) != hipSuccess) return e;
+    if ((e = upload_vec(P.d_ljrods, P.ljrods)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_lj, P.lj)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_ljb, P.ljb)) != hipSuccess) return e;
     return upload_vec(P.d_pts, P.pts);
@@ -296,11 +305,20 @@ hipError_t run_stage(mrs_context *ctx, Plan &P, int stage_state, int elastic, in
         });
         if (e != hipSuccess) return e;
     }
-    e = timed(ctx, "rod_forces", s, [&] {
-        return launch_rod_forces(stage_state, elastic, scheme, stage, dt, P.d_desc.as<EnsDesc>(),
-                                 P.d_rods.as<RodItem>(), (int)P.rods.size(), s);
-    });
-    if (e != hipSuccess) return e;
+    if (!P.ljrods.empty()) {
+        e = timed(ctx, "lj_rod_forces", s, [&] {
+            return launch_lj_rods(stage_state, elastic, scheme, stage, dt, P.d_desc.as<EnsDesc>(),
+                                  P.d_ljrods.as<RodItem>(), (int)P.ljrods.size(), P.lj_points, s);
+        });
+        if (e != hipSuccess) return e;
+    }
+    if (!P.rods.empty()) {
+        e = timed(ctx, "rod_forces", s, [&] {
+            return launch_rod_forces(stage_state, elastic, scheme, stage, dt, P.d_desc.as<EnsDesc>(),
+                                     P.d_rods.as<RodItem>(), (int)P.rods.size(), s);
+        });
+        if (e != hipSuccess) return e;
+    }
     if ((e = run_pairs(ctx, P, s)) != hipSuccess) return e;
     return timed(ctx, epi_name(epi), s, [&] {
         return launch_reduce(epi, stage, scheme, dt, P.d_desc.as<EnsDesc>(), P.d_pts.as<PointItem>(),
