@@ -56,7 +56,7 @@ __device__ __forceinline__ void block_desc_from_x(const EnsDesc &E, const double
 // One thread per point; with block descriptors (E.blk set) every wave
 // (64 consecutive points, block-aligned) also writes its block's descriptor.
 __global__ __launch_bounds__(kBlock) void k_pack_aos(const EnsDesc *__restrict__ desc) {
-    const EnsDesc &E = desc[0];
+    const EnsDesc E = global_desc(desc[0]);
     const int i = blockIdx.x * kBlock + threadIdx.x;
     const double *X = E.Xin_aos;
     if (i < E.N) {
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kBlock) void k_rod_forces(int stage_state, int elas
                                                         double dt, const EnsDesc *__restrict__ desc,
                                                        const RodItem *__restrict__ items) {
     const RodItem it = items[blockIdx.x];
-    const EnsDesc &E = desc[it.ens];
+    const EnsDesc E = global_desc(desc[it.ens]);
     if (it.fil < 0) {  // the whole block takes this branch
         const int b = (-1 - it.fil) * (kBlock / 64) + (int)(threadIdx.x >> 6);
         if (b * kDescPoints < E.N) block_desc_from_x(E, stage_state ? E.Xs : E.X, false, b);
@@ -126,7 +126,7 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
 __global__ __launch_bounds__(kBlock) void k_lj_boxes(int stage_state, const EnsDesc *__restrict__ desc,
                                                      const PointItem *__restrict__ items) {
     const PointItem it = items[blockIdx.x];
-    const EnsDesc &E = desc[it.ens];
+    const EnsDesc E = global_desc(desc[it.ens]);
     const int b = it.p0 + (int)(threadIdx.x >> 6);
     if (b >= E.n_ljblk) return;  // wave-uniform
     const int N = E.N;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_forces(int stage_state, co
     __shared__ double sRun[kLjRuns][6];
     __shared__ double sPart[kLjWaves][3][64];
     const PointItem it = items[blockIdx.x];
-    const EnsDesc &E = desc[it.ens];
+    const EnsDesc E = global_desc(desc[it.ens]);
     const int N = E.N;
     const double *__restrict__ X = stage_state ? E.Xs : E.X;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int 
     constexpr int kThreads = 64 * kLjWaves, kRodThreads = 128, kLoads = 8;
     static_assert(kLjRodBlocks <= 64, "one source block per lane");
     const RodItem it = items[blockIdx.x];
-    const EnsDesc &E = desc[it.ens];
+    const EnsDesc E = global_desc(desc[it.ens]);
     const int N = E.N, nblk = E.n_ljblk;
     const double *__restrict__ X = stage_state ? E.Xs : E.X;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(int stage, int scheme
                                                    const PointItem *__restrict__ items) {
     __shared__ double sPart[kReduceThreads / 64][6][64];
     const PointItem it = items[blockIdx.x];
-    const EnsDesc &E = desc[it.ens];
+    const EnsDesc E = global_desc(desc[it.ens]);
     const int N = E.N;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int i = it.p0 + lane;
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_steps(int nsteps, int e
     __shared__ double sF[3][P + 1], sN[3][P + 1], sX[3][P + 1];
     __shared__ double sPart[kWaves][6][P];
     __shared__ double sClock;
-    const EnsDesc &G0 = desc[blockIdx.x];
+    const EnsDesc G0 = global_desc(desc[blockIdx.x]);
     const int N = G0.N;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (elastic < 0) elastic = G0.elastic;

@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
     int idx = PERSIST ? claim_item(queue, &sNext) : (int)blockIdx.x;
     while (idx < n_items) {
     const PairItem it = items[idx];
-    const EnsDesc &E = desc[it.ens];
+    const EnsDesc &E = desc[it.ens];  // not global_desc: even in time, and 12 B of spills when persistent
     const RecF32 *__restrict__ rec = reinterpret_cast<const RecF32 *>(E.rec);
     const int tid = threadIdx.x;
     // target slot of this lane: the block's lanes (tiled) or the wave's (QUAD)
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
     int idx = PERSIST ? claim_item(queue, &sNext) : (int)blockIdx.x;
     while (idx < n_items) {
     const PairItem it = items[idx];
-    const EnsDesc &E = desc[it.ens];
+    const EnsDesc E = global_desc(desc[it.ens]);
     const RecF64 *__restrict__ rec = reinterpret_cast<const RecF64 *>(E.rec);
     const int tid = threadIdx.x;
     const double eps = E.rec_eps, e2 = eps * eps, c375e2 = 3.75 * e2;
@@ -690,7 +690,7 @@ __device__ __forceinline__ void split_item(const EnsDesc &E, const PairItem it) 
 __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restrict__ desc,
                                                         const PairItem *__restrict__ items) {
     const PairItem it = items[blockIdx.x];
-    split_item<false>(desc[it.ens], it);
+    split_item<false>(global_desc(desc[it.ens]), it);
 }
 
 // One-shot evaluation of E.N <= kDirectMaxPoints points in one launch, with no
