@@ -240,7 +240,8 @@ hipError_t launch_rows_out(const RowArrays &ra, const int32_t *inv, int64_t N, i
 hipError_t launch_set_value(double *p, double v, hipStream_t s);
 
 // Pair-kernel modes.
-// PAIR_QUAD (FP32C): tiles of 64 targets whose four waves split the sources.
+// PAIR_QUAD: tiles of 64 targets whose four waves split the sources (FP32C
+// items of 64 targets; FP64 in quarters of PAIR_TILE items).
 enum PairMode : int { PAIR_TILE = 0, PAIR_SPLIT = 1, PAIR_QUAD = 2 };
 // Schedules of the tiled pair kernels: one block per item, or a resident
 // grid whose blocks claim items from a queue.

@@ -540,28 +540,47 @@ __device__ __forceinline__ void far_block_f64(const STAGE &S, int sb, int se, co
     }
 }
 
+// QUAD: a block takes a quarter of an item's targets, 64, and its four waves
+// split each source block: four times the blocks of a quarter of the time.  In
+// a small grid a wave has a SIMD to itself or shares it with one or two
+// others, so the time is that of the longest chain and of the fullest CU (25
+// swimmers of 51 points, 100 items: 14.6 -> 8.8 us, MI355X).
 // Blocks per CU the register budget allows: 4 with one target per lane, 3 with two.
-template <int T, bool PERSIST>
+template <int T, bool PERSIST, bool QUAD>
 __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const EnsDesc *__restrict__ desc,
                                                            const PairItem *__restrict__ items, int n_items,
                                                            uint32_t *queue) {
+    static_assert(!QUAD || T == 1, "four-wave source split: one target per lane");
+    constexpr int kTargets = QUAD ? 64 : kBlock;    // targets per block and t
+    constexpr int kPart = QUAD ? kDescPoints / 4 : kDescPoints;  // sources of a block per wave
     __shared__ SrcStageF64<kSrcTile> S;
     __shared__ int sNext;
     int idx = PERSIST ? claim_item(queue, &sNext) : (int)blockIdx.x;
     while (idx < n_items) {
-    const PairItem it = items[idx];
+    PairItem it = items[QUAD ? idx / 4 : idx];
+    if (QUAD) {
+        const int q = 64 * (idx % 4);
+        if (q >= it.ntgt) {  // the last tile is not full
+            if (!PERSIST) break;
+            idx = claim_item(queue, &sNext);
+            continue;
+        }
+        it.tgt0 += q;
+        it.ntgt = min(64, it.ntgt - q);
+    }
     const EnsDesc E = global_desc(desc[it.ens]);
     const RecF64 *__restrict__ rec = reinterpret_cast<const RecF64 *>(E.rec);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, tl = QUAD ? tid & 63 : tid;
+    const int part0 = QUAD ? __builtin_amdgcn_readfirstlane(tid >> 6) * kPart : 0;
     const double eps = E.rec_eps, e2 = eps * eps, c375e2 = 3.75 * e2;
     double tx[T], ty[T], tz[T], acc[T][6];
     const desc_float *tbox[T];  // descriptors of the blocks this wave's targets lie in (wave-uniform)
 #pragma unroll
     for (int t = 0; t < T; t++) {
-        const int li = min(tid + t * kBlock, it.ntgt - 1);
+        const int li = min(tl + t * kTargets, it.ntgt - 1);
         const RecF64 &r = rec[it.tgt0 + li];
         tx[t] = r.x; ty[t] = r.y; tz[t] = r.z;
-        const int wb = (it.tgt0 + min((tid & ~63) + t * kBlock, it.ntgt - 1)) / kDescPoints;
+        const int wb = (it.tgt0 + min((tl & ~63) + t * kTargets, it.ntgt - 1)) / kDescPoints;
         tbox[t] = desc_at(E.blk, __builtin_amdgcn_readfirstlane(wb));
 #pragma unroll
         for (int k = 0; k < 6; k++) acc[t][k] = 0.0;
@@ -573,7 +592,7 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
         __syncthreads();
         const int cnt = min(kSrcTile, it.nsrc - base);
         for (int sb = 0; sb < cnt; sb += kDescPoints) {
-            const int se = min(sb + kDescPoints, cnt);
+            const int s0 = sb + part0, se = min(s0 + kPart, cnt);
             const desc_float *d = desc_at(E.blk, (it.src0 + base + sb) / kDescPoints);
             float slo[3], shi[3], gap2 = INFINITY;
 #pragma unroll
@@ -586,11 +605,11 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
                 gap2 = fminf(gap2, box_gap2(lo, hi, slo, shi));
             }
             if (gap2 > kFarBoxGap2 && gap2 > kSplitGapRatio2F64 * d[9]) {  // wave-uniform
-                far_block_f64<T>(S, sb, se, tx, ty, tz, (double)d[6] * eps, (double)d[7] * eps, (double)d[8] * eps, e2,
+                far_block_f64<T>(S, s0, se, tx, ty, tz, (double)d[6] * eps, (double)d[7] * eps, (double)d[8] * eps, e2,
                                  acc);
             } else {
 #pragma unroll 2
-                for (int jj = sb; jj < se; jj++) {
+                for (int jj = s0; jj < se; jj++) {
                     const double2 A = S.a[jj], B = S.b[jj], C = S.c[jj], D = S.d[jj];
                     const double nz = S.e[jj].x;
 #pragma unroll
@@ -601,12 +620,29 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
         }
     }
     const int N = E.N;
+    if (QUAD) {
+        // the four waves' sums for the same targets, added in wave order (the
+        // staged sources are no longer needed)
+        double *sum = reinterpret_cast<double *>(&S);  // [6][kBlock]
+        static_assert(sizeof(S) >= 6 * kBlock * sizeof(double), "sums of four waves");
+        __syncthreads();
 #pragma unroll
-    for (int t = 0; t < T; t++) {
-        const int li = tid + t * kBlock;
-        if (li < it.ntgt) {
+        for (int k = 0; k < 6; k++) sum[k * kBlock + tid] = acc[0][k];
+        __syncthreads();
+        for (int k = tid >> 6; k < 6; k += kBlock / 64) {
+            double v = sum[k * kBlock + tl];
 #pragma unroll
-            for (int k = 0; k < 6; k++) E.part[((size_t)it.chunk * 6 + k) * N + it.tgt0 + li] = acc[t][k];
+            for (int w = 1; w < kBlock / 64; w++) v += sum[k * kBlock + w * 64 + tl];
+            if (tl < it.ntgt) E.part[((size_t)it.chunk * 6 + k) * N + it.tgt0 + tl] = v;
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < T; t++) {
+            const int li = tid + t * kBlock;
+            if (li < it.ntgt) {
+#pragma unroll
+                for (int k = 0; k < 6; k++) E.part[((size_t)it.chunk * 6 + k) * N + it.tgt0 + li] = acc[t][k];
+            }
         }
     }
     if (!PERSIST) break;
@@ -716,7 +752,7 @@ static void launch_tile(int prec, dim3 g, dim3 b, hipStream_t s, const EnsDesc *
                         int n_items, uint32_t *queue) {
     if (prec == 1)
         hipLaunchKernelGGL((k_pairs_tile_f32<T, PERSIST, false>), g, b, 0, s, d_desc, d_items, n_items, queue);
-    else hipLaunchKernelGGL((k_pairs_tile_f64<T, PERSIST>), g, b, 0, s, d_desc, d_items, n_items, queue);
+    else hipLaunchKernelGGL((k_pairs_tile_f64<T, PERSIST, false>), g, b, 0, s, d_desc, d_items, n_items, queue);
 }
 
 // Resident blocks per CU of a tiled pair kernel (persistent schedule).
@@ -730,8 +766,8 @@ int pairs_resident_blocks(int prec, int tpl) {
         e = tpl == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pairs_tile_f32<2, true, false>, kBlock, 0)
                      : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pairs_tile_f32<1, true, false>, kBlock, 0);
     else
-        e = tpl == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pairs_tile_f64<2, true>, kBlock, 0)
-                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pairs_tile_f64<1, true>, kBlock, 0);
+        e = tpl == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pairs_tile_f64<2, true, false>, kBlock, 0)
+                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pairs_tile_f64<1, true, false>, kBlock, 0);
     c = (e == hipSuccess && nb > 0) ? nb : 1;
     return c;
 }
@@ -743,7 +779,14 @@ hipError_t launch_pairs(int prec, int mode, int tpl, const EnsDesc *d_desc, cons
     if (mode == PAIR_SPLIT) {
         const dim3 g(n_items);
         hipLaunchKernelGGL(k_pairs_split, g, b, 0, s, d_desc, d_items);
-    } else if (mode == PAIR_QUAD) {  // FP32C only (the plan never makes FP64 QUAD items)
+    } else if (mode == PAIR_QUAD && prec != 1) {  // in quarters: four blocks per item
+        const int n = 4 * n_items;
+        if (queue && resident > 0)
+            hipLaunchKernelGGL((k_pairs_tile_f64<1, true, true>), dim3((unsigned)std::min(n, resident)), b, 0, s,
+                               d_desc, d_items, n, queue);
+        else
+            hipLaunchKernelGGL((k_pairs_tile_f64<1, false, true>), dim3(n), b, 0, s, d_desc, d_items, n, nullptr);
+    } else if (mode == PAIR_QUAD) {
         if (queue && resident > 0)
             hipLaunchKernelGGL((k_pairs_tile_f32<1, true, true>), dim3((unsigned)std::min(n_items, resident)), b, 0, s,
                                d_desc, d_items, n_items, queue);

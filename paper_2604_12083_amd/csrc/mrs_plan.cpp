@@ -141,6 +141,15 @@ bool wide_records(const PairCfg &c, int64_t N, int prec, bool has_lj) {
     return c.mode == PAIR_SPLIT || (c.mode == PAIR_TILE && c.tpl == 1 && has_lj && N <= kWideContactPoints);
 }
 
+// Ensembles whose FP64 sum at one target per lane runs in quarters of the work
+// items (k_pairs_tile_f64).  Alone that fills the chip better, in deep batches
+// its further staging costs some percent (pair kernel alone and in batches of
+// eight, in place of whole items: 1,275 points 13.8 -> 8.5 and 38.2 -> 31.7 us,
+// 2,048 points 15.3 -> 13.0 and 69.7 -> 71.4, 3,200 points 38.4 -> 27.5 and
+// 170 -> 167; 3,968 points 39.9 -> 36.0 but 247 -> 252, 5,120 points 68 -> 59
+// but 395 -> 415; MI355X).
+constexpr int64_t kQuarterPoints = 3200;
+
 void add_items(Plan &P, int e, int64_t N, int n_fil, const PairCfg &c) {
     if (c.mode != PAIR_SPLIT && c.sched == SCHED_PERSISTENT) P.sched = SCHED_PERSISTENT;
     if (c.mode == PAIR_SPLIT) {
@@ -149,8 +158,9 @@ void add_items(Plan &P, int e, int64_t N, int n_fil, const PairCfg &c) {
     } else {
         const bool quad = c.mode == PAIR_QUAD;
         const int64_t tile = quad ? 64 : (int64_t)kBlock * c.tpl;
-        auto &dst = quad ? P.quad : (c.wide ? P.wide1 : (c.tpl == 2 ? P.tile2 : P.tile1));
-        auto &tail = quad ? P.tailq : (c.wide ? P.tailw : (c.tpl == 2 ? P.tail2 : P.tail1));
+        const bool quart = !quad && c.tpl == 1 && (c.wide || (P.prec == MRS_FP64 && N <= kQuarterPoints));
+        auto &dst = quad ? P.quad : (quart ? P.quart : (c.tpl == 2 ? P.tile2 : P.tile1));
+        auto &tail = quad ? P.tailq : (quart ? P.tailr : (c.tpl == 2 ? P.tail2 : P.tail1));
         // chunk-major: consecutive blocks share a source chunk, so every XCD
         // (blocks go to the 8 XCDs in turn) reads each chunk once into its L2
         const int64_t B = c.tail_start > 0 ? c.tail_start : N;  // end of the regular chunks
@@ -191,15 +201,15 @@ void order_items(Plan &P) {
     near_blocks_first(P.tile1);
     near_blocks_first(P.tile2);
     near_blocks_first(P.quad);
-    near_blocks_first(P.wide1);
+    near_blocks_first(P.quart);
     P.tile1.insert(P.tile1.end(), P.tail1.begin(), P.tail1.end());
     P.tile2.insert(P.tile2.end(), P.tail2.begin(), P.tail2.end());
     P.quad.insert(P.quad.end(), P.tailq.begin(), P.tailq.end());
-    P.wide1.insert(P.wide1.end(), P.tailw.begin(), P.tailw.end());
+    P.quart.insert(P.quart.end(), P.tailr.begin(), P.tailr.end());
     P.tail1.clear();
     P.tail2.clear();
     P.tailq.clear();
-    P.tailw.clear();
+    P.tailr.clear();
 }
 
 // Ensembles of at most kSmallPoints points (the limit's reason: k_small_steps)
@@ -208,7 +218,7 @@ void order_items(Plan &P) {
 bool small_plan(const Plan &P) {
     for (const EnsDesc &d : P.h_desc)
         if (d.N > kSmallPoints || d.K != 1 || d.has_lj) return false;
-    return !P.split.empty() && P.tile1.empty() && P.tile2.empty() && P.quad.empty() && P.wide1.empty();
+    return !P.split.empty() && P.tile1.empty() && P.tile2.empty() && P.quad.empty() && P.quart.empty();
 }
 
 }  // namespace mrs
@@ -227,7 +237,7 @@ extern "C" mrs_status mrs_plan_items(int64_t n, mrs_precision prec, int32_t n_cu
     add_items(P, 0, n, 0, c);
     order_items(P);
     const std::vector<PairItem> &v =
-        c.mode == PAIR_SPLIT ? P.split : (c.mode == PAIR_QUAD ? P.quad : (c.tpl == 2 ? P.tile2 : P.tile1));
+        c.mode == PAIR_SPLIT ? P.split : (c.mode == PAIR_QUAD ? P.quad : (c.tpl == 2 ? P.tile2 : (P.quart.empty() ? P.tile1 : P.quart)));
     *n_items = (int64_t)v.size();
     if (mode) *mode = c.mode;
     if (targets_per_lane) *targets_per_lane = c.tpl;

@@ -81,7 +81,7 @@ DevPool::~DevPool() {
 }
 
 void plan_use_pool(Plan &P, DevPool *pool) {
-    for (DevBuf *b : {&P.d_desc, &P.d_split, &P.d_tile1, &P.d_tile2, &P.d_quad, &P.d_wide1, &P.d_rods, &P.d_ljrods, &P.d_pts,
+    for (DevBuf *b : {&P.d_desc, &P.d_split, &P.d_tile1, &P.d_tile2, &P.d_quad, &P.d_quart, &P.d_rods, &P.d_ljrods, &P.d_pts,
                       &P.d_lj, &P.d_ljb, &P.d_queue})
         b->pool = pool;
 }
@@ -136,7 +136,7 @@ hipError_t finalize_plan(Plan &P) {
     if ((e = upload_vec(P.d_tile1, P.tile1)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_tile2, P.tile2)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_quad, P.quad)) != hipSuccess) return e;
-    if ((e = upload_vec(P.d_wide1, P.wide1)) != hipSuccess) return e;
+    if ((e = upload_vec(P.d_quart, P.quart)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_rods, P.rods)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_ljrods, P.ljrods)) != hipSuccess) return e;
     if ((e = upload_vec(P.d_lj, P.lj)) != hipSuccess) return e;
@@ -249,16 +249,16 @@ static const char *pair_name(int prec, int mode) {
 // counters when the plan runs the persistent schedule.
 static hipError_t pair_launches(mrs_context *ctx, int prec, int sched, const EnsDesc *dd, const PairItem *split,
                                 int n_split, const PairItem *t1, int n_t1, const PairItem *t2, int n_t2,
-                                const PairItem *tq, int n_tq, const PairItem *tw, int n_tw, uint32_t *queue,
+                                const PairItem *tq, int n_tq, const PairItem *tr, int n_tr, uint32_t *queue,
                                 hipStream_t s) {
     hipError_t e = hipSuccess;
     const bool pers = sched == SCHED_PERSISTENT && queue;
     if (n_split)
         e = timed(ctx, pair_name(prec, PAIR_SPLIT), s,
                   [&] { return launch_pairs(prec, PAIR_SPLIT, 1, dd, split, n_split, s); });
-    if (e == hipSuccess && n_tw)  // records of the FP64 kind
+    if (e == hipSuccess && n_tr)  // records of the FP64 kind
         e = timed(ctx, pair_name(prec, PAIR_TILE), s, [&] {
-            return launch_pairs(MRS_FP64, PAIR_TILE, 1, dd, tw, n_tw, s, pers ? queue + 6 : nullptr,
+            return launch_pairs(MRS_FP64, PAIR_QUAD, 1, dd, tr, n_tr, s, pers ? queue + 6 : nullptr,
                                 pers ? pairs_resident_blocks(MRS_FP64, 1) * ctx->n_cu : 0);
         });
     if (e == hipSuccess && n_t1)
@@ -283,7 +283,7 @@ hipError_t run_pairs(mrs_context *ctx, Plan &P, hipStream_t s) {
     return pair_launches(ctx, P.prec, P.sched, P.d_desc.as<EnsDesc>(), P.d_split.as<PairItem>(), (int)P.split.size(),
                          P.d_tile1.as<PairItem>(), (int)P.tile1.size(), P.d_tile2.as<PairItem>(),
                          (int)P.tile2.size(), P.d_quad.as<PairItem>(), (int)P.quad.size(),
-                         P.d_wide1.as<PairItem>(), (int)P.wide1.size(), P.d_queue.as<uint32_t>(), s);
+                         P.d_quart.as<PairItem>(), (int)P.quart.size(), P.d_queue.as<uint32_t>(), s);
 }
 
 const char *epi_name(int epi) {
@@ -741,7 +741,7 @@ struct EvalLayout {
     Plan P;
     EnsDesc d{};
     std::vector<char> blob;
-    size_t o_desc = 0, o_split = 0, o_t1 = 0, o_t2 = 0, o_tq = 0, o_pts = 0, o_queue = 0;
+    size_t o_desc = 0, o_split = 0, o_t1 = 0, o_t2 = 0, o_tq = 0, o_tr = 0, o_pts = 0, o_queue = 0;
 };
 
 static mrs_status eval_args(mrs_context *ctx, int64_t n, const double *dX, const double *df, const double *dt,
@@ -805,6 +805,7 @@ static void eval_layout(EvalLayout &L, int64_t n, const EnsDesc &args, int p, co
     L.o_t1 = put(L.P.tile1.data(), L.P.tile1.size() * sizeof(PairItem));
     L.o_t2 = put(L.P.tile2.data(), L.P.tile2.size() * sizeof(PairItem));
     L.o_tq = put(L.P.quad.data(), L.P.quad.size() * sizeof(PairItem));
+    L.o_tr = put(L.P.quart.data(), L.P.quart.size() * sizeof(PairItem));
     L.o_pts = put(L.P.pts.data(), L.P.pts.size() * sizeof(PointItem));
     const uint32_t zero[kQueueWords] = {};
     L.o_queue = put(zero, sizeof zero);  // work-queue counters start at zero
@@ -819,7 +820,8 @@ static hipError_t eval_launch(mrs_context *ctx, const EvalLayout &L, int p, cons
         e = pair_launches(ctx, p, P.sched, dd, reinterpret_cast<const PairItem *>(base + L.o_split),
                           (int)P.split.size(), reinterpret_cast<const PairItem *>(base + L.o_t1), (int)P.tile1.size(),
                           reinterpret_cast<const PairItem *>(base + L.o_t2), (int)P.tile2.size(),
-                          reinterpret_cast<const PairItem *>(base + L.o_tq), (int)P.quad.size(), nullptr, 0,
+                          reinterpret_cast<const PairItem *>(base + L.o_tq), (int)P.quad.size(),
+                          reinterpret_cast<const PairItem *>(base + L.o_tr), (int)P.quart.size(),
                           reinterpret_cast<uint32_t *>(const_cast<char *>(base) + L.o_queue), s);
     if (e == hipSuccess)
         e = timed(ctx, "reduce_write", s, [&] {

@@ -85,15 +85,15 @@ struct Plan {
     int prec = 0;
     int n_ens = 0;
     std::vector<EnsDesc> h_desc;
-    std::vector<PairItem> split, tile1, tile2, quad, wide1;  // wide1: tile1 on REC_WIDE records (FP64 kernel)
-    std::vector<PairItem> tail1, tail2, tailq, tailw;  // tail-split items, dispatched after tile1 / tile2 / quad / wide1
+    std::vector<PairItem> split, tile1, tile2, quad, quart;  // quart: quarters of tile1 items (FP64 kernel)
+    std::vector<PairItem> tail1, tail2, tailq, tailr;  // tail-split items, dispatched after tile1 / tile2 / quad / quart
     std::vector<RodItem> rods;
     std::vector<RodItem> ljrods;  // rods of the ensembles k_lj_rods takes, the largest of lj_points points
     int lj_points = 0;
     std::vector<PointItem> pts;
     std::vector<PointItem> lj;   // 64-point target blocks of the ensembles with LJ repulsion
     std::vector<PointItem> ljb;  // their LJ source blocks, kBlock / 64 per item
-    DevBuf d_desc, d_split, d_tile1, d_tile2, d_quad, d_wide1, d_rods, d_ljrods, d_pts, d_lj, d_ljb;
+    DevBuf d_desc, d_split, d_tile1, d_tile2, d_quad, d_quart, d_rods, d_ljrods, d_pts, d_lj, d_ljb;
     int sched = SCHED_GRID;  // persistent if any ensemble of the plan asks for it
     DevBuf d_queue;          // kQueueWords uint32, zero between launches
     // cached graphs: key = (integrator, dt bits, steps, elastic)
