@@ -199,10 +199,9 @@ hipError_t launch_pairs(int prec, int mode, int tpl, const EnsDesc *d_desc, cons
                         int n_items, hipStream_t s, uint32_t *queue = nullptr, int resident = 0);
 // One-shot evaluation in one launch: h_desc's row-major inputs (Xin_aos, fext,
 // next) and outputs (U, W), its scales and size; outputs must not overlap
-// inputs.  Up to kDirectMaxPoints points every block forms all records again
-// for little (at 2,048 points a fortieth of its pair work).
-constexpr int kDirectMaxPoints = 2048;
-hipError_t launch_eval_direct(const EnsDesc &h_desc, hipStream_t s);
+// inputs.  Every block forms all records again, for little (at 2,048 points a
+// fortieth of its pair work).
+hipError_t launch_eval_direct(const EnsDesc &h_desc, int n_cu, hipStream_t s);
 // Resident blocks per CU of the persistent tiled pair kernel.
 int pairs_resident_blocks(int prec, int tpl);
 // dt = NaN: every ensemble uses its own EnsDesc::dt.

@@ -668,9 +668,8 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
 // the pack and reduction kernels.
 constexpr int kSplitRound = kBlock;
 
-template <bool DIRECT>
+template <bool DIRECT, int TW>
 __device__ __forceinline__ void split_item(const EnsDesc &E, const PairItem it) {
-    constexpr int TW = kSplitTargetsPerWave;
     static_assert(sizeof(RecF32) == 48 && sizeof(RecF64) == 80, "record layouts");
     __shared__ RecF64 sRec[kSplitRound];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -726,24 +725,34 @@ __device__ __forceinline__ void split_item(const EnsDesc &E, const PairItem it) 
 __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restrict__ desc,
                                                         const PairItem *__restrict__ items) {
     const PairItem it = items[blockIdx.x];
-    split_item<false>(global_desc(desc[it.ens]), it);
+    split_item<false, kSplitTargetsPerWave>(global_desc(desc[it.ens]), it);
 }
 
-// One-shot evaluation of E.N <= kDirectMaxPoints points in one launch, with no
-// scratch and no work list: a 64-point FP64 call takes 12 us on one stream,
-// 23 us on streams in turn (each waits for the one before) instead of 36 with
-// pack, pair and reduction kernels and an uploaded list (MI355X).
+// One-shot evaluation in one launch, with no scratch and no work list: a
+// 64-point FP64 call takes 12 us on one stream, 23 us on streams in turn (each
+// waits for the one before) instead of 36 with pack, pair and reduction
+// kernels and an uploaded list (MI355X).  Larger ones, see launch_eval_direct.
+template <int TW>
 __global__ __launch_bounds__(kBlock) void k_eval_direct(const EnsDesc E) {
-    const int t0 = (int)blockIdx.x * kSplitTargetsPerBlock;
-    split_item<true>(E, {0, t0, min(kSplitTargetsPerBlock, E.N - t0), 0, E.N, 0});
+    constexpr int kTargets = TW * (kBlock / 64);
+    const int t0 = (int)blockIdx.x * kTargets;
+    split_item<true, TW>(E, {0, t0, min(kTargets, E.N - t0), 0, E.N, 0});
 }
 
 // --------------------------------------------------------- launch wrapper
 
-hipError_t launch_eval_direct(const EnsDesc &h_desc, hipStream_t s) {
+// Two targets per wave read each staged source once for both, but halve the
+// blocks: taken when the fullest CU then has no more targets (FP64 calls, one
+// against two targets per wave: 1,000 points 10.4 and 12.8 us, 2,560 points
+// 27.6 and 30.9, 3,200 points 40.0 and 36.9, 5,003 points 74.4 and 74.8, 6,144
+// points 105 and 93; four never won by more than 1 us; MI355X).
+hipError_t launch_eval_direct(const EnsDesc &h_desc, int n_cu, hipStream_t s) {
     if (h_desc.N == 0) return hipSuccess;
-    const dim3 g((h_desc.N + kSplitTargetsPerBlock - 1) / kSplitTargetsPerBlock), b(kBlock);
-    hipLaunchKernelGGL(k_eval_direct, g, b, 0, s, h_desc);
+    const int w = kBlock / 64;
+    const auto blocks = [&](int tw) { return (h_desc.N + tw * w - 1) / (tw * w); };
+    const auto per_cu = [&](int tw) { return tw * ((blocks(tw) + n_cu - 1) / n_cu); };
+    if (per_cu(2) <= per_cu(1)) hipLaunchKernelGGL(k_eval_direct<2>, dim3(blocks(2)), dim3(kBlock), 0, s, h_desc);
+    else hipLaunchKernelGGL(k_eval_direct<1>, dim3(blocks(1)), dim3(kBlock), 0, s, h_desc);
     return hipGetLastError();
 }
 

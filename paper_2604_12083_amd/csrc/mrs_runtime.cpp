@@ -771,11 +771,28 @@ static EnsDesc eval_desc(int64_t n, const double *dX, const double *df, const do
     return d;
 }
 
-// Small evaluations (wave-split configurations) run in one launch without
-// scratch, unless an output lies over an input (other blocks may still read
-// it then; the general path reads every input before it writes).
-static bool eval_is_direct(const EnsDesc &d, const PairCfg &c) {
-    if (c.mode != PAIR_SPLIT || d.N > kDirectMaxPoints) return false;
+// Small evaluations run in one launch without scratch (k_eval_direct), unless
+// an output lies over an input (other blocks may still read it then; the
+// general path reads every input before it writes).  Wave-split configurations
+// do so up to kDirectMaxPoints; a stored configuration with another
+// decomposition than the automatic one is followed otherwise.  For that one the
+// limit is a number of points per CU, in FP32C the smaller one, since beyond the near pairs the tiled kernel takes less than
+// half the time per pair there (calls on one stream, general path against one
+// launch: 1,100 points 28.1 and 13.8 us FP64, 35.1 and 13.7 FP32C; 2,048 points
+// 31.9 and 19.4, 36.7 and 19.3; 3,200 points 45.4 and 36.9, 45.3 and 36.8; 4,096
+// points 57.9 and 46.8, 45.8 and 46.5; 5,003 points 97.4 and 74.4, 67 and 74;
+// 6,144 points 115.7 and 93; 6,400 points 116 and 118; MI355X).
+constexpr int kDirectMaxPoints = 2048, kDirectPerCuF64 = 24, kDirectPerCuF32 = 14;
+
+// Same decomposition (the schedule changes no result).
+static bool same_items(const PairCfg &a, const PairCfg &b) {
+    return a.mode == b.mode && a.tpl == b.tpl && a.K == b.K && a.chunk == b.chunk;
+}
+
+static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p, const PairCfg &c) {
+    const int64_t limit = (int64_t)(p == MRS_FP64 ? kDirectPerCuF64 : kDirectPerCuF32) * ctx->n_cu;
+    const bool split = c.mode == PAIR_SPLIT && d.N <= kDirectMaxPoints;
+    if (!split && (d.N > limit || !same_items(c, choose_cfg_for(nullptr, d.N, p, ctx->n_cu)))) return false;
     const size_t b = (size_t)d.N * 3 * sizeof(double);
     for (const void *o : {d.U, d.W})
         for (const void *i : {d.Xin_aos, d.fext, d.next})
@@ -864,11 +881,11 @@ static hipError_t eval_end(mrs_context *ctx, hipStream_t s) {
 
 // A small evaluation keeps its place in the order of the context's
 // evaluations, though it shares no scratch with them.
-static mrs_status eval_direct(mrs_context *ctx, EnsDesc args, int p, const PairCfg &c, hipStream_t s) {
-    set_records(args, nullptr, args.N, rec_form(p, c), false);
+static mrs_status eval_direct(mrs_context *ctx, EnsDesc args, int p, hipStream_t s) {
+    set_records(args, nullptr, args.N, p == MRS_FP64 ? REC_F64 : REC_WIDE, false);
     HIPCHK(ctx, eval_begin(ctx, s));
     HIPCHK(ctx, timed(ctx, p == MRS_FP32C ? "pairs_split_f32c" : "pairs_split_f64", s,
-                      [&] { return launch_eval_direct(args, s); }));
+                      [&] { return launch_eval_direct(args, ctx->n_cu, s); }));
     HIPCHK(ctx, eval_end(ctx, s));
     return MRS_OK;
 }
@@ -886,7 +903,7 @@ mrs_status mrs_eval_device(mrs_context *ctx, int64_t n, const double *dX, const 
     PairCfg c = choose_cfg(ctx, n, p);
     c.wide = wide_records(c, n, p, false);
     const EnsDesc args = eval_desc(n, dX, df, dt, eps, mu, p, dU, dW);
-    if (eval_is_direct(args, c)) return eval_direct(ctx, args, p, c, s);
+    if (eval_is_direct(ctx, args, p, c)) return eval_direct(ctx, args, p, s);
     // the scratch below is shared by every evaluation of the context: this
     // one waits on its stream for the previous one (any stream) to finish,
     // and growing a buffer (which frees the old one) first waits on the host
@@ -937,7 +954,7 @@ mrs_status mrs_eval_device_noalloc(mrs_context *ctx, int64_t n, const double *dX
     PairCfg c = choose_cfg(ctx, n, p);
     c.wide = wide_records(c, n, p, false);
     const EnsDesc args = eval_desc(n, dX, df, dt, eps, mu, p, dU, dW);
-    if (eval_is_direct(args, c)) return eval_direct(ctx, args, p, c, s);
+    if (eval_is_direct(ctx, args, p, c)) return eval_direct(ctx, args, p, s);
     if (c.K > k_room) {
         PairCfg t;
         t.mode = c.mode;

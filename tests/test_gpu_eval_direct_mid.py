@@ -1,0 +1,56 @@
+"""One-shot evaluations in one launch up to 3,584 (FP32C) and 6,144 (FP64)
+points of 256 CUs, with one and two targets per wave: both sides of each limit,
+last blocks of one target, a repeat on other streams and the allocation-free
+entry, against the FP64 oracle.
+
+Tolerance.  A target's velocity is a sum of N < 7,000 terms of total size S_i; N
++ 110 roundings per side stay below 2^-39.9 S_i, both sides together 2^-38 S_i.
+FP32C adds the rounding of the loads, 2^-24 S_i (doubled here); above its limit
+the FP32 pair arithmetic, 2^-17 S_i."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import dev, say
+from tests.test_gpu_quarters import _cloud
+from tests.test_gpu_wide_records import _term_sizes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mrs():
+    import paper_2604_12083_amd as m
+
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(mrs):
+    c = mrs.mrs_context_create(0)
+    yield c
+    mrs.mrs_context_destroy(c)
+
+
+@pytest.mark.parametrize("n", [1025, 2041, 2049, 2561, 3584, 3585, 6144, 6145])
+def test_one_launch_against_the_oracle(mrs, ctx, n):
+    import torch
+
+    X, f, t = _cloud(n)
+    eps = 0.05
+    Uo, Wo = oracle.mrs_eval(X, f, t, eps, 0.7)
+    SU, SW = (s / 0.7 for s in _term_sizes(X, f, t, eps))
+    dX, df, dn = dev(X), dev(f), dev(t)
+    for prec, tol in ((mrs.MRS_FP64, 2.0 ** -38), (mrs.MRS_FP32C, 2.0 ** -23 if n <= 3584 else 2.0 ** -17)):
+        got = []
+        for entry in (mrs.mrs_eval_device, mrs.mrs_eval_device, mrs.mrs_eval_device_noalloc):
+            say("direct", n, prec, entry.__name__)
+            s = torch.cuda.Stream()
+            U, W = torch.empty_like(dX), torch.empty_like(dX)
+            torch.cuda.synchronize()
+            entry(ctx, n, dX, df, dn, eps, 0.7, prec, U, W, s)
+            torch.cuda.synchronize()
+            got.append((U.cpu().numpy(), W.cpu().numpy()))
+        U, W = got[0]
+        assert (np.linalg.norm(U - Uo, axis=1) <= tol * SU).all() and (np.linalg.norm(W - Wo, axis=1) <= tol * SW).all()
+        assert all(np.array_equal(U, a) and np.array_equal(W, b) for a, b in got[1:])
