@@ -174,7 +174,7 @@ inline void set_records(EnsDesc &d, void *rec, int64_t n, RecForm form, bool des
 }
 
 // Launch wrappers (mrs_pairs.hip, mrs_kernels.hip).  All return the launch's hipError_t.
-hipError_t launch_pack_aos(const EnsDesc *d_desc, const EnsDesc &h_desc, hipStream_t s);
+hipError_t launch_pack_aos(const EnsDesc &h_desc, const void *src, void *dst, size_t bytes, hipStream_t s);
 // elastic < 0: every ensemble uses its own EnsDesc::elastic.  The waveform
 // time of the launch is clock + c dt, c the node of RK stage `stage` of
 // `scheme` (0 for stage 0); dt = NaN: every ensemble uses its own dt.

@@ -400,25 +400,43 @@ static hipError_t graph_steps(mrs_context *ctx, Plan &P, int integ, double dt, i
     return hipSuccess;
 }
 
-hipError_t upload(mrs_context *ctx, void *dst, const void *src, size_t bytes, hipStream_t s) {
+// The next staging slot, free and of at least `bytes`.
+static hipError_t stage_slot(mrs_context *ctx, size_t bytes, mrs_context::Stage **out) {
+    mrs_context::Stage &S = ctx->stage[ctx->stage_next];
     hipError_t e;
-    if (ctx->stage_pending) {
-        if ((e = hipEventSynchronize(ctx->stage_event)) != hipSuccess) return e;
-        ctx->stage_pending = false;
+    if (S.pending) {
+        if ((e = hipEventSynchronize(S.event)) != hipSuccess) return e;
+        S.pending = false;
     }
-    if (bytes > ctx->stage_bytes) {
-        if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
-        ctx->stage_host = nullptr;
-        ctx->stage_bytes = 0;
-        size_t nb = std::max<size_t>(bytes, 1 << 16);
-        if ((e = hipHostMalloc(&ctx->stage_host, nb, hipHostMallocDefault)) != hipSuccess) return e;
-        ctx->stage_bytes = nb;
+    if (!S.event && (e = hipEventCreateWithFlags(&S.event, hipEventDisableTiming)) != hipSuccess) return e;
+    if (bytes > S.bytes) {
+        if (S.host) (void)hipHostFree(S.host);
+        S.host = nullptr;
+        S.bytes = 0;
+        const size_t nb = std::max<size_t>(bytes, 1 << 16);
+        if ((e = hipHostMalloc(&S.host, nb, hipHostMallocMapped)) != hipSuccess ||
+            (e = hipHostGetDevicePointer(&S.dev, S.host, 0)) != hipSuccess)
+            return e;
+        S.bytes = nb;
     }
-    std::memcpy(ctx->stage_host, src, bytes);
-    if ((e = hipMemcpyAsync(dst, ctx->stage_host, bytes, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
-    if ((e = hipEventRecord(ctx->stage_event, s)) != hipSuccess) return e;
-    ctx->stage_pending = true;
+    ctx->stage_next ^= 1;
+    *out = &S;
     return hipSuccess;
+}
+
+static hipError_t stage_read(mrs_context::Stage &S, hipStream_t s) {
+    const hipError_t e = hipEventRecord(S.event, s);
+    S.pending = e == hipSuccess;
+    return e;
+}
+
+hipError_t upload(mrs_context *ctx, void *dst, const void *src, size_t bytes, hipStream_t s) {
+    mrs_context::Stage *S;
+    hipError_t e = stage_slot(ctx, bytes, &S);
+    if (e != hipSuccess) return e;
+    std::memcpy(S->host, src, bytes);
+    if ((e = hipMemcpyAsync(dst, S->host, bytes, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
+    return stage_read(*S, s);
 }
 
 size_t ensemble_bytes(int64_t N, int n_fil, bool has_ext, int K64, int K32) {
@@ -643,7 +661,6 @@ mrs_status mrs_context_create(int device, mrs_context **out) {
     if (ctx->arch.empty()) ctx->arch = "unknown";
     void *flag = nullptr;
     if (hipStreamCreateWithFlags(&ctx->own_stream, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->stage_event, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->eval_done, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->rod_done, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->in_event, hipEventDisableTiming) != hipSuccess ||
@@ -653,7 +670,6 @@ mrs_status mrs_context_create(int device, mrs_context **out) {
         if (ctx->eval_done) (void)hipEventDestroy(ctx->eval_done);
         if (ctx->rod_done) (void)hipEventDestroy(ctx->rod_done);
         if (ctx->in_event) (void)hipEventDestroy(ctx->in_event);
-        if (ctx->stage_event) (void)hipEventDestroy(ctx->stage_event);
         if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);
         delete ctx;
         return MRS_EDEVICE;
@@ -680,12 +696,15 @@ void mrs_context_destroy(mrs_context *ctx) {
         (void)hipEventDestroy(r.stop);
     }
     for (auto ev : ctx->event_pool) (void)hipEventDestroy(ev);
-    if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
+    for (auto &S : ctx->stage) {
+        if (S.pending) (void)hipEventSynchronize(S.event);
+        if (S.host) (void)hipHostFree(S.host);
+        if (S.event) (void)hipEventDestroy(S.event);
+    }
     for (int i = 0; i < 2; i++) {
         if (ctx->row_host[i]) (void)hipHostFree(ctx->row_host[i]);
         if (ctx->row_event[i]) (void)hipEventDestroy(ctx->row_event[i]);
     }
-    if (ctx->stage_event) (void)hipEventDestroy(ctx->stage_event);
     if (ctx->eval_done) (void)hipEventDestroy(ctx->eval_done);
     if (ctx->rod_done) (void)hipEventDestroy(ctx->rod_done);
     if (ctx->in_event) (void)hipEventDestroy(ctx->in_event);
@@ -778,11 +797,11 @@ static EnsDesc eval_desc(int64_t n, const double *dX, const double *df, const do
 // decomposition than the automatic one is followed otherwise.  For that one the
 // limit is a number of points per CU, in FP32C the smaller one, since beyond the near pairs the tiled kernel takes less than
 // half the time per pair there (calls on one stream, general path against one
-// launch: 1,100 points 28.1 and 13.8 us FP64, 35.1 and 13.7 FP32C; 2,048 points
-// 31.9 and 19.4, 36.7 and 19.3; 3,200 points 45.4 and 36.9, 45.3 and 36.8; 4,096
-// points 57.9 and 46.8, 45.8 and 46.5; 5,003 points 97.4 and 74.4, 67 and 74;
-// 6,144 points 115.7 and 93; 6,400 points 116 and 118; MI355X).
-constexpr int kDirectMaxPoints = 2048, kDirectPerCuF64 = 24, kDirectPerCuF32 = 14;
+// launch: 1,025 points 21.4 and 13.9 us FP64, 30.5 and 14.3 FP32C; 2,048 points
+// 26.6 and 19.3, 32.0 and 21.6; 3,072 points 39.6 and 33.1, 40.8 and 34.5; 3,584
+// points FP32C 41.0 and 41.7; FP64 4,096 points 54.3 and 47.2, 5,120 points 84.1
+// and 76.9, 6,144 points 101.8 and 95.1, 6,400 points even; MI355X).
+constexpr int kDirectMaxPoints = 2048, kDirectPerCuF64 = 24, kDirectPerCuF32 = 12;
 
 // Same decomposition (the schedule changes no result).
 static bool same_items(const PairCfg &a, const PairCfg &b) {
@@ -826,20 +845,26 @@ static void eval_layout(EvalLayout &L, int64_t n, const EnsDesc &args, int p, co
     L.o_pts = put(L.P.pts.data(), L.P.pts.size() * sizeof(PointItem));
     const uint32_t zero[kQueueWords] = {};
     L.o_queue = put(zero, sizeof zero);  // work-queue counters start at zero
+    L.blob.resize((L.blob.size() + 15) & ~size_t(15));  // copied 16 bytes at a time
 }
 
-// Queue the kernels of an evaluation whose blob is on the device at `base`.
-static hipError_t eval_launch(mrs_context *ctx, const EvalLayout &L, int p, const char *base, hipStream_t s) {
+// Queue the kernels of an evaluation whose blob is on the device at `base`, or
+// comes there from `staged` with the first of them.
+static hipError_t eval_launch(mrs_context *ctx, const EvalLayout &L, int p, char *base, mrs_context::Stage *staged,
+                              hipStream_t s) {
     const Plan &P = L.P;
     const EnsDesc *dd = reinterpret_cast<const EnsDesc *>(base + L.o_desc);
-    hipError_t e = timed(ctx, "pack_aos", s, [&] { return launch_pack_aos(dd, L.d, s); });
+    hipError_t e = timed(ctx, "pack_aos", s, [&] {
+        return launch_pack_aos(L.d, staged ? staged->dev : nullptr, base, staged ? L.blob.size() : 0, s);
+    });
+    if (e == hipSuccess && staged) e = stage_read(*staged, s);
     if (e == hipSuccess)
         e = pair_launches(ctx, p, P.sched, dd, reinterpret_cast<const PairItem *>(base + L.o_split),
                           (int)P.split.size(), reinterpret_cast<const PairItem *>(base + L.o_t1), (int)P.tile1.size(),
                           reinterpret_cast<const PairItem *>(base + L.o_t2), (int)P.tile2.size(),
                           reinterpret_cast<const PairItem *>(base + L.o_tq), (int)P.quad.size(),
                           reinterpret_cast<const PairItem *>(base + L.o_tr), (int)P.quart.size(),
-                          reinterpret_cast<uint32_t *>(const_cast<char *>(base) + L.o_queue), s);
+                          reinterpret_cast<uint32_t *>(base + L.o_queue), s);
     if (e == hipSuccess)
         e = timed(ctx, "reduce_write", s, [&] {
             return launch_reduce(EPI_WRITE, 0, 0, 0.0, dd, reinterpret_cast<const PointItem *>(base + L.o_pts),
@@ -923,8 +948,10 @@ mrs_status mrs_eval_device(mrs_context *ctx, int64_t n, const double *dX, const 
     eval_layout(L, n, args, p, c, sc);
     if (ctx->eval_pending && L.blob.size() > ctx->eval_items.bytes) HIPCHK(ctx, hipEventSynchronize(ctx->eval_done));
     HIPCHK(ctx, ctx->eval_items.reserve(L.blob.size()));
-    HIPCHK(ctx, upload(ctx, ctx->eval_items.p, L.blob.data(), L.blob.size(), s));
-    HIPCHK(ctx, eval_launch(ctx, L, p, ctx->eval_items.as<char>(), s));
+    mrs_context::Stage *staged;
+    HIPCHK(ctx, stage_slot(ctx, L.blob.size(), &staged));
+    std::memcpy(staged->host, L.blob.data(), L.blob.size());
+    HIPCHK(ctx, eval_launch(ctx, L, p, ctx->eval_items.as<char>(), staged, s));
     HIPCHK(ctx, eval_end(ctx, s));
     return MRS_OK;
 }
@@ -976,7 +1003,7 @@ mrs_status mrs_eval_device_noalloc(mrs_context *ctx, int64_t n, const double *dX
     HIPCHK(ctx, eval_begin(ctx, s));
     // pageable source: the call returns once the list has been staged
     HIPCHK(ctx, hipMemcpyAsync(base, L.blob.data(), L.blob.size(), hipMemcpyHostToDevice, s));
-    HIPCHK(ctx, eval_launch(ctx, L, p, base, s));
+    HIPCHK(ctx, eval_launch(ctx, L, p, base, nullptr, s));
     HIPCHK(ctx, eval_end(ctx, s));
     return MRS_OK;
 }

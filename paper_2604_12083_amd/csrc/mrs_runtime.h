@@ -137,11 +137,16 @@ struct mrs_context {
     // of filament offsets too long for the kernel's arguments)
     hipEvent_t rod_done = nullptr;
     bool rod_pending = false;
-    // pinned staging for small uploads, reused after its event completes
-    void *stage_host = nullptr;
-    size_t stage_bytes = 0;
-    hipEvent_t stage_event = nullptr;
-    bool stage_pending = false;
+    // pinned, device-mapped staging for small uploads: two slots in turn, each
+    // reused after its event completes, so that the host fills one while the
+    // device reads the other
+    struct Stage {
+        void *host = nullptr, *dev = nullptr;
+        size_t bytes = 0;
+        hipEvent_t event = nullptr;
+        bool pending = false;
+    } stage[2];
+    int stage_next = 0;
     // pinned, device-mapped slots through which ensemble state and loads go in
     // and out (rows_in, rows_out): grow-only up to kRowSlotRows rows of 18
     // doubles each; a slot is reused once its event has completed

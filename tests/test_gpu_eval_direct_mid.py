@@ -1,4 +1,4 @@
-"""One-shot evaluations in one launch up to 3,584 (FP32C) and 6,144 (FP64)
+"""One-shot evaluations in one launch up to 3,072 (FP32C) and 6,144 (FP64)
 points of 256 CUs, with one and two targets per wave: both sides of each limit,
 last blocks of one target, a repeat on other streams and the allocation-free
 entry, against the FP64 oracle.
@@ -32,7 +32,7 @@ def ctx(mrs):
     mrs.mrs_context_destroy(c)
 
 
-@pytest.mark.parametrize("n", [1025, 2041, 2049, 2561, 3584, 3585, 6144, 6145])
+@pytest.mark.parametrize("n", [1025, 2041, 2049, 2561, 3072, 3073, 6144, 6145])
 def test_one_launch_against_the_oracle(mrs, ctx, n):
     import torch
 
@@ -41,7 +41,7 @@ def test_one_launch_against_the_oracle(mrs, ctx, n):
     Uo, Wo = oracle.mrs_eval(X, f, t, eps, 0.7)
     SU, SW = (s / 0.7 for s in _term_sizes(X, f, t, eps))
     dX, df, dn = dev(X), dev(f), dev(t)
-    for prec, tol in ((mrs.MRS_FP64, 2.0 ** -38), (mrs.MRS_FP32C, 2.0 ** -23 if n <= 3584 else 2.0 ** -17)):
+    for prec, tol in ((mrs.MRS_FP64, 2.0 ** -38), (mrs.MRS_FP32C, 2.0 ** -23 if n <= 3072 else 2.0 ** -17)):
         got = []
         for entry in (mrs.mrs_eval_device, mrs.mrs_eval_device, mrs.mrs_eval_device_noalloc):
             say("direct", n, prec, entry.__name__)
