@@ -188,6 +188,14 @@ __device__ __forceinline__ void preferred_strain(const EnsDesc &E, double s, dou
     if (E.has_wave) om[1] += -E.wave[1] * E.wave[1] * E.wave[0] * sin(E.wave[1] * s + E.wave[2] * t);
 }
 
+// Waveform time of a stage: step start (the clock) + c_stage dt; 0 without a waveform.
+__device__ __forceinline__ double wave_time(const EnsDesc &E, double clock, int scheme, int stage, double dt) {
+    FP_STRICT;
+    if (!E.has_wave) return 0.0;
+    if (dt != dt) dt = E.dt;
+    return clock + (stage > 0 ? kRkNextNode[scheme][stage - 1] : 0.0) * dt;
+}
+
 // Component c of the w-vector of point p: SoA arrays of N points (resident
 // ensembles) or the caller's row-major arrays (AOS).
 template <bool AOS>
@@ -195,18 +203,19 @@ __device__ __forceinline__ size_t at(int N, int w, int c, int p) {
     return AOS ? (size_t)w * p + c : (size_t)c * N + p;
 }
 
-// F and N of the segment between nodes ka and kb = ka + 1 at arclength s_mid
-// (its midpoint) and time t.
+// F and N of the segment between two neighbouring nodes at arclength s_mid (its
+// midpoint) and time t: nodes xa and xa + 1 of the positions X (of N points), da
+// and da + 1 of the frames D (of ND points).
 template <bool AOS>
-__device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__restrict__ X,
-                                            const double *__restrict__ D, int N, int ka, int kb,
-                                            double s_mid, double t, double *F, double *Nv, double *dX) {
+__device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__restrict__ X, int N, int xa,
+                                            const double *__restrict__ D, int ND, int da, double s_mid, double t,
+                                            double *F, double *Nv, double *dX) {
     FP_STRICT;
     double Da[9], Db[9];
 #pragma unroll
     for (int k = 0; k < 9; k++) {
-        Da[k] = D[at<AOS>(N, 9, k, ka)];
-        Db[k] = D[at<AOS>(N, 9, k, kb)];
+        Da[k] = D[at<AOS>(ND, 9, k, da)];
+        Db[k] = D[at<AOS>(ND, 9, k, da + 1)];
     }
     // A = sum_j D^j_b (D^j_a)^T maps frame a onto frame b.
     double A[9];
@@ -221,7 +230,7 @@ __device__ __forceinline__ void rod_segment(const EnsDesc &E, const double *__re
 #pragma unroll
     for (int i = 0; i < 3; i++) quat_rotate(h, Da + 3 * i, Dh + 3 * i);
 #pragma unroll
-    for (int c = 0; c < 3; c++) dX[c] = X[at<AOS>(N, 3, c, kb)] - X[at<AOS>(N, 3, c, ka)];
+    for (int c = 0; c < 3; c++) dX[c] = X[at<AOS>(N, 3, c, xa + 1)] - X[at<AOS>(N, 3, c, xa)];
     const double ids = 1.0 / E.ds;
     F[0] = F[1] = F[2] = 0.0;
     Nv[0] = Nv[1] = Nv[2] = 0.0;
@@ -283,12 +292,7 @@ __device__ __forceinline__ void rod_filament(int stage_state, int elastic, int s
     const double *__restrict__ D = stage_state ? E.Ds : E.D;
     const int tid = threadIdx.x;
     if (elastic < 0) elastic = E.elastic;
-    // waveform time of this stage: step start + c_stage dt
-    double t = 0.0;
-    if (E.has_wave) {
-        if (dt != dt) dt = E.dt;
-        t = *E.clock + (stage > 0 ? kRkNextNode[scheme][stage - 1] : 0.0) * dt;
-    }
+    const double t = wave_time(E, E.has_wave ? *E.clock : 0.0, scheme, stage, dt);
     for (int c0 = 0; c0 < M; c0 += BLOCK - 1) {
         // this thread's node: its external loads and position, loaded before
         // the segment work so that the two memory latencies overlap
@@ -312,7 +316,7 @@ __device__ __forceinline__ void rod_filament(int stage_state, int elastic, int s
                 const int s = c0 - 1 + tid;
                 double F[3] = {0.0, 0.0, 0.0}, Nv[3] = {0.0, 0.0, 0.0}, dX[3] = {0.0, 0.0, 0.0};
                 if (s >= 0 && s <= M - 2)
-                    rod_segment<AOS>(E, X, D, N, k0 + s, k0 + s + 1, (s + 0.5) * E.ds, t, F, Nv, dX);
+                    rod_segment<AOS>(E, X, N, k0 + s, D, N, k0 + s, (s + 0.5) * E.ds, t, F, Nv, dX);
 #pragma unroll
                 for (int c = 0; c < 3; c++) {
                     sF[c][tid] = F[c];

@@ -315,8 +315,11 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_forces(int stage_state, co
 // most kLjRodPoints points in kLjRodBlocks source blocks whose pair kernel
 // reads no LJ mask: every block takes all positions into LDS and makes the
 // boxes itself, so k_lj_boxes, k_lj_forces and k_rod_forces, each a chain of
-// memory latencies on a nearly idle chip, become one: 25 swimmers of 51 points
-// take 9.9 us instead of 4.2 + 12.8 + 5.5 (MI355X).
+// memory latencies on a nearly idle chip, become one.  Rods of at most kRodNodes
+// nodes are summed out of LDS while other waves make the boxes; longer ones by
+// rod_filament.  25 swimmers of 51 points take 7.9 us instead of 4.2 + 12.8 +
+// 5.5 (9.6 with rod_filament after the repulsion: its loads of frames and loads
+// alone took 1.9 us; MI355X).
 __global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int elastic, int scheme, int stage,
                                                            double dt, const EnsDesc *__restrict__ desc,
                                                            const RodItem *__restrict__ items) {
@@ -324,7 +327,10 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int 
     __shared__ double sBox[kLjRodBlocks][6];
     __shared__ int sBlk[kLjRodBlocks][3];
     __shared__ double sPart[kLjWaves][3][64];
-    constexpr int kThreads = 64 * kLjWaves, kRodThreads = 128, kLoads = 8;
+    constexpr int kThreads = 64 * kLjWaves, kLoads = 8;
+    constexpr int kRodThreads = 128, kRodNodes = 128, kSegWaves = kRodNodes / 64;
+    __shared__ double sD[9][kRodNodes];
+    __shared__ double sF[3][kRodNodes + 1], sN[3][kRodNodes + 1], sdX[3][kRodNodes + 1];
     static_assert(kLjRodBlocks <= 64, "one source block per lane");
     const RodItem it = items[blockIdx.x];
     const EnsDesc E = global_desc(desc[it.ens]);
@@ -339,20 +345,22 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int 
     }
     const int k0 = E.off[it.fil], k1 = E.off[it.fil + 1];
     // every load the block starts from is in flight before the first is waited
-    // for (each is an L2 miss: the last kernel wrote it on other XCDs); what
-    // rod_filament reads first goes to the L1
-    double pre[16];
-    if (w < kRodThreads / 64) {
+    // for (each is an L2 miss: the last kernel wrote it on other XCDs)
+    const int M = k1 - k0;
+    const bool whole = M <= kRodNodes;  // block-uniform: the rod in one pass, out of LDS
+    const bool node = whole && tid < M;
+    double Dp[9], ext[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, clock = 0.0;
+    if (w < (kRodNodes + 63) / 64) {
         const double *__restrict__ D = stage_state ? E.Ds : E.D;
         const int p = max(min(k0 + tid, k1 - 1), 0);
 #pragma unroll
-        for (int c = 0; c < 9; c++) pre[c] = D[(size_t)c * N + p];
+        for (int c = 0; c < 9; c++) Dp[c] = D[(size_t)c * N + p];
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-            pre[9 + c] = E.fext ? E.fext[(size_t)c * N + p] : 0.0;
-            pre[12 + c] = E.next ? E.next[(size_t)c * N + p] : 0.0;
+            if (E.fext) ext[c] = E.fext[(size_t)c * N + p];
+            if (E.next) ext[3 + c] = E.next[(size_t)c * N + p];
         }
-        pre[15] = *E.clock;
+        if (E.has_wave) clock = *E.clock;
     }
     const int blk = E.lj_blk[min(tid, 3 * nblk - 1)];
     for (int q0 = 0; q0 < 3 * N; q0 += kLoads * kThreads) {
@@ -364,30 +372,49 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int 
             if (q0 + u * kThreads + tid < 3 * N) sX[q0 + u * kThreads + tid] = v[u];
     }
     if (tid < 3 * nblk) sBlk[tid / 3][tid % 3] = blk;
-    if (w < kRodThreads / 64) {
+    if (elastic < 0) elastic = E.elastic;
+    if (node) {
 #pragma unroll
-        for (int c = 0; c < 16; c++) asm volatile("" ::"v"(pre[c]));
+        for (int c = 0; c < 9; c++) sD[c][tid] = Dp[c];
     }
+    if (tid < 9) (tid < 3 ? sF[tid] : (tid < 6 ? sN[tid - 3] : sdX[tid - 6]))[0] = 0.0;
     __syncthreads();
-    // four lanes per box and coordinate
-    for (int q = tid >> 2; q < 3 * nblk; q += kThreads / 4) {
-        const int b = q / 3, c = q - 3 * b, j0 = sBlk[b][0], j1 = sBlk[b][1] - 1;
-        double lo = INFINITY, hi = -INFINITY;
+    // the rod's segments by the first waves (node t: the segment after it, slot
+    // t + 1), the boxes by the others, four lanes per box and coordinate
+    if (w < kSegWaves) {
+        if (elastic && node) {
+            double F[3] = {0.0, 0.0, 0.0}, Nv[3] = {0.0, 0.0, 0.0}, dX[3] = {0.0, 0.0, 0.0};
+            if (tid < M - 1)
+                rod_segment<false>(E, sX, N, k0 + tid, &sD[0][0], kRodNodes, tid, (tid + 0.5) * E.ds,
+                                   wave_time(E, clock, scheme, stage, dt), F, Nv, dX);
 #pragma unroll
-        for (int k = 0; k < kLjBlockPoints; k += 4) {
-            const double v = sX[c * N + min(j0 + k + (tid & 3), j1)];
-            lo = fmin(lo, v);
-            hi = fmax(hi, v);
+            for (int c = 0; c < 3; c++) {
+                sF[c][tid + 1] = F[c];
+                sN[c][tid + 1] = Nv[c];
+                sdX[c][tid + 1] = dX[c];
+            }
         }
+    } else {
+        for (int q = (tid >> 2) - 16 * kSegWaves; q < 3 * nblk; q += 16 * (kLjWaves - kSegWaves)) {
+            const int b = q / 3, c = q - 3 * b, j0 = sBlk[b][0], j1 = sBlk[b][1] - 1;
+            double lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-        for (int off = 1; off <= 2; off <<= 1) {
-            lo = fmin(lo, __shfl_xor(lo, off, 4));
-            hi = fmax(hi, __shfl_xor(hi, off, 4));
+            for (int k = 0; k < kLjBlockPoints; k += 4) {
+                const double v = sX[c * N + min(j0 + k + (tid & 3), j1)];
+                lo = fmin(lo, v);
+                hi = fmax(hi, v);
+            }
+#pragma unroll
+            for (int off = 1; off <= 2; off <<= 1) {
+                lo = fmin(lo, __shfl_xor(lo, off, 4));
+                hi = fmax(hi, __shfl_xor(hi, off, 4));
+            }
+            if ((tid & 3) == 0) { sBox[b][c] = lo; sBox[b][3 + c] = hi; }
         }
-        if ((tid & 3) == 0) { sBox[b][c] = lo; sBox[b][3 + c] = hi; }
     }
     __syncthreads();
     const LjConst L(E);
+    double lj[3] = {0.0, 0.0, 0.0};  // force on node tid (whole)
     for (int p0 = k0; p0 < k1; p0 += 64) {
         const int i = p0 + lane;
         const bool real = i < k1;
@@ -415,14 +442,24 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int 
 #pragma unroll
         for (int c = 0; c < 3; c++) sPart[w][c][lane] = acc[c];
         __syncthreads();
-        if (w == 0 && real) {
-            lj_combine(sPart, lane, acc);
+        if (w == (whole ? (p0 - k0) / 64 : 0) && real) {
+            lj_combine(sPart, lane, lj);
+            if (!whole) {
 #pragma unroll
-            for (int c = 0; c < 3; c++) E.flj[(size_t)c * N + i] = acc[c];
+                for (int c = 0; c < 3; c++) E.flj[(size_t)c * N + i] = lj[c];
+            }
         }
         __syncthreads();
     }
-    rod_filament<kRodThreads, false, kThreads>(stage_state, elastic, scheme, stage, dt, E, k0, k1 - k0);
+    if (!whole) {
+        rod_filament<kRodThreads, false, kThreads>(stage_state, elastic, scheme, stage, dt, E, k0, M);
+    } else if (node) {  // as rod_filament
+        double g[3], m[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) { g[c] = ext[c] + lj[c]; m[c] = ext[3 + c]; }
+        if (elastic) rod_node<kRodNodes + 1>(sF, sN, sdX, tid, g, m);
+        store_rec(E, k0 + tid, sX[k0 + tid], sX[N + k0 + tid], sX[2 * N + k0 + tid], g[0], g[1], g[2], m[0], m[1], m[2]);
+    }
 }
 
 // ------------------------------------------------------- reduce + epilogue
@@ -588,10 +625,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_steps(int nsteps, int e
             if (elastic) {
                 if (node) {
                     double F[3] = {0.0, 0.0, 0.0}, Nv[3] = {0.0, 0.0, 0.0}, dX[3] = {0.0, 0.0, 0.0};
-                    double t = 0.0;
-                    if (E.has_wave) t = sClock + (SCHEME >= 0 && st > 0 ? kRkNextNode[SCHEME & 1][st - 1] : 0.0) * dt;
-                    if (!last)
-                        rod_segment<false>(E, X, D, N, tid, tid + 1, (seg + 0.5) * E.ds, t, F, Nv, dX);
+                    const double t = wave_time(E, sClock, SCHEME & 1, SCHEME >= 0 ? st : 0, dt);
+                    if (!last) rod_segment<false>(E, X, N, tid, D, N, tid, (seg + 0.5) * E.ds, t, F, Nv, dX);
 #pragma unroll
                     for (int c = 0; c < 3; c++) {
                         sF[c][tid + 1] = F[c];

@@ -74,7 +74,7 @@ def _force_sizes(off, X):
 
 
 @pytest.mark.parametrize("F,M", [(2, 51), (25, 51), (64, 49), (65, 49), (32, 100), (10, 130), (2, 700), (100, 3),
-                                 (40, 90)])
+                                 (40, 90), (24, 128), (20, 129)])
 def test_lj_velocities(mrs, ctx, F, M):
     import torch
 
