@@ -19,9 +19,8 @@ namespace mrs {
 // (1,000 swimmers) and 5% off a 64-point Euler step (4.9 -> 4.65 us, MI355X).
 template <class T>
 __device__ __forceinline__ T *as_global(T *p) {
-    auto q = (__attribute__((address_space(1))) T *)p;
-    asm("" : "+s"(q));  // or the two casts are folded away
-    return (T *)q;
+    // by way of an integer, or the two casts are folded away
+    return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
 }
 
 // The descriptor d with its addresses known to be global.
