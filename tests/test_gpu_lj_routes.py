@@ -110,3 +110,26 @@ def test_lj_velocities(mrs, ctx, F, M):
     assert (np.linalg.norm(U - U1, axis=1) <= 2.0 ** -40 * SU).all()
     assert (np.linalg.norm(W - W1, axis=1) <= 2.0 ** -40 * SW).all()
     mrs.mrs_ensemble_destroy(h)
+
+
+@pytest.mark.parametrize("mode,tpl,sched", [(0, 1, 0), (0, 1, 1), (0, 2, 0), (0, 2, 1), (2, 1, 0), (2, 1, 1)])
+def test_contact_sources_in_every_fp32_form(mrs, mode, tpl, sched):
+    """The FP32 path above 3,200 points: tiles, two targets per lane and the
+    four-wave split, in both schedules."""
+    off, X, D, f, n = _scene(40, 90, 3600)
+    flj = oracle.lj_forces(off, X, (SIG, EN))
+    Uo, Wo = oracle.mrs_eval(X, f + flj, n, EPS, 1.0)
+    SU, SW = _term_sizes(X, f + flj, n, EPS)
+    c = mrs.mrs_context_create(0)
+    try:
+        mrs.mrs_tune_set(c, len(X), mrs.MRS_FP32C, mode, tpl, 0, sched)
+        h = mrs.mrs_ensemble_create(c, off, X, D, f, n, EPS, 1.0, rod_of(mrs, _Rod))
+        mrs.mrs_ensemble_set_swimming(c, h, None, (SIG, EN))
+        say("contact", mode, tpl, sched)
+        mrs.mrs_ensemble_eval(c, h, mrs.MRS_FP32C, False)
+        U, W = mrs.mrs_ensemble_get(c, h)[2:]
+        mrs.mrs_ensemble_destroy(h)
+    finally:
+        mrs.mrs_context_destroy(c)
+    assert (np.linalg.norm(U - Uo, axis=1) <= 2.0 ** -17 * SU).all()
+    assert (np.linalg.norm(W - Wo, axis=1) <= 2.0 ** -17 * SW).all()
