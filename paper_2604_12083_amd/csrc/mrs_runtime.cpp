@@ -808,7 +808,8 @@ static bool same_items(const PairCfg &a, const PairCfg &b) {
     return a.mode == b.mode && a.tpl == b.tpl && a.K == b.K && a.chunk == b.chunk;
 }
 
-static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p, const PairCfg &c) {
+static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p) {
+    const PairCfg c = choose_cfg(ctx, d.N, p);
     const int64_t limit = (int64_t)(p == MRS_FP64 ? kDirectPerCuF64 : kDirectPerCuF32) * ctx->n_cu;
     const bool split = c.mode == PAIR_SPLIT && d.N <= kDirectMaxPoints;
     if (!split && (d.N > limit || !same_items(c, choose_cfg_for(nullptr, d.N, p, ctx->n_cu)))) return false;
@@ -817,6 +818,30 @@ static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p, const Pair
         for (const void *i : {d.Xin_aos, d.fext, d.next})
             if ((const char *)o < (const char *)i + b && (const char *)i < (const char *)o + b) return false;
     return true;
+}
+
+// Configuration of an evaluation that takes the general path.  In place of the
+// automatic tiles, FP32C evaluations up to 20 points per CU split 256-source
+// chunks over a block's four waves: at one to three tiled blocks per CU the
+// fullest CU sets the time (pair + reduction kernels: 3,328 points 32.7 -> 24.7
+// us, 3,968 points 33.1 -> 29.2, 5,120 points 44.7 -> 37.4, 5,632 points 47 -> 42,
+// 6,400 points even; MI355X).  Ensembles keep the tiles: in batches of
+// different sizes the four-wave kernel is one more launch with a tail of its
+// own (12 ensembles of 518 to 9,216 points: 1,038 -> 1,077 us).
+constexpr int kFourWavePerCu = 20;
+
+static PairCfg eval_cfg(mrs_context *ctx, int64_t n, int p) {
+    PairCfg c = choose_cfg(ctx, n, p);
+    if (p == MRS_FP32C && c.mode == PAIR_TILE && n <= (int64_t)kFourWavePerCu * ctx->n_cu &&
+        same_items(c, choose_cfg_for(nullptr, n, p, ctx->n_cu))) {
+        PairCfg four;
+        four.mode = PAIR_QUAD;
+        four.K = (int)((n + kBlock - 1) / kBlock);
+        four.sched = c.sched;
+        c = choose_cfg_for(&four, n, p, ctx->n_cu);
+    }
+    c.wide = wide_records(c, n, p, false);
+    return c;
 }
 
 static void eval_layout(EvalLayout &L, int64_t n, const EnsDesc &args, int p, const PairCfg &c,
@@ -925,10 +950,9 @@ mrs_status mrs_eval_device(mrs_context *ctx, int64_t n, const double *dX, const 
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
     hipStream_t s = pick_stream(ctx, stream);
     const int p = (int)prec;
-    PairCfg c = choose_cfg(ctx, n, p);
-    c.wide = wide_records(c, n, p, false);
     const EnsDesc args = eval_desc(n, dX, df, dt, eps, mu, p, dU, dW);
-    if (eval_is_direct(ctx, args, p, c)) return eval_direct(ctx, args, p, s);
+    if (eval_is_direct(ctx, args, p)) return eval_direct(ctx, args, p, s);
+    PairCfg c = eval_cfg(ctx, n, p);
     // the scratch below is shared by every evaluation of the context: this
     // one waits on its stream for the previous one (any stream) to finish,
     // and growing a buffer (which frees the old one) first waits on the host
@@ -978,10 +1002,9 @@ mrs_status mrs_eval_device_noalloc(mrs_context *ctx, int64_t n, const double *dX
     const size_t part_off = rec_off + ((rec_buffer_bytes(n) + 255) & ~size_t(255));
     const size_t per_chunk = (size_t)n * 6 * sizeof(double);
     const int64_t k_room = (int64_t)((kNoallocBytes - part_off) / per_chunk);
-    PairCfg c = choose_cfg(ctx, n, p);
-    c.wide = wide_records(c, n, p, false);
     const EnsDesc args = eval_desc(n, dX, df, dt, eps, mu, p, dU, dW);
-    if (eval_is_direct(ctx, args, p, c)) return eval_direct(ctx, args, p, s);
+    if (eval_is_direct(ctx, args, p)) return eval_direct(ctx, args, p, s);
+    PairCfg c = eval_cfg(ctx, n, p);
     if (c.K > k_room) {
         PairCfg t;
         t.mode = c.mode;

@@ -32,7 +32,7 @@ def ctx(mrs):
     mrs.mrs_context_destroy(c)
 
 
-@pytest.mark.parametrize("n", [1025, 2041, 2049, 2561, 3072, 3073, 6144, 6145])
+@pytest.mark.parametrize("n", [1025, 2041, 2049, 2561, 3072, 3073, 5120, 5121, 6144, 6145])
 def test_one_launch_against_the_oracle(mrs, ctx, n):
     import torch
 
