@@ -126,10 +126,14 @@ mrs_status mrs_eval_host(mrs_context *ctx, int64_t n, const double *X, const dou
 
 /* Same on caller-owned device arrays (n x 3 each), queued on `stream`.
  * The evaluation scratch (source records, split-K partial sums, work list)
- * belongs to the context: each call makes its stream wait for the end of
- * the previous call's kernels (an event), so calls queued on different
+ * belongs to the context: a call on another stream than the previous one
+ * makes its stream wait for the end of that call's kernels (an event), so
+ * calls queued on different
  * streams without a host synchronisation between them run one after the
- * other on the device and each gives its own result.  The outputs are not
+ * other on the device and each gives its own result.  Small calls (up to 24
+ * points per compute unit in FP64, 12 in FP32C) run in one launch without
+ * scratch when the decomposition in force is the automatic one and no output
+ * overlaps an input; their FP32C pairs are summed in FP64.  The outputs are not
  * checked for finiteness (the call returns before they exist). */
 mrs_status mrs_eval_device(mrs_context *ctx, int64_t n, const double *dX, const double *df,
                            const double *dtorque, double eps, double mu, mrs_precision prec,
@@ -376,8 +380,8 @@ typedef struct {
  * one and two targets per lane with automatic chunking on either schedule
  * and with the chunk counts that give 1 to 64 blocks per compute unit, the
  * four-wave split (FP32C) and, up to 8,192 points, the wave-split mode.
- * The time of a candidate is the device time of one mrs_eval_device call
- * (every kernel of it).  Every candidate runs once; the fastest quarter (at
+ * The time of a candidate is the device time of one evaluation (pack, pair
+ * and reduction kernels, as an ensemble runs them).  Every candidate runs once; the fastest quarter (at
  * least four) and the automatic configuration then run `reps` (1..20)
  * more times each, interleaved, and the medians decide.  The automatic
  * configuration is kept unless another is more than 1% faster, so a tuned

@@ -183,12 +183,14 @@ mrs_status load_table(mrs_context *ctx, const char *path, bool missing_ok) {
 }
 
 // Device time of one mrs_eval_device call: the sum of its kernels' event
-// times (the host work between launches is not counted).
+// times (the host work between launches is not counted).  It runs the kernels
+// of the configuration, as an ensemble would, not those that take their place
+// in one-shot evaluations.
 mrs_status time_eval(mrs_context *ctx, int64_t n, const double *dX, const double *df, const double *dt, double eps,
                      int prec, double *dU, double *dW, double *ms) {
-    ctx->prof_on = true;
+    ctx->prof_on = ctx->tuning = true;
     mrs_status st = mrs_eval_device(ctx, n, dX, df, dt, eps, 1.0, (mrs_precision)prec, dU, dW, ctx->stream);
-    ctx->prof_on = false;
+    ctx->prof_on = ctx->tuning = false;
     if (st != MRS_OK) return st;
     int64_t launches = 0;
     st = mrs_profile_query(ctx, "", &launches, ms);

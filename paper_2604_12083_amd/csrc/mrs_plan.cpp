@@ -132,8 +132,9 @@ PairCfg choose_cfg_for(const PairCfg *tuned, int64_t N, int prec, int n_cu) {
 // every target, lane by lane after the FP32 pass (swimmers, pair kernel alone
 // and in batches of eight: 1,275 points 28.4 -> 13.6 and 49 -> 38 us, 3,060
 // points 58.6 -> 36.7 and 151 -> 147 us; 4,080 points 49 -> 39 but 214 -> 256
-// us).  Without contact forces the FP32C kernel wins in batches (1,152 points:
-// 23 us against 31).
+// us; in quarters since, 8.5 and 32, 27.4 and 164 us at 3,162 points).  Without
+// contact forces the FP32C kernel wins in batches (1,152 points: 22 us against
+// 29).
 constexpr int64_t kWideContactPoints = 3200;
 
 bool wide_records(const PairCfg &c, int64_t N, int prec, bool has_lj) {

@@ -809,6 +809,7 @@ static bool same_items(const PairCfg &a, const PairCfg &b) {
 }
 
 static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p) {
+    if (ctx->tuning) return false;
     const PairCfg c = choose_cfg(ctx, d.N, p);
     const int64_t limit = (int64_t)(p == MRS_FP64 ? kDirectPerCuF64 : kDirectPerCuF32) * ctx->n_cu;
     const bool split = c.mode == PAIR_SPLIT && d.N <= kDirectMaxPoints;
@@ -832,7 +833,7 @@ constexpr int kFourWavePerCu = 20;
 
 static PairCfg eval_cfg(mrs_context *ctx, int64_t n, int p) {
     PairCfg c = choose_cfg(ctx, n, p);
-    if (p == MRS_FP32C && c.mode == PAIR_TILE && n <= (int64_t)kFourWavePerCu * ctx->n_cu &&
+    if (!ctx->tuning && p == MRS_FP32C && c.mode == PAIR_TILE && n <= (int64_t)kFourWavePerCu * ctx->n_cu &&
         same_items(c, choose_cfg_for(nullptr, n, p, ctx->n_cu))) {
         PairCfg four;
         four.mode = PAIR_QUAD;

@@ -161,6 +161,7 @@ struct mrs_context {
     bool in_pending = false;
     // profiling
     bool prof_on = false;
+    bool tuning = false;  // evaluations run the configuration's own kernels (mrs_autotune)
     std::string prof_sel;  // bracket only kernels whose name contains this (empty = all)
     std::vector<mrs::ProfRec> prof;
     std::vector<hipEvent_t> event_pool;
