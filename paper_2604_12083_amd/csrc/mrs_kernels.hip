@@ -536,9 +536,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(int stage, int scheme
 // by the Runge-Kutta scheme of that number.
 //
 // Such a step is a chain of latencies, and three launches of 3 to 4 us each
-// against 1.8 us of pair arithmetic on one CU: 64 FP64 points take 4.9 instead
-// of 10.6 us per Euler step, 256 such ensembles 6.9 instead of 27 us (MI355X).
-// At 128 points one CU has four times the pairs, a step takes 10.6 instead of
+// against 1.8 us of pair arithmetic on one CU: 64 FP64 points take 4.45 instead
+// of 10.6 us per Euler step, 256 such ensembles 6.4 instead of 27 us (MI355X; of
+// 10,450 cycles the pairs take 5,300, rod segments and nodes 2,900, the sums and
+// the update 2,150).
+// At 128 points one CU has four times the pairs, a step took 10.6 instead of
 // 11.2 us and a call of one step 25 instead of 23, so those go by stages.
 //
 // Every operation and every sum is that of k_rod_forces, k_pairs_split and
