@@ -495,6 +495,14 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 5 : 3) void k_pairs_tile_f32(const
 // at 3,000 to 51,200 points).
 constexpr float kSplitGapRatio2F64 = 16.0f;
 
+// Position x relative to a block's centre c (in units of eps).  One rounding, by
+// a fused operation that is asked for and not left to the compiler: sources
+// (w) and targets (u) have to be taken from the same unrounded centre, or every
+// pair of the block gets the rounding of c eps, up to half an ulp of the
+// coordinate, in n x r and f x r (blocks of 0.12 across, 40 eps apart, eps 0.02, at
+// 10^4 from the origin: errors of 2e-13 instead of 2e-16 of the terms).
+__device__ __forceinline__ double from_centre(double x, float c, double eps) { return fma(-(double)c, eps, x); }
+
 // Sources of one staged round of the FP64 kernel: x, y | z, fx | fy, fz |
 // nx, ny | nz, m | k with m = w x n, k = w x f.
 template <int SLOTS>
@@ -506,8 +514,8 @@ struct SrcStageF64 {
         const double2 *src = reinterpret_cast<const double2 *>(E.rec) + (size_t)i * 5;
         const double2 w0 = src[0], w1 = src[1], w2 = src[2], w3 = src[3], w4 = src[4];
         const desc_float *bd = desc_at(E.blk, __builtin_amdgcn_readfirstlane(i / kDescPoints));
-        const double wx = w0.x - (double)bd[6] * E.rec_eps, wy = w0.y - (double)bd[7] * E.rec_eps,
-                     wz = w1.x - (double)bd[8] * E.rec_eps;
+        const double wx = from_centre(w0.x, bd[6], E.rec_eps), wy = from_centre(w0.y, bd[7], E.rec_eps),
+                     wz = from_centre(w1.x, bd[8], E.rec_eps);
         const double fx = w1.y, fy = w2.x, fz = w2.y, nx = w3.x, ny = w3.y, nz = w4.x;
         a[j] = w0; b[j] = w1; c[j] = w2; d[j] = w3;
         e[j] = make_double2(nz, fma(wy, nz, -(wz * ny)));
@@ -527,8 +535,8 @@ struct SrcStageF64 {
 // its 1.6 rounds of blocks weighs more).
 template <int T, class STAGE>
 __device__ __forceinline__ void far_block_f64(const STAGE &S, int sb, int se, const double (&tx)[T],
-                                              const double (&ty)[T], const double (&tz)[T], double cx, double cy,
-                                              double cz, double e2, double (&acc)[T][6]) {
+                                              const double (&ty)[T], const double (&tz)[T], const float *ctr,
+                                              double eps, double e2, double (&acc)[T][6]) {
     const double c15e2 = 1.5 * e2, c375e2 = 3.75 * e2;
     double sn[T][3], sf[T][3], su[T][3];
 #pragma unroll
@@ -571,7 +579,8 @@ __device__ __forceinline__ void far_block_f64(const STAGE &S, int sb, int se, co
     }
 #pragma unroll
     for (int t = 0; t < T; t++) {
-        const double ux = tx[t] - cx, uy = ty[t] - cy, uz = tz[t] - cz;
+        const double ux = from_centre(tx[t], ctr[0], eps), uy = from_centre(ty[t], ctr[1], eps),
+                     uz = from_centre(tz[t], ctr[2], eps);
         acc[t][0] += fma(sn[t][1], uz, -(sn[t][2] * uy));
         acc[t][1] += fma(sn[t][2], ux, -(sn[t][0] * uz));
         acc[t][2] += fma(sn[t][0], uy, -(sn[t][1] * ux));
@@ -646,8 +655,8 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 4 : 3) void k_pairs_tile_f64(const
                 gap2 = fminf(gap2, box_gap2(lo, hi, slo, shi));
             }
             if (gap2 > kFarBoxGap2 && gap2 > kSplitGapRatio2F64 * d[9]) {  // wave-uniform
-                far_block_f64<T>(S, s0, se, tx, ty, tz, (double)d[6] * eps, (double)d[7] * eps, (double)d[8] * eps, e2,
-                                 acc);
+                const float ctr[3] = {d[6], d[7], d[8]};
+                far_block_f64<T>(S, s0, se, tx, ty, tz, ctr, eps, e2, acc);
             } else {
 #pragma unroll 2
                 for (int jj = s0; jj < se; jj++) {
