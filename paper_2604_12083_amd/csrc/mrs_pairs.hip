@@ -779,8 +779,8 @@ __global__ __launch_bounds__(kBlock) void k_pairs_split(const EnsDesc *__restric
 }
 
 // One-shot evaluation in one launch, with no scratch and no work list: a
-// 64-point FP64 call takes 12 us on one stream, 23 us on streams in turn (each
-// waits for the one before) instead of 36 with pack, pair and reduction
+// 64-point FP64 call takes 8 us on one stream and 20 us on streams in turn (each
+// waits for the one before) instead of 20 and 36 with pack, pair and reduction
 // kernels and an uploaded list (MI355X).  Larger ones, see launch_eval_direct.
 template <int TW>
 __global__ __launch_bounds__(kBlock) void k_eval_direct(const EnsDesc E) {

@@ -1,0 +1,89 @@
+"""Order of the library's work across streams, without a GPU: the library runs on
+a stand-in for the HIP runtime (tests/hip_recorder.cpp) that records launches,
+event records and waits, in a process of its own."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+ROCM = "/opt/rocm/include"
+LIB = os.path.join(ROOT, "paper_2604_12083_amd", "libmrs.so")
+
+pytestmark = pytest.mark.skipif(not (os.path.exists(LIB) and shutil.which("g++") and os.path.isdir(ROCM)),
+                                reason="needs the built library, g++ and the HIP headers")
+
+# out: what the child reports; A, B: stream handles of the caller; buf(n): an
+# array of n doubles; log(): the recorded lines since the last call
+_CHILD = """
+import ctypes, json, sys
+sys.modules["torch"] = None
+import numpy as np
+import paper_2604_12083_amd as mrs
+rec = ctypes.CDLL(None)
+rec.rec_take.restype = ctypes.c_char_p
+log = lambda: rec.rec_take().decode().splitlines()
+ready, capturing = rec.rec_events_ready, lambda s: rec.rec_capturing(ctypes.c_void_p(s))
+A, B = 0x1000, 0x2000
+keep = []
+def buf(n):
+    keep.append(np.zeros(n))
+    return keep[-1]
+def names(lines, kind):
+    return [x.split()[1] for x in lines if x.split()[0] == kind]
+def status(call, *a, **k):
+    try:
+        call(*a, **k)
+    except mrs.MrsError as e:
+        return e.status
+    return 0
+ctx = mrs.mrs_context_create(0)
+def evaluate(n, stream=None, prec=mrs.MRS_FP64, call=mrs.mrs_eval_device):
+    log()
+    call(ctx, n, buf(3 * n), buf(3 * n), buf(3 * n), 0.1, 1.0, prec, buf(3 * n), buf(3 * n), stream)
+    return log()
+out = {}
+"""
+
+
+@pytest.fixture(scope="module")
+def child(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("rec") / "rec.so")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-I", ROCM,
+                           os.path.join(HERE, "hip_recorder.cpp"), "-o", lib])
+
+    def run(body):
+        env = dict(os.environ, LD_PRELOAD=lib, PYTHONPATH=ROOT)
+        r = subprocess.run([sys.executable, "-c", _CHILD + body + "\nprint(json.dumps(out))"], cwd=ROOT, env=env,
+                           stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return run
+
+
+@pytest.mark.parametrize("n", [64, 20000])  # one launch, general path
+def test_equal_handle_is_no_proof_of_order(child, n):
+    """A stream may be destroyed with work in flight and its handle be given to
+    another one: an evaluation waits for an unfinished one before it also on an
+    equal handle, but not for a finished one, and a captured one not for what
+    its own stream holds."""
+    out = child(f"""
+n = {n}
+waits = lambda lines: names(lines, "wait")
+out["first"] = waits(evaluate(n, A))
+out["same handle"] = waits(evaluate(n, A))
+out["other stream"] = waits(evaluate(n, B))
+ready(1)
+out["finished"] = waits(evaluate(n, A)); ready(0)
+out["context stream"] = len(waits(evaluate(n)))
+out["context stream again"] = len(waits(evaluate(n)))
+evaluate(n, B); capturing(B)
+out["captured"] = waits(evaluate(n, B))
+""")
+    assert out == {"first": [], "same handle": ["1000"], "other stream": ["2000"], "finished": [], "context stream": 1,
+                   "context stream again": 1, "captured": []}
