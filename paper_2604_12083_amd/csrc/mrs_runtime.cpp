@@ -726,8 +726,9 @@ mrs_status mrs_context_set_stream(mrs_context *ctx, void *stream) {
     CHECK_CTX(ctx);
     hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->own_stream;
     // new state, loads or time may still be on their way in on the old stream
-    // (which the caller may have destroyed since)
-    if (s != ctx->stream && ctx->in_pending) {
+    // (which the caller may have destroyed since, so that an equal handle may
+    // name another one)
+    if (ctx->in_pending) {
         HIPCHK(ctx, hipEventSynchronize(ctx->in_event));
         ctx->in_pending = false;
     }

@@ -87,3 +87,21 @@ out["captured"] = waits(evaluate(n, B))
 """)
     assert out == {"first": [], "same handle": ["1000"], "other stream": ["2000"], "finished": [], "context stream": 1,
                    "context stream again": 1, "captured": []}
+
+
+def test_setting_a_stream_waits_for_queued_state(child):
+    """State, loads and time may still be on their way in on the stream that
+    mrs_context_set_stream replaces, also when the new one has its handle."""
+    out = child("""
+ens = mrs.mrs_ensemble_create(ctx, [0, 8], buf(24), buf(72), None, None, 0.1, 1.0, mrs.rod_params())
+mrs.mrs_context_set_stream(ctx, A)
+log()
+for name, call in (("state", lambda: mrs.mrs_ensemble_set_state(ctx, ens, buf(24), buf(72))),
+                   ("loads", lambda: mrs.mrs_ensemble_set_external(ctx, ens, buf(24), buf(24))),
+                   ("time", lambda: mrs.mrs_ensemble_set_time(ctx, ens, 1.0))):
+    for stream in (B, B):
+        call(); queued = log()
+        mrs.mrs_context_set_stream(ctx, stream)
+        out[name + " " + str(len(out))] = [x.split()[2] for x in queued if x.startswith("record")][-1:] == names(log(), "eventsync")
+""")
+    assert len(out) == 6 and all(out.values()), out
