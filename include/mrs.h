@@ -195,7 +195,8 @@ mrs_status mrs_ensemble_create(mrs_context *ctx, int32_t n_fil, const int32_t *o
 /* Replace the state (host arrays, copied; either may be NULL to keep it).
  * This call, mrs_ensemble_set_external and mrs_ensemble_set_time return once
  * the caller's values have been read; their way to the device is queued on
- * the context stream ahead of every later call. */
+ * the context stream ahead of every later call (MRS_EDEVICE while that stream
+ * is being captured, as for every copy in or out). */
 mrs_status mrs_ensemble_set_state(mrs_ensemble *ens, const double *X, const double *D);
 /* Replace the external point force f_ext and torque n_ext exerted on the
  * fluid at every point (Sec. II.C, Eq. superposition: the loads the MRS sum

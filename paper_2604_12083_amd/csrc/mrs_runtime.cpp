@@ -1240,6 +1240,14 @@ static hipError_t row_slot(mrs_context *ctx, size_t bytes, int *slot) {
     return hipSuccess;
 }
 
+// A graph would replay what later calls put into the slots: calls through them
+// are refused while s is captured.
+static hipError_t not_captured(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &cap);
+    return e != hipSuccess || cap == hipStreamCaptureStatusNone ? e : hipErrorStreamCaptureUnsupported;
+}
+
 static size_t row_width(const std::vector<HostRows> &arrays) {
     size_t w = 0;
     for (auto &r : arrays) w += r.host ? r.w : 0;
@@ -1259,6 +1267,7 @@ static hipError_t in_queued(mrs_context *ctx) {
 static hipError_t rows_in(mrs_ensemble *E, const std::vector<HostRows> &arrays) {
     mrs_context *ctx = E->ctx;
     hipError_t e;
+    if ((e = not_captured(ctx->stream)) != hipSuccess) return e;
     for (int64_t i0 = 0; i0 < E->N; i0 += kRowSlotRows) {
         const int64_t n = std::min(kRowSlotRows, E->N - i0);
         int slot;
@@ -1285,6 +1294,7 @@ static hipError_t rows_in(mrs_ensemble *E, const std::vector<HostRows> &arrays) 
 static hipError_t rows_out(mrs_ensemble *E, const std::vector<HostRows> &arrays, bool *finite) {
     mrs_context *ctx = E->ctx;
     hipError_t e;
+    if ((e = not_captured(ctx->stream)) != hipSuccess) return e;
     volatile int32_t *flag = ctx->flag_host + 1;
     *flag = 0;
     struct Chunk {
@@ -1425,6 +1435,7 @@ mrs_status mrs_ensemble_create(mrs_context *ctx, int32_t n_fil, const int32_t *o
         return fail(ctx, MRS_ENOMEM, "ensemble allocation (%lld points)", (long long)n);
     HIPCHK(ctx, hipMemcpy(E->off.p, soff.data(), (n_fil + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
     HIPCHK(ctx, hipMemcpy(E->inv.p, inv.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
+    HIPCHK(ctx, not_captured(ctx->stream));
     HIPCHK(ctx, launch_set_value(E->clock.as<double>(), 0.0, ctx->stream));
     auto in = [](const double *p) { return const_cast<double *>(p); };
     HIPCHK(ctx, rows_in(E.get(), {{E->X.as<double>(), in(X), 3},
@@ -1522,6 +1533,7 @@ mrs_status mrs_ensemble_set_time(mrs_ensemble *E, double t) {
     mrs_context *ctx = E->ctx;
     if (!std::isfinite(t)) return fail(ctx, MRS_EINVAL, "time must be finite");
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
+    HIPCHK(ctx, not_captured(ctx->stream));  // as the other values of the caller
     HIPCHK(ctx, launch_set_value(E->clock.as<double>(), t, ctx->stream));
     HIPCHK(ctx, in_queued(ctx));
     return MRS_OK;

@@ -105,3 +105,25 @@ for name, call in (("state", lambda: mrs.mrs_ensemble_set_state(ctx, ens, buf(24
         out[name + " " + str(len(out))] = [x.split()[2] for x in queued if x.startswith("record")][-1:] == names(log(), "eventsync")
 """)
     assert len(out) == 6 and all(out.values()), out
+
+
+def test_state_and_loads_stay_out_of_graphs(child):
+    """Rows go in and out through pinned memory that later calls use again, so a
+    captured copy would replay other values: calls on a captured context stream
+    are refused, without a launch, and leave everything as it was."""
+    out = child("""
+mrs.mrs_context_set_stream(ctx, A)
+make = lambda: mrs.mrs_ensemble_create(ctx, [0, 8], buf(24), buf(72), buf(24), buf(24), 0.1, 1.0, mrs.rod_params())
+ens = make()
+calls = {"state": lambda: mrs.mrs_ensemble_set_state(ctx, ens, buf(24), buf(72)),
+         "loads": lambda: mrs.mrs_ensemble_set_external(ctx, ens, buf(24), buf(24)),
+         "time": lambda: mrs.mrs_ensemble_set_time(ctx, ens, 1.0),
+         "get": lambda: mrs.mrs_ensemble_get(ctx, ens), "create": make}
+for on in (True, False):
+    capturing(A if on else None)
+    for name, call in calls.items():
+        log()
+        out[f"{name} {on}"] = [status(call), len(names(log(), "launch")) > 0]
+""")
+    for name in ("state", "loads", "time", "get", "create"):
+        assert out[name + " True"] == [-3, False] and out[name + " False"] == [0, True], (name, out)
