@@ -165,7 +165,10 @@ mrs_status mrs_eval_device_noalloc(mrs_context *ctx, int64_t n, const double *dX
  * i.e. -ds times the paper's fluid-on-rod densities f_k, n_k, with F, N of
  * the absent end segments zero (free ends).  `offsets` is a host array;
  * dX (n x 3), dD (n x 9), dfext, dnext (n x 3, may be NULL = zero), dg, dm
- * (n x 3) are device arrays.  Queued on `stream`. */
+ * (n x 3) are device arrays.  Queued on `stream`: the call returns before its
+ * kernel has run (it waits only where an output lies over an input other than
+ * the loads at the same place).  Under capture MRS_EDEVICE in that case, and
+ * for 800 filaments or more that are not all of one length. */
 mrs_status mrs_rod_forces_device(mrs_context *ctx, int32_t n_fil, const int32_t *offsets,
                                  const double *dX, const double *dD, const mrs_rod_params *rod,
                                  const double *dfext, const double *dnext, double *dg, double *dm,

@@ -629,6 +629,14 @@ static void *scratch_ptr(int device) {
 
 static bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
+// A graph would replay what later calls put into the pinned buffers that values
+// of the host come through: calls that use them are refused while s is captured.
+static hipError_t not_captured(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &cap);
+    return e != hipSuccess || cap == hipStreamCaptureStatusNone ? e : hipErrorStreamCaptureUnsupported;
+}
+
 static hipStream_t pick_stream(mrs_context *ctx, void *stream) {
     return stream ? reinterpret_cast<hipStream_t>(stream) : ctx->stream;
 }
@@ -1108,6 +1116,7 @@ mrs_status mrs_rod_forces_device(mrs_context *ctx, int32_t n_fil, const int32_t 
     const bool stage = under_output(dX, b3, false) || under_output(dD, 3 * b3, false) ||
                        under_output(dfext, b3, true) || under_output(dnext, b3, true);
     if (stage) {
+        HIPCHK(ctx, not_captured(s));  // the copies last as long as this call
         HIPCHK(ctx, copy.reserve(6 * b3));
         char *c = copy.as<char>();
         for (auto in : {std::make_pair(&dX, b3), std::make_pair(&dD, 3 * b3), std::make_pair(&dfext, b3),
@@ -1143,7 +1152,9 @@ mrs_status mrs_rod_forces_device(mrs_context *ctx, int32_t n_fil, const int32_t 
     } else {
         // the list is shared by the context's calls: wait on the stream for
         // the last kernel that reads it (any stream), and on the host before
-        // it is replaced by a larger one
+        // it is replaced by a larger one; a graph would replay a later call's
+        if (not_captured(s) != hipSuccess)
+            return fail(ctx, MRS_EDEVICE, "%d uneven filaments in a captured call (at most %d)", n_fil, kRodArgOffsets - 1);
         const size_t bytes = (size_t)(n_fil + 1) * sizeof(int32_t);
         if (ctx->rod_pending) {
             if (bytes > ctx->eval_rod.bytes) HIPCHK(ctx, hipEventSynchronize(ctx->rod_done));
@@ -1238,14 +1249,6 @@ static hipError_t row_slot(mrs_context *ctx, size_t bytes, int *slot) {
     }
     *slot = i;
     return hipSuccess;
-}
-
-// A graph would replay what later calls put into the slots: calls through them
-// are refused while s is captured.
-static hipError_t not_captured(hipStream_t s) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(s, &cap);
-    return e != hipSuccess || cap == hipStreamCaptureStatusNone ? e : hipErrorStreamCaptureUnsupported;
 }
 
 static size_t row_width(const std::vector<HostRows> &arrays) {

@@ -127,3 +127,25 @@ for on in (True, False):
 """)
     for name in ("state", "loads", "time", "get", "create"):
         assert out[name + " True"] == [-3, False] and out[name + " False"] == [0, True], (name, out)
+
+
+def test_long_offset_lists_stay_out_of_graphs(child):
+    """Filament offsets that fit the kernel's arguments may be captured; a longer
+    list goes through a buffer that later calls use again and is refused."""
+    out = child("""
+call = lambda off: mrs.mrs_rod_forces_device(ctx, off, buf(3 * off[-1]), buf(9 * off[-1]), mrs.rod_params(), None, None,
+                                             buf(3 * off[-1]), buf(3 * off[-1]), A)
+uneven = lambda n: np.concatenate([[0], np.cumsum(2 + np.arange(n) % 2)])
+capturing(A)
+for name, off in (("equal", np.arange(2001) * 3), ("799", uneven(799)), ("800", uneven(800))):
+    log()
+    out[name] = [status(call, off), log()]
+log(); X = buf(30)  # an output over an input goes through copies of the call's own
+out["overlap"] = [status(mrs.mrs_rod_forces_device, ctx, [0, 10], X, buf(90), mrs.rod_params(), None, None, X, buf(30), A),
+                  log()]
+capturing(None)
+out["not captured"] = [status(call, uneven(800)), len(names(log(), "launch"))]
+""")
+    launch = "launch k_rod_forces_aos 1000"
+    assert out == {"equal": [0, [launch]], "799": [0, [launch]], "800": [-3, []], "overlap": [-3, []],
+                   "not captured": [0, 1]}
