@@ -389,7 +389,10 @@ typedef struct {
  * least four) and the automatic configuration then run `reps` (1..20)
  * more times each, interleaved, and the medians decide.  The automatic
  * configuration is kept unless another is more than 1% faster, so a tuned
- * size class is never measurably slower than an untuned one.  *best (may be
+ * size class is never measurably slower than an untuned one.  One-shot
+ * evaluations of up to 24 points per compute unit (FP64; FP32C 20) run kernels
+ * of their own, which are not candidates: they go on with those, and follow only
+ * entries set by mrs_tune_set (also when read back from a file).  *best (may be
  * NULL) receives the stored configuration and *best_ms its median time.
  * Ensembles already planned keep the configuration they were planned with.
  * With a table file set by mrs_tune_on_first_use the file is rewritten. */

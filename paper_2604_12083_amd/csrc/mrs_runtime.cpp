@@ -803,7 +803,7 @@ static EnsDesc eval_desc(int64_t n, const double *dX, const double *df, const do
 // an output lies over an input (other blocks may still read it then; the
 // general path reads every input before it writes).  Wave-split configurations
 // do so up to kDirectMaxPoints; a stored configuration with another
-// decomposition than the automatic one is followed otherwise.  For that one the
+// decomposition than the automatic one is followed otherwise (eval_choice).  For that one the
 // limit is a number of points per CU, in FP32C the smaller one, since beyond the near pairs the tiled kernel takes less than
 // half the time per pair there (calls on one stream, general path against one
 // launch: 1,025 points 21.4 and 13.9 us FP64, 30.5 and 14.3 FP32C; 2,048 points
@@ -812,6 +812,22 @@ static EnsDesc eval_desc(int64_t n, const double *dX, const double *df, const do
 // and 76.9, 6,144 points 101.8 and 95.1, 6,400 points even; MI355X).
 constexpr int kDirectMaxPoints = 2048, kDirectPerCuF64 = 24, kDirectPerCuF32 = 12;
 
+// FP32C evaluations up to this many points per CU: see eval_cfg.
+constexpr int kFourWavePerCu = 20;
+
+// The configuration an evaluation goes by.  The tuner times the kernels of an
+// ensemble, so where evaluations have their own (one launch; four-wave items), an
+// entry that it stored says nothing about them, and following it to the general
+// path would make a tuned size class slower than an untuned one (1,025 points:
+// 21.4 instead of 13.9 us, above).  Entries set by hand, which have no times, are followed.
+static PairCfg eval_choice(mrs_context *ctx, int64_t n, int p) {
+    const int64_t own = (int64_t)(p == MRS_FP64 ? kDirectPerCuF64 : kFourWavePerCu) * ctx->n_cu;
+    const auto t = ctx->tune_ms.find({p, size_bucket(n)});
+    if (!ctx->tuning && n <= own && t != ctx->tune_ms.end() && t->second.first > 0.0)
+        return choose_cfg_for(nullptr, n, p, ctx->n_cu);
+    return choose_cfg(ctx, n, p);
+}
+
 // Same decomposition (the schedule changes no result).
 static bool same_items(const PairCfg &a, const PairCfg &b) {
     return a.mode == b.mode && a.tpl == b.tpl && a.K == b.K && a.chunk == b.chunk;
@@ -819,7 +835,7 @@ static bool same_items(const PairCfg &a, const PairCfg &b) {
 
 static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p) {
     if (ctx->tuning) return false;
-    const PairCfg c = choose_cfg(ctx, d.N, p);
+    const PairCfg c = eval_choice(ctx, d.N, p);
     const int64_t limit = (int64_t)(p == MRS_FP64 ? kDirectPerCuF64 : kDirectPerCuF32) * ctx->n_cu;
     const bool split = c.mode == PAIR_SPLIT && d.N <= kDirectMaxPoints;
     if (!split && (d.N > limit || !same_items(c, choose_cfg_for(nullptr, d.N, p, ctx->n_cu)))) return false;
@@ -838,10 +854,8 @@ static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p) {
 // 6,400 points even; MI355X).  Ensembles keep the tiles: in batches of
 // different sizes the four-wave kernel is one more launch with a tail of its
 // own (12 ensembles of 518 to 9,216 points: 1,038 -> 1,077 us).
-constexpr int kFourWavePerCu = 20;
-
 static PairCfg eval_cfg(mrs_context *ctx, int64_t n, int p) {
-    PairCfg c = choose_cfg(ctx, n, p);
+    PairCfg c = eval_choice(ctx, n, p);
     if (!ctx->tuning && p == MRS_FP32C && c.mode == PAIR_TILE && n <= (int64_t)kFourWavePerCu * ctx->n_cu &&
         same_items(c, choose_cfg_for(nullptr, n, p, ctx->n_cu))) {
         PairCfg four;

@@ -149,3 +149,38 @@ out["not captured"] = [status(call, uneven(800)), len(names(log(), "launch"))]
     launch = "launch k_rod_forces_aos 1000"
     assert out == {"equal": [0, [launch]], "799": [0, [launch]], "800": [-3, []], "overlap": [-3, []],
                    "not captured": [0, 1]}
+
+
+@pytest.mark.parametrize("prec,n,entry,untuned,followed", [
+    (0, 1000, (0, 1, 4), "k_eval_direct<", "k_pairs_tile_f64<1, false, true>"),
+    (0, 2048, (0, 1, 16), "k_eval_direct<", "k_pairs_tile_f64<1, false, true>"),
+    (0, 6144, (0, 2, 9), "k_eval_direct<", "k_pairs_tile_f64<2, false, false>"),
+    (0, 6145, (0, 2, 9), None, "k_pairs_tile_f64<2, false, false>"),
+    (1, 3072, (0, 2, 4), "k_eval_direct<", "k_pairs_tile_f32<2, false, false>"),
+    (1, 5120, (0, 2, 4), "k_pairs_tile_f32<1, false, true>", "k_pairs_tile_f32<2, false, false>"),
+    (1, 5121, (0, 2, 4), None, "k_pairs_tile_f32<2, false, false>")])
+@pytest.mark.parametrize("call", ["mrs_eval_device", "mrs_eval_device_noalloc"])
+def test_evaluations_keep_their_own_kernels_in_a_tuned_class(child, tmp_path, prec, n, entry, untuned, followed, call):
+    """An entry that the tuner stored (it has times) was timed against the kernels
+    of an ensemble: one-shot evaluations follow it only beyond the sizes for which
+    they have faster kernels of their own, an entry set by hand always."""
+    line = f"{prec} {n.bit_length() - 1} {entry[0]} {entry[1]} {entry[2]} 0"
+    files = {}
+    for name, times in (("tuned", "0.02 0.03"), ("hand", "-1 -1")):
+        files[name] = str(tmp_path / name)
+        with open(files[name], "w") as f:
+            f.write(f"mrs-pair-tuning 1 gfx950 256 0\n{line} {times}\n")
+    out = child(f"""
+run = lambda: [x[7:x.rindex(" ")] for x in evaluate({n}, A, {prec}, mrs.{call}) if x.startswith("launch")]
+out["none"] = run()
+for name, path in {files!r}.items():
+    mrs.mrs_tune_load(ctx, path)
+    out[name] = run()
+    out[name + " chunks"] = mrs.mrs_tune_get(ctx, {n}, {prec})["chunks"]
+""")
+    tiled = ["k_pack_aos", followed, "k_reduce<0>"]
+    assert out["hand"] == tiled and out["hand chunks"] == out["tuned chunks"] == entry[2]
+    if untuned is None:
+        assert out["tuned"] == tiled
+    else:
+        assert out["tuned"] == out["none"] and out["tuned"] != tiled and out["tuned"][len(out["tuned"]) // 2].startswith(untuned)
