@@ -127,3 +127,27 @@ def test_automatic_items_of_ensembles(mrs, ctx, prec, N):
         got.append(g)
     _check(got[0], X, f, n, 0.05, prec, f"ensemble N {N} prec {prec} {auto}")
     assert all(np.array_equal(got[0][k], g[k]) for g in got[1:] for k in (0, 1))
+
+
+@pytest.mark.parametrize("offset", [0.0, 1e4, 1e6])
+def test_filaments_far_from_the_origin(mrs, ctx, offset):
+    """Straight filaments at separations from contact to a few hundred eps,
+    crossing ones among them, `offset` eps from the origin (beyond 2^16 eps the hi
+    parts of the FP32C positions round by more than a hundredth of eps, and the
+    boxes are widened by it): masked, exact and anchored blocks on every form."""
+    rng = np.random.default_rng(41)
+    M, ds = 64, 1.0 / 64
+    eps = 1.5 * ds
+    X = []
+    for k in range(48):
+        d = rng.normal(size=3)
+        at = rng.uniform(0.0, 200.0 * eps, 3) if k % 3 else rng.normal(scale=0.5 * eps, size=3) - 0.5 * d / np.linalg.norm(d)
+        X.append(at + (np.arange(M) * ds)[:, None] * d / np.linalg.norm(d))
+    X = np.concatenate(X) + offset * eps * np.array([0.6, -0.64, 0.48])
+    f, n = rng.normal(size=X.shape), rng.normal(size=X.shape)
+    for prec in (1, 0):
+        for cfg in ((0, 1, 9, 0), (0, 2, 9, 0), (2, 1, 9, 0)):
+            mrs.mrs_tune_set(ctx, len(X), prec, *cfg)
+            got, names = _launches(mrs, ctx, lambda: _eval(mrs, ctx, "mrs_eval_device", X, f, n, eps, prec))
+            assert _is(names, prec, cfg[0]), (cfg, names)
+            _check(got, X, f, n, eps, prec, f"offset {offset:g} prec {prec} cfg {cfg}")
