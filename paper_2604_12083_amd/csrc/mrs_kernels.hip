@@ -245,7 +245,8 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_forces(int stage_state, co
     double acc[3] = {0.0, 0.0, 0.0};
     const int nblk = E.n_ljblk;
     // boxes of the runs, six bounds each, shared by the waves
-    const uint64_t starts = __ballot(lane == 0 || fi != __shfl_up(fi, 1, 64) ? 1 : 0);
+    const int before = __shfl_up(fi, 1, 64);  // by all lanes, or lane 1 reads from a masked one
+    const uint64_t starts = __ballot(lane == 0 || fi != before ? 1 : 0);
     const int run = min(__popcll(starts & (~0ull >> (63 - lane))) - 1, kLjRuns - 1);
     const int runs = min(__popcll(starts), kLjRuns);
     for (int q = w; q < 6 * runs; q += kLjWaves) {
