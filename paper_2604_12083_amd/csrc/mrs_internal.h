@@ -14,9 +14,9 @@ constexpr int kSrcTile = 256;
 constexpr int kKahanBlock = 64;
 // Targets per wave in the small-N pair kernel (lanes split the sources).
 // One: the kernel is latency-bound, and four times the waves shorten each
-// wave's chain (MI355X: 64 points 10.2 -> 6.6 us FP32C, 8.2 -> 6.3 us FP64;
-// 960 points 27.7 -> 15.0 us and 19.1 -> 11.8 us; same results, since each
-// target's sum is formed the same way).
+// wave's chain (MI355X, FP64 records, which both precisions use: 64 points 8.2 ->
+// 6.3 us, 960 points 19.1 -> 11.8; same results, since each target's sum is formed
+// the same way).
 constexpr int kSplitTargetsPerWave = 1;
 constexpr int kSplitTargetsPerBlock = kSplitTargetsPerWave * (kBlock / 64);
 

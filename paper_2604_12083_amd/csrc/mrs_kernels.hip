@@ -320,7 +320,11 @@ __global__ __launch_bounds__(64 * kLjWaves) void k_lj_forces(int stage_state, co
 // nodes are summed out of LDS while other waves make the boxes; longer ones by
 // rod_filament.  25 swimmers of 51 points take 7.9 us instead of 4.2 + 12.8 +
 // 5.5 (9.6 with rod_filament after the repulsion: its loads of frames and loads
-// alone took 1.9 us; MI355X).
+// alone took 1.9 us; MI355X).  Near the limit a block holds 120 KB of LDS, one
+// block per CU, and the largest ensemble of a batch sets that for all: still
+// faster than the three launches before it (their sum and this launch): 16
+// ensembles of 3,162 points 47.6 and 40.6 us, one of 3,162 with 64 of 306 points
+// 31.3 and 18.1, with 24 of 306 points 29.2 and 13.3 (11.8 without the large one).
 __global__ __launch_bounds__(64 * kLjWaves) void k_lj_rods(int stage_state, int elastic, int scheme, int stage,
                                                            double dt, const EnsDesc *__restrict__ desc,
                                                            const RodItem *__restrict__ items) {
@@ -542,7 +546,10 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(int stage, int scheme
 // 10,450 cycles the pairs take 5,300, rod segments and nodes 2,900, the sums and
 // the update 2,150).
 // At 128 points one CU has four times the pairs, a step took 10.6 instead of
-// 11.2 us and a call of one step 25 instead of 23, so those go by stages.
+// 11.2 us and a call of one step 25 instead of 23, so those go by stages.  So do 65
+// to 127 points, at the time of 128 (65 points 10.6 us per step, 127 points 10.9):
+// the form has one lane per target, and the one measured at 128 has two targets
+// per lane, the same chain at 65.
 //
 // Every operation and every sum is that of k_rod_forces, k_pairs_split and
 // k_reduce in the same order, so the bits are the same: small_pairs<MOD> sums

@@ -27,7 +27,11 @@ namespace mrs {
 // dispatched last.  A SIMD issues the oldest of its waves first, so the waves
 // that start last run alone at the end of the grid; short ones keep that end
 // short (measured on MI355X: pair kernel -3.4% at 12,800 points, -0.6% at
-// 256,000; the FP64 kernel, two targets per lane, gets slower).
+// 256,000).  The FP64 kernel (two targets per lane, three resident blocks per CU)
+// keeps equal chunks: with the tail split 12,800 points take 314.6 instead of
+// 298.7 us, 19,200 points 670 instead of 655; on the persistent schedule it gains
+// from about 25,600 points on (1,160 -> 1,126 us; 51,200 points 4,464 -> 4,424,
+// of which the longer reduction takes 4 back).
 constexpr int kTailPercent = 8, kTailDiv = 4;
 
 // Blocks of the tiled kernel at `tpl` targets per lane and 128-source chunks.
@@ -49,25 +53,29 @@ static bool fp64_one_target(int64_t N, int n_cu) { return blocks_at(N, 2) < (int
 static bool small_grid(int64_t N, int tpl, int n_cu) { return blocks_at(N, tpl) <= (int64_t)n_cu; }
 
 // Ensembles up to 1,024 points use the wave-split kernel (one target per
-// wave, lanes split the sources), in both precisions.  Alone it is faster
-// than the tiled kernel up to ~1,500 points (MI355X, pair + reduction
-// kernels, FP32C: 1,024 points 18.8 vs 25.8 us, 1,280 points 20.4 vs 26.1),
-// but in batches of 16 ensembles it loses from ~1,000 points on (1,024
-// points 67 vs 44 us, 1,280 points 90 vs 58; 512 points even), so the limit
-// stays where the batched cost is still moderate.
+// wave, lanes split the sources), in both precisions.  In FP32C it is much
+// faster alone and loses in deep batches (MI355X, pair + reduction kernels,
+// wave-split and tiled, alone, in batches of 4 and of 16: 512 points 10.4 and
+// 20.3, 12.2 and 21.2, 22.0 and 21.9 us; 768 points 12.3 and 21.3, 15.3 and 21.4,
+// 33.4 and 26.9; 1,024 points 13.5 and 20.9, 20.6 and 21.6, 52.1 and 34.2; 1,280
+// points 16.1 and 21.0, 26.6 and 22.1, 73.5 and 44.3): the line lies where
+// batches of 4 still gain.  In FP64 the tiled kernel, in quarters of its items,
+// is as fast alone from 768 points on and the faster one in batches (512 points
+// 11.4 and 12.2, 12.2 and 11.8, 21.9 and 18.4 us; 768 points 11.8 and 11.5, 15.9
+// and 15.3, 34.4 and 28.9; 1,024 points 13.2 and 12.0, 21.6 and 18.9, 54.1 and
+// 44.8); the line dates from before the quarters.
 static bool split_mode(int64_t N, int) { return N <= 1024; }
 
 // Automatic tiled configurations with at least this many blocks per CU run
-// the persistent schedule (blocks claim items from a queue).  In grids this
-// deep it was faster than the hardware grid on MI355X (interleaved A/B of
-// the pair kernel: 256,000 points -1.3% FP32C and -1.5% FP64, 1,000
-// swimmers (51,000 points, 58 blocks per CU) -1.4% FP32C; the tuner's
-// one-shot evaluations: 102,400 points -1.3% and -1.1%); in shallow grids
-// it is much slower (12,800 points, 12 blocks per CU: +20%).  The FP64
-// kernel at two targets per lane keeps four blocks per CU resident instead
-// of five, and from about six rounds of them (24 blocks per CU) the
-// persistent schedule won there too (51,200 points: -1.9% in the tuner;
-// 1,000 swimmers, 24 blocks per CU: -1.3% in interleaved A/B).
+// the persistent schedule (blocks claim items from a queue).  FP32C, five
+// blocks per CU resident (pair + reduction kernels, grid and persistent): 19,200
+// points (20 blocks per CU) 335 and 361 us, 25,600 (27) 568 and 591, 38,400 (41)
+// 1,242 and 1,239, 51,200 (57) 2,176 and 2,150, 89,600 (91) 6,603 and 6,475.  FP64
+// at two targets per lane, three resident (pair kernel): 12,800 points (5) 298
+// and 308 us, 19,200 (9) 656 and 660, 25,600 (11) 1,198 and 1,162, 38,400 (18)
+// 2,578 and 2,535, 51,200 (24) 4,548 and 4,489, 64,000 (31) 7,102 and 6,994
+// (MI355X).  So FP32C crosses at about 40 blocks per CU, close to the line, and
+// FP64 at about 10: its line was drawn when four blocks of it were resident.
 constexpr int kPersistentBlocksPerCu = 48, kPersistentBlocksPerCuF64T2 = 24;
 
 PairCfg choose_cfg_for(const PairCfg *tuned, int64_t N, int prec, int n_cu) {
@@ -125,16 +133,23 @@ PairCfg choose_cfg_for(const PairCfg *tuned, int64_t N, int prec, int n_cu) {
 
 // FP32C ensembles that the FP64 kernels sum faster (with REC_WIDE records, so
 // no value loses precision).  Wave-split configurations always: the launch is
-// bound by latency and its near pairs are FP64 anyway (1,020 points in
-// contact 14.6 -> 9.1 us, 46 -> 27 us in batches of eight; 512 points of long
-// filaments 8.5 -> 6.6 and 14.7 -> 11.6 us).  One target per lane with contact
-// forces up to kWideContactPoints: every contact source is summed in FP64 for
-// every target, lane by lane after the FP32 pass (swimmers, pair kernel alone
-// and in batches of eight: 1,275 points 28.4 -> 13.6 and 49 -> 38 us, 3,060
-// points 58.6 -> 36.7 and 151 -> 147 us; 4,080 points 49 -> 39 but 214 -> 256
-// us; in quarters since, 8.5 and 32, 27.4 and 164 us at 3,162 points).  Without
-// contact forces the FP32C kernel wins in batches (1,152 points: 22 us against
-// 29).
+// bound by latency and its near pairs are FP64 anyway (whole evaluations, FP32C
+// records and these, alone and in batches of 256: 128 points 21.7 -> 19.7 and
+// 85.7 -> 77.0 us; 512 points 23.8 -> 22.0 and 318.6 -> 245.0; 1,024 points 27.3 ->
+// 25.0 and 828 -> 734; 20 swimmers in contact, 1,020 points, 44.3 -> 27.3 and in
+// batches of 128 691 -> 415).  One target per lane with contact forces up to
+// kWideContactPoints: the FP32 kernel sums every contact source in FP64 for every
+// target after its own pass, a chain that a small grid waits for.  Deep batches
+// fill the chip with either kernel and run at their rates, FP32C's the higher one
+// (whole evaluations, FP32C records and these, alone and in batches of 4, 8, 16
+// and 32: 1,275 points 56 -> 29, 64 -> 41, 73 -> 55, 103 -> 88, 154 -> 155; 1,785
+// points 63 -> 34, 73 -> 55, 94 -> 87, 135 -> 149, 221 -> 272; 2,550 points 67 ->
+// 43, 92 -> 84, 131 -> 146, 210 -> 269, 372 -> 513; 3,162 points 81 -> 51, 110 ->
+// 115, 171 -> 204, 284 -> 386, 509 -> 747).  An ensemble has to give the same bits
+// alone and in a batch, so one rule serves both: the line lies where an ensemble
+// alone, the ordinary call, still gains a third, and batches of eight and more of
+// the larger ones pay for it.  Without contact forces the FP32C kernel wins in
+// batches (1,152 points: 22 us against 29).
 constexpr int64_t kWideContactPoints = 3200;
 
 bool wide_records(const PairCfg &c, int64_t N, int prec, bool has_lj) {
@@ -143,12 +158,16 @@ bool wide_records(const PairCfg &c, int64_t N, int prec, bool has_lj) {
 }
 
 // Ensembles whose FP64 sum at one target per lane runs in quarters of the work
-// items (k_pairs_tile_f64).  Alone that fills the chip better, in deep batches
-// its further staging costs some percent (pair kernel alone and in batches of
-// eight, in place of whole items: 1,275 points 13.8 -> 8.5 and 38.2 -> 31.7 us,
-// 2,048 points 15.3 -> 13.0 and 69.7 -> 71.4, 3,200 points 38.4 -> 27.5 and
-// 170 -> 167; 3,968 points 39.9 -> 36.0 but 247 -> 252, 5,120 points 68 -> 59
-// but 395 -> 415; MI355X).
+// items (k_pairs_tile_f64).  Alone that fills the chip better; in deep batches its
+// block sums, taken four times as often, cost 2 to 6% (whole evaluations, whole
+// items and quarters, alone and in batches of 4, 8, 16 and 32: 1,080 points 31.0 ->
+// 25.3, 40.1 -> 34.5, 50 -> 46, 77 -> 73, 120 -> 120 us; 1,500 points 32.2 -> 28.2,
+// 49 -> 44, 70 -> 65, 106 -> 107, 183 -> 191; 2,048 points 32.9 -> 30.3, 60 -> 59, 94
+// -> 96, 160 -> 168, 292 -> 313; 2,500 points 41.5 -> 38.3, 86 -> 82, 136 -> 138, 239
+// -> 250, 451 -> 479; 3,200 points 56 -> 46, 121 -> 112, 202 -> 198, 366 -> 372, 692 ->
+// 717; pair kernel alone at 3,968 points 39.9 -> 36.0 but in batches of eight 247 ->
+// 252, at 5,120 68 -> 59 but 395 -> 415; MI355X).  As above one rule serves both;
+// the line lies where batches of eight lose 2% at most.
 constexpr int64_t kQuarterPoints = 3200;
 
 void add_items(Plan &P, int e, int64_t N, int n_fil, const PairCfg &c) {

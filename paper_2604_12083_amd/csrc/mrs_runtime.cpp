@@ -850,8 +850,12 @@ static bool eval_is_direct(mrs_context *ctx, const EnsDesc &d, int p) {
 // automatic tiles, FP32C evaluations up to 20 points per CU split 256-source
 // chunks over a block's four waves: at one to three tiled blocks per CU the
 // fullest CU sets the time (pair + reduction kernels: 3,328 points 32.7 -> 24.7
-// us, 3,968 points 33.1 -> 29.2, 5,120 points 44.7 -> 37.4, 5,632 points 47 -> 42,
-// 6,400 points even; MI355X).  Ensembles keep the tiles: in batches of
+// us, 3,968 points 33.1 -> 29.2, 5,120 points 44.7 -> 37.4; whole calls beyond the
+// line, tiles and four waves, on one stream and on three in turn: 5,200 points
+// 54.5 and 49.3, 64.0 and 58.6 us, 5,632 points 56.4 and 51.6, 65.8 and 61.2, 6,144
+// points 62.3 and 58.1, 71.8 and 66.9, 6,656 points 68.5 and 64.5, 77.5 and 73.6:
+// the crossing lies beyond 26 points per CU, the line stays at the sizes that the
+// kernel times were taken at; MI355X).  Ensembles keep the tiles: in batches of
 // different sizes the four-wave kernel is one more launch with a tail of its
 // own (12 ensembles of 518 to 9,216 points: 1,038 -> 1,077 us).
 static PairCfg eval_cfg(mrs_context *ctx, int64_t n, int p) {
