@@ -347,38 +347,39 @@ def bench_tune(mrs, sizes, reps=7, tune_reps=5):
     """The tuner against the automatic configuration: for each size (sinusoidal
     128-point filaments at the density of 100 in a box of side 10; the tuner
     itself times straight ones) and precision, mrs_autotune in a fresh
-    context, then `reps` interleaved evaluations (mrs_eval_device, device time
-    of all its kernels) with the automatic entry and with the tuned one."""
-    import torch
-
+    context, then `reps` interleaved evaluations of two resident ensembles
+    (device time of all their kernels), one planned with the automatic entry
+    and one with the tuned one."""
     import synth
 
     rows = []
     for n in sizes:
         F = n // 128
         e = synth.filaments(F, 128, 10.0 * (F / 100.0) ** (1.0 / 3.0), 4000 + F)
-        dX, df, dn = (torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0") for a in (e.X, e.f, e.n))
-        dU, dW = torch.empty_like(dX), torch.empty_like(dX)
-        s = torch.cuda.current_stream()
+        rod = mrs.rod_params(*(getattr(e.rod(), k) for k in ("a", "b", "omega0", "ds")))
         for prec, tag in ((mrs.MRS_FP32C, "fp32c"), (mrs.MRS_FP64, "fp64")):
             ctx = mrs.mrs_context_create(0)
             try:
                 auto = mrs.mrs_tune_get(ctx, e.N, prec)
-                auto_entry = (auto["mode"], auto["targets_per_lane"], 1 if auto["mode"] == 1 else 0, 0)
+                auto_entry = (auto["mode"], auto["targets_per_lane"], 1 if auto["mode"] == 1 else 0, auto["schedule"])
                 log(f"tune N={e.N} {tag}: automatic {auto}")
                 t0 = time.perf_counter()
                 best, best_ms = mrs.mrs_autotune(ctx, e.N, prec, tune_reps)
                 tune_s = time.perf_counter() - t0
                 tuned = mrs.mrs_tune_get(ctx, e.N, prec)
                 entry = (best["mode"], best["targets_per_lane"], best["chunks"], best["schedule"])
-                times = {"automatic": [], "tuned": []}
+                times, ens = {"automatic": [], "tuned": []}, {}
+                for name, cfg in (("automatic", auto_entry), ("tuned", entry)):
+                    mrs.mrs_tune_set(ctx, e.N, prec, *cfg)
+                    ens[name] = mrs.mrs_ensemble_create(ctx, e.offsets, e.X, e.D, e.f, e.n, e.eps, e.mu, rod)
+                    mrs.mrs_ensemble_eval(ctx, ens[name], prec, False)  # keeps the entry it was planned with
                 for r in range(reps + 1):
-                    for name, cfg in (("automatic", auto_entry), ("tuned", entry)):
-                        mrs.mrs_tune_set(ctx, e.N, prec, *cfg)
-                        mrs.mrs_profile_reset(ctx)
-                        mrs.mrs_profile_select(ctx, "")
-                        mrs.mrs_profile_enable(ctx, True)
-                        mrs.mrs_eval_device(ctx, e.N, dX, df, dn, e.eps, e.mu, prec, dU, dW, s)
+                    for name in times:
+                        for timed in (False, False, True):  # two untimed, so that each follows its like
+                            mrs.mrs_profile_reset(ctx)
+                            mrs.mrs_profile_select(ctx, "")
+                            mrs.mrs_profile_enable(ctx, timed)
+                            mrs.mrs_ensemble_eval(ctx, ens[name], prec, False)
                         mrs.mrs_profile_enable(ctx, False)
                         _, ms = mrs.mrs_profile_query(ctx)
                         if r > 0:
