@@ -41,14 +41,14 @@ FLOPS_PER_PAIR = 92       # algorithmic flops of one (target, source) evaluation
 # gives for the workload) and the schedule (0 grid, 1 persistent) they were
 # taken on: any other kernel, decomposition or schedule reports null.
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2604_12083_amd", "csrc", f) for f in ("mrs_pairs.hip", "mrs_device_pairs.h")]
-KERNEL_SHA = "cad473a4f5822343cafcc7e2fabf35c52c6ac4514f95bbe4e7e9cf477de9ee6d"
+KERNEL_SHA = "2f64090ca6c5ac31f1087066d52c792c2b2e899f86107ee690ba8988752375cb"
 MEASURED_TRAFFIC = {
-    ("ens12800", "fp32c", "678ec7c5e5d82ecf", 0): (3561.4 * 2.0 + 37200.0) * 1024,
-    ("ens12800", "fp64", "adb3c89bda2d142d", 0): (4264.11 * 2.0 + 30000.0) * 1024,
-    ("ens256000", "fp32c", "4a2b01f9e8a27aa9", 1): (319025.31 * 2.0 + 264767.56) * 1024,
-    ("ens256000", "fp64", "571ba5e594123b76", 1): (480128.75 * 2.0 + 396563.69) * 1024,
-    ("swim", "fp32c", "72ec18efbf0e53ad", 1): (41799.62 * 2.0 + 177672.91) * 1024,
-    ("swim", "fp64", "df10004c75444124", 1): (76843.16 * 2.0 + 148467.09) * 1024,
+    ("ens12800", "fp32c", "678ec7c5e5d82ecf", 0): (3562.29 * 2.0 + 37200.0) * 1024,
+    ("ens12800", "fp64", "adb3c89bda2d142d", 0): (4263.38 * 2.0 + 30000.0) * 1024,
+    ("ens256000", "fp32c", "4a2b01f9e8a27aa9", 1): (311687.83 * 2.0 + 264767.56) * 1024,
+    ("ens256000", "fp64", "571ba5e594123b76", 1): (482783.83 * 2.0 + 396563.69) * 1024,
+    ("swim", "fp32c", "72ec18efbf0e53ad", 1): (41756.09 * 2.0 + 177671.21) * 1024,
+    ("swim", "fp64", "df10004c75444124", 1): (77404.88 * 2.0 + 148466.86) * 1024,
 }
 
 
