@@ -134,7 +134,9 @@ mrs_status mrs_eval_host(mrs_context *ctx, int64_t n, const double *X, const dou
  * points per compute unit in FP64, 12 in FP32C) run in one launch without
  * scratch when the decomposition in force is the automatic one and no output
  * overlaps an input; their FP32C pairs are summed in FP64.  The outputs are not
- * checked for finiteness (the call returns before they exist). */
+ * checked for finiteness (the call returns before they exist).  In a graph,
+ * only calls without scratch outlive a later, larger call (which moves the
+ * scratch): capture mrs_eval_device_noalloc instead. */
 mrs_status mrs_eval_device(mrs_context *ctx, int64_t n, const double *dX, const double *df,
                            const double *dtorque, double eps, double mu, mrs_precision prec,
                            double *dU, double *dOmega, void *stream);

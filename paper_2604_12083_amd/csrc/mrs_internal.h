@@ -173,8 +173,17 @@ inline void set_records(EnsDesc &d, void *rec, int64_t n, RecForm form, bool des
     d.blk = desc ? reinterpret_cast<float *>(b + r + w) : nullptr;
 }
 
+// A part of an evaluation's work list as a kernel argument (k_store_list).
+constexpr int kListWords = 240;  // argument blocks end at 4 KiB
+struct ListPart {
+    uint4 v[kListWords];
+};
+
 // Launch wrappers (mrs_pairs.hip, mrs_kernels.hip).  All return the launch's hipError_t.
 hipError_t launch_pack_aos(const EnsDesc &h_desc, const void *src, void *dst, size_t bytes, hipStream_t s);
+// bytes (a multiple of 16) of host memory to dst by value: once queued, or
+// captured, the source is not read again.
+hipError_t launch_store_list(const void *src, void *dst, size_t bytes, hipStream_t s);
 // elastic < 0: every ensemble uses its own EnsDesc::elastic.  The waveform
 // time of the launch is clock + c dt, c the node of RK stage `stage` of
 // `scheme` (0 for stage 0); dt = NaN: every ensemble uses its own dt.

@@ -1,6 +1,7 @@
 // HIP kernels (gfx950) of the MRS filament path other than the pair sum.
 //
 //   k_pack_aos        n x 3 caller arrays -> source records
+//   k_store_list      the work list of a captured evaluation
 //   k_rod_forces      per segment: A = sum_j D^j_{k+1} (D^j_k)^T, its principal
 //                     square root, mid frame, F and N (Sec. II.B, Eqs.
 //                     mid_triad, F_comp_discrete, N_comp_discrete; Alg. 1);
@@ -18,6 +19,8 @@
 // Source records: FP32C positions in units of eps (rho = x/eps) split
 // hi + lo, forces f/eps and torques n/eps^2; FP64 records hold x, f, n.
 #include <hip/hip_runtime.h>
+
+#include <cstring>
 
 #include "mrs_device_pairs.h"
 #include "mrs_device_rod.h"
@@ -76,6 +79,15 @@ __global__ __launch_bounds__(kBlock) void k_pack_aos(const EnsDesc E, const uint
     const int b = i / kDescPoints;  // wave-uniform
     if (E.blk && b * kDescPoints < E.N) block_desc_from_x(E, X, true, b);
 }
+
+// The work list of a captured evaluation: a graph replays kernel arguments, while
+// a copy would read the host memory again, which by then holds something else.
+// 3.8 KB per launch, 20 launches at 12,800 points; eager calls copy.
+__global__ __launch_bounds__(kBlock) void k_store_list(uint4 *__restrict__ dst, int n, const ListPart part) {
+    const int q = threadIdx.x;
+    if (q < n) dst[q] = part.v[q];
+}
+static_assert(kListWords <= kBlock, "one thread per word");
 
 // One block per filament (rod_filament), or one wave per source-block
 // descriptor (RodItem with fil < 0): the descriptors depend only on the
@@ -809,6 +821,20 @@ hipError_t launch_pack_aos(const EnsDesc &h_desc, const void *src, void *dst, si
     hipLaunchKernelGGL(k_pack_aos, dim3(blocks_for(h_desc.N) + copy), dim3(kBlock), 0, s, h_desc,
                        static_cast<const uint4 *>(src), static_cast<uint4 *>(dst), n16, copy);
     return hipGetLastError();
+}
+
+hipError_t launch_store_list(const void *src, void *dst, size_t bytes, hipStream_t s) {
+    if (bytes % sizeof(uint4)) return hipErrorInvalidValue;
+    const size_t words = bytes / sizeof(uint4);
+    hipError_t e = hipSuccess;
+    for (size_t w = 0; w < words && e == hipSuccess; w += kListWords) {
+        const int n = (int)(words - w < (size_t)kListWords ? words - w : (size_t)kListWords);
+        ListPart part{};
+        std::memcpy(part.v, static_cast<const uint4 *>(src) + w, (size_t)n * sizeof(uint4));
+        hipLaunchKernelGGL(k_store_list, dim3(1), dim3(kBlock), 0, s, static_cast<uint4 *>(dst) + w, n, part);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 hipError_t launch_rod_forces(int stage_state, int elastic, int scheme, int stage, double dt,

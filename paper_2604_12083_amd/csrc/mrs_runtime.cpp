@@ -1001,9 +1001,13 @@ mrs_status mrs_eval_device(mrs_context *ctx, int64_t n, const double *dX, const 
     eval_layout(L, n, args, p, c, sc);
     if (ctx->eval_pending && L.blob.size() > ctx->eval_items.bytes) HIPCHK(ctx, hipEventSynchronize(ctx->eval_done));
     HIPCHK(ctx, ctx->eval_items.reserve(L.blob.size()));
-    mrs_context::Stage *staged;
-    HIPCHK(ctx, stage_slot(ctx, L.blob.size(), &staged));
-    std::memcpy(staged->host, L.blob.data(), L.blob.size());
+    mrs_context::Stage *staged = nullptr;
+    if (not_captured(s) != hipSuccess) {
+        HIPCHK(ctx, launch_store_list(L.blob.data(), ctx->eval_items.p, L.blob.size(), s));
+    } else {
+        HIPCHK(ctx, stage_slot(ctx, L.blob.size(), &staged));
+        std::memcpy(staged->host, L.blob.data(), L.blob.size());
+    }
     HIPCHK(ctx, eval_launch(ctx, L, p, ctx->eval_items.as<char>(), staged, s));
     HIPCHK(ctx, eval_end(ctx, s));
     return MRS_OK;
@@ -1053,8 +1057,10 @@ mrs_status mrs_eval_device_noalloc(mrs_context *ctx, int64_t n, const double *dX
     // calls of this context on different streams run in order (as in
     // mrs_eval_device); calls of other contexts on this device race
     HIPCHK(ctx, eval_begin(ctx, s));
-    // pageable source: the call returns once the list has been staged
-    HIPCHK(ctx, hipMemcpyAsync(base, L.blob.data(), L.blob.size(), hipMemcpyHostToDevice, s));
+    // pageable source: the call returns once the list has been staged; a
+    // captured copy would read it at every replay, when it is gone
+    if (not_captured(s) != hipSuccess) HIPCHK(ctx, launch_store_list(L.blob.data(), base, L.blob.size(), s));
+    else HIPCHK(ctx, hipMemcpyAsync(base, L.blob.data(), L.blob.size(), hipMemcpyHostToDevice, s));
     HIPCHK(ctx, eval_launch(ctx, L, p, base, nullptr, s));
     HIPCHK(ctx, eval_end(ctx, s));
     return MRS_OK;

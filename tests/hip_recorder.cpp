@@ -1,6 +1,7 @@
 // Stands in for the HIP runtime on a machine without a GPU (preloaded by
-// tests/test_call_order.py): device memory is host memory, kernels do nothing,
-// and every call that orders work on a stream is written to a log.
+// tests/test_call_order.py): device memory is host memory, kernels do nothing
+// (but k_store_list, which copies its argument), and every call that orders work
+// on a stream is written to a log.
 #define __HIP_PLATFORM_AMD__ 1
 #include <cxxabi.h>
 #include <hip/hip_runtime_api.h>
@@ -59,7 +60,8 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, hipStream_t *
     *g = g_config.g; *b = g_config.b; *sh = g_config.sh; *s = g_config.s;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *fn, dim3, dim3, void **, size_t, hipStream_t s) {
+hipError_t hipLaunchKernel(const void *fn, dim3, dim3, void **args, size_t, hipStream_t s) {
+    if (g_kernels[fn] == "k_store_list") std::memcpy(*(void **)args[0], args[2], *(int *)args[1] * size_t(16));
     return note(("launch " + g_kernels[fn]).c_str(), s);
 }
 
@@ -72,7 +74,8 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
     return hipSuccess;
 }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 3; return hipSuccess; }
-hipError_t hipGetSymbolAddress(void **p, const void *) { static void *m = std::calloc(1, 64 << 20); *p = m; return hipSuccess; }
+void *rec_symbol() { static void *m = std::calloc(1, 64 << 20); return m; }  // the library's static device array
+hipError_t hipGetSymbolAddress(void **p, const void *) { *p = rec_symbol(); return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
 

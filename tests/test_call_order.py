@@ -184,3 +184,32 @@ for name, path in {files!r}.items():
         assert out["tuned"] == tiled
     else:
         assert out["tuned"] == out["none"] and out["tuned"] != tiled and out["tuned"][len(out["tuned"]) // 2].startswith(untuned)
+
+
+@pytest.mark.parametrize("call", ["mrs_eval_device", "mrs_eval_device_noalloc"])
+@pytest.mark.parametrize("prec,n", [(0, 6145), (0, 20000), (1, 5003), (1, 12800)])
+def test_captured_work_lists_are_kernel_arguments(child, call, prec, n):
+    """A replay reads a captured copy's host memory again, when the call's list is
+    gone (or its staging buffer holds another call's): under capture the list
+    travels in kernel arguments, ahead of the kernels that read it."""
+    out = child(f"""
+rec.rec_symbol.restype = ctypes.c_void_p
+arrays = [buf(3 * {n}) for _ in range(5)]
+def run():
+    log()
+    mrs.{call}(ctx, {n}, *arrays[:3], 0.1, 1.0, {prec}, *arrays[3:], A)
+    return [x.rsplit(" ", 1)[0] if x[0] == "l" else x.split()[0] for x in log()]
+out["eager"] = run()
+eager = ctypes.string_at(rec.rec_symbol(), 1 << 20)
+ctypes.memset(rec.rec_symbol(), 0, 1 << 20)
+ctx = mrs.mrs_context_create(0)
+capturing(A); out["captured"] = run(); capturing(None)
+out["same list"] = [eager == ctypes.string_at(rec.rec_symbol(), 1 << 20), any(eager)]
+""")
+    assert out["same list"] == [True, call == "mrs_eval_device_noalloc"]
+    names = out["captured"]
+    lists = names.count("launch k_store_list")
+    assert lists and names[:lists] == ["launch k_store_list"] * lists and names[lists] == "launch k_pack_aos"
+    assert "copy" not in names and "eventsync" not in names
+    kernels = lambda names: [x for x in names if x.startswith("launch") and x != "launch k_store_list"]
+    assert kernels(names) == kernels(out["eager"]) and "launch k_store_list" not in out["eager"]
